@@ -169,9 +169,11 @@ def _buffers(n_hits, cl, track_cap=1 << 14, object_cap=1024, member_cap=1 << 16)
 
 def _cluster_outputs(b):
     """A ClusterBuffers' tensors, the track and object records split into
-    their integer and floating fields (views)."""
+    their integer and floating fields (views).  The seed search's count of the
+    distances it happened to compute (``work``, which the roofline figures
+    read) is a measurement of the search and no result: it is left out."""
     ft, fo = b.tracks.view(torch.float32), b.objects.view(torch.float32)
-    return dict(counts=b.counts, work=b.work, owner=b.hit_owner, members=b.members, vacc=b.vacc,
+    return dict(counts=b.counts, owner=b.hit_owner, members=b.members, vacc=b.vacc,
                 track_head=b.tracks[:, :7], track_fit=ft[:, 7:13], track_hits=b.tracks[:, 13:],
                 object_head=b.objects[:, :4], object_place=fo[:, 4:7], object_begin=b.objects[:, 7:])
 
