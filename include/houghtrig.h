@@ -136,9 +136,8 @@ typedef struct {
                               member) pairs), 0; a count above INT32_MAX reads INT32_MAX */
   unsigned long long* work;/* [2] device, or NULL: the seed search's work as 64-bit totals:
                               [0] road tests the method defines (as counts[6], unclamped),
-                              [1] float64 circle distances actually computed (members that
-                              pass the float32 pre-filter on lanes still able to reach
-                              min_layers, plus the tied lanes' distance sums) */
+                              [1] float64 circle distances actually computed (the rest of the
+                              road tests are settled in float32) */
 } ht_cluster_out;
 
 typedef struct ht_plan ht_plan;
@@ -365,7 +364,8 @@ int ht_remap_track_hits(ht_track* tracks, int32_t track_cap, const int32_t* coun
  *   HT_STAGE_VOTE     the vote kernel of hough_vote,
  *   HT_STAGE_PEAKS    the kernels of hough_peaks,
  *   HT_STAGE_ASSOC    all of assoc_cluster,
- *   HT_STAGE_MEMBERS  its member sweep (inside HT_STAGE_ASSOC),
+ *   HT_STAGE_MEMBERS  its grouping of the hits, and the member sweep of events that
+ *                     take it (inside HT_STAGE_ASSOC),
  *   HT_STAGE_REFINE   its seed search (inside HT_STAGE_ASSOC).
  * At most `depth` launches per stage are recorded between two reads; later
  * ones are not timed.  ht_profile_read waits for the recorded events, ADDS

@@ -62,14 +62,14 @@ int dalloc(Plan* plan, T** p, size_t n) {
 
 void free_plan(Plan* p) {
   void* ptrs[] = {p->d_kap,       p->d_kapc,      p->d_d0c,       p->d_q,         p->d_t,        p->d_bits,      p->d_tile_cnt,
-                  p->d_tile_off,  p->d_pbits,     p->d_col_first, p->d_hx,       p->d_hy,
+                  p->d_tile_off,  p->d_hx,       p->d_hy,
                   p->d_hq,        p->d_hitB,      p->d_mcount,    p->d_mem,      p->d_cstat,
                   p->d_cgeo,      p->d_chit,      p->d_cnl,      p->d_owner_key, p->d_ctile_cnt,
                   p->d_ctile_off, p->d_trk_peak,  p->d_arc0,     p->d_arcn,     p->d_arci0,    p->d_arcin,      p->d_tunit,      p->d_vacc,
                   p->d_obj_cnt,   p->d_vtile,     p->d_scalars,  p->d_ckl,       p->d_ckh,
                   p->d_cql,       p->d_ctl,       p->d_cqh,      p->d_cth,      p->d_spread,
-                  p->d_cls,       p->d_bkt,       p->d_bkt_off,  p->d_hkey,     p->d_shit,
-                  p->d_sphi};
+                  p->d_lay,       p->d_bkt,       p->d_bkt_off,  p->d_hkey,     p->d_srec,
+                  p->d_srad,      p->d_sphi,      p->d_sxy,       p->d_sq};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
 }
@@ -154,7 +154,6 @@ int ht_plan_create(const ht_grid* grid, const ht_limits* lim, ht_plan** out) {
   }
   const size_t nh = (size_t)lim->max_hits;
   const size_t np = (size_t)lim->max_peaks;
-  const size_t words = (size_t)p->n_tiles * 8 + 2;
   const int64_t ctiles = ((int64_t)np + 255) / 256;
   if (rc == HT_OK) rc = dalloc(p, &p->d_kap, (size_t)g.n_qpt);
   if (rc == HT_OK) rc = dalloc(p, &p->d_kapc, (size_t)g.n_qpt);
@@ -165,8 +164,6 @@ int ht_plan_create(const ht_grid* grid, const ht_limits* lim, ht_plan** out) {
   if (rc == HT_OK) rc = dalloc(p, &p->d_bits, (size_t)((p->n_tiles + 3) / 4) * 32 + 2);
   if (rc == HT_OK) rc = dalloc(p, &p->d_tile_cnt, (size_t)p->n_tiles);
   if (rc == HT_OK) rc = dalloc(p, &p->d_tile_off, (size_t)p->n_tiles);
-  if (rc == HT_OK) rc = dalloc(p, &p->d_pbits, words);
-  if (rc == HT_OK) rc = dalloc(p, &p->d_col_first, ncol);
   if (rc == HT_OK) rc = dalloc(p, &p->d_hx, nh);
   if (rc == HT_OK) rc = dalloc(p, &p->d_hy, nh);
   if (rc == HT_OK) rc = dalloc(p, &p->d_hq, nh);
@@ -191,12 +188,15 @@ int ht_plan_create(const ht_grid* grid, const ht_limits* lim, ht_plan** out) {
   if (rc == HT_OK) rc = dalloc(p, &p->d_vtile, (size_t)lim->max_vertex_cells / 1024 + 1);
   if (rc == HT_OK) rc = dalloc(p, &p->d_scalars, 16);
   if (rc == HT_OK) rc = dalloc(p, &p->d_spread, ht::kSpreadWords);
-  if (rc == HT_OK) rc = dalloc(p, &p->d_cls, (size_t)ht::kClsSlots);
+  if (rc == HT_OK) rc = dalloc(p, &p->d_lay, (size_t)3 * HT_MAX_LAYERS);
   if (rc == HT_OK) rc = dalloc(p, &p->d_bkt, (size_t)ht::kBucketKeys);
-  if (rc == HT_OK) rc = dalloc(p, &p->d_bkt_off, (size_t)ht::kBucketKeys + 1);
+  if (rc == HT_OK) rc = dalloc(p, &p->d_bkt_off, (size_t)HT_MAX_LAYERS * ht::kRunRow);
   if (rc == HT_OK) rc = dalloc(p, &p->d_hkey, nh);
-  if (rc == HT_OK) rc = dalloc(p, &p->d_shit, nh);
-  if (rc == HT_OK) rc = dalloc(p, &p->d_sphi, nh);
+  if (rc == HT_OK) rc = dalloc(p, &p->d_srec, 2 * nh);
+  if (rc == HT_OK) rc = dalloc(p, &p->d_srad, 2 * nh);
+  if (rc == HT_OK) rc = dalloc(p, &p->d_sphi, 2 * nh);
+  if (rc == HT_OK) rc = dalloc(p, &p->d_sxy, 2 * nh);
+  if (rc == HT_OK) rc = dalloc(p, &p->d_sq, 2 * nh);
   // band-vote corner tables: (smallest kappa, lower d0 edge) and (largest
   // kappa, upper d0 edge) of every column
   if (rc == HT_OK) rc = dalloc(p, &p->d_ckl, (size_t)g.n_qpt);

@@ -8,22 +8,21 @@
 //   prep      per hit: float64 Cartesian coordinates (canonical sincos) and
 //             a float32 record; ownership keys cleared; counters and the
 //             vertex accumulator zeroed;
-//   mark      peak bitmap and the first peak index of every column (and,
-//             with an accumulator, the count of hits beyond the layer
-//             range);
-//   members   by candidate: the hits grouped by (radius class, azimuth
-//             bucket) with a counting sort (the classes in the mark launch,
-//             then bcount, scan, bscatter), then one wave per candidate
-//             tests the hits of the buckets its member window reaches for
-//             each class (mcand); events with
-//             more distinct radii than the classes hold use a sweep shaped
-//             like the vote instead (member_kernel);
-//   refine    one wave per candidate: member layers, seed layers, the
-//             seed_k nearest members of each seed layer by rank, then one
-//             seed combination per lane (<= 64) scored against the members
-//             in LDS, smallest non-seed layers first; the best lane wins by
-//             (inliers, sum, index) and offers each inlier hit its 64-bit
-//             ownership key (atomicMax); totals go to spread counters;
+//   runs      each layer's radius range and hit count; the hits grouped by
+//             (layer, azimuth bucket) with a counting sort (layers, bcount,
+//             bscan, bscatter; small events: prep and runs in one launch,
+//             prep_small).  Events with a layer of widely spread radii take the
+//             sweep instead;
+//   reject,   the seed search on the layer runs, one wave per candidate: member
+//   runs      layers, seed layers, the seed_k nearest members of each seed
+//             layer by rank, then one seed combination per lane (<= 64) tested
+//             against the layers' hits, smallest non-seed layers first; the best
+//             lane wins by (inliers, sum, index) and offers each inlier hit its
+//             64-bit ownership key (atomicMax); totals go to spread counters.
+//             reject_kernel settles the many candidates that fail in float32;
+//   members,  events that take the sweep only: the members of every candidate by
+//   refine    a sweep shaped like the vote (member_kernel), then the seed search
+//             on those lists;
 //   survive   ordered compaction of the candidates owning >= min_layers
 //             hits into the track list (tile counts and their sums per 64
 //             tiles, then each tile places its survivors);
@@ -53,14 +52,15 @@ constexpr int kSweepWaves = 16;
 constexpr int kSweepThreads = kSweepWaves * kWave;
 constexpr int kMaxMembers = 1024; // largest member_cap (LDS slots per wave in refine)
 constexpr int kGridCap = 8192;    // grid-stride launches use at most this many blocks
+constexpr int kSweepGrid = 4096;  // ... and the seed search behind the member sweep
 
 // S_NBAD: valid hits whose layer is HT_MAX_LAYERS or more (they vote but are no members)
 constexpr float kPiF = 3.14159265358979f;
 constexpr float k2PiF = 6.28318530717959f;
 
-// S_MODE: 1 when the member lists are built by candidate (see radius_classes);
-// S_COVER: set when the hits have more distinct radii than the hash holds
-enum { S_NP = 0, S_NBAD = 2, S_NTRK = 3, S_NOBJ = 4, S_NMEM = 5, S_MODE = 6, S_COVER = 7 };
+// S_MODE: 1 when the seed search reads the layer runs (see layer_mode)
+// S_QUEUE: candidates that reject_kernel could not reject, listed in mcount
+enum { S_NP = 0, S_NBAD = 2, S_NTRK = 3, S_NOBJ = 4, S_NMEM = 5, S_MODE = 6, S_QUEUE = 7 };
 // The seed search's totals (road tests, refined candidates, candidates over
 // member_cap, (candidate, member) pairs within it) are summed per workgroup
 // and added to kSpread counters in separate 128-byte lines, chosen by
@@ -278,8 +278,6 @@ struct AssocArgs {
   // cfg
   ht_cluster_cfg cfg;
   // scratch
-  uint32_t* pbits;
-  int32_t* col_first;
   int32_t* mcount;
   // member_cap slots per candidate: hit | layer << 16, |x - cell centre| bits
   uint2* pool;
@@ -301,13 +299,16 @@ struct AssocArgs {
   int32_t* vtile;  // vertex peaks per 1024-cell tile
   int32_t* sc;  // device scalars
   unsigned long long* spread;  // [kSpreadWords] spread counters
-  // member lists by candidate
-  uint32_t* cls;       // hash of the radii
-  int32_t* bkt;        // hits per (class, bucket)
+  // layer runs
+  int32_t* lay;        // smallest and largest radius (float bits) and hits of each layer
+  int32_t* bkt;        // hits per (layer, bucket)
   int32_t* bkt_off;    // bucket starts
-  int32_t* hkey;       // each hit's bucket key | slot << 14, or -1
-  int32_t* shit;       // hits in bucket order (hit | layer << 16)
-  float* sphi;         // their azimuths
+  int32_t* hkey;       // each hit's bucket key | slot << 15, or -1
+  float4* srec;        // by bucket: x, y (float32), azimuth, hit
+  float4* srad;        // r, 1/r, the window's hit part
+  float* sphi;         // azimuth
+  double2* sxy;        // x, y
+  double* sq;          // x^2+y^2
   // outputs
   ht_cluster_out out;
 };
@@ -338,78 +339,58 @@ __device__ __forceinline__ int hits_of(const AssocArgs& A) {
 }
 
 // ---- prep ------------------------------------------------------------------
+// a hit's coordinates and record; returns whether it is valid
+__device__ __forceinline__ bool prep_hit(const AssocArgs& A, int h, double* x, double* y, double* q,
+                                         float4* rec) {
+  const float r = A.r[h], ph = A.phi[h];
+  const bool ok = hit_ok(r, ph);
+  double s, c;
+  csincos(ok ? (double)ph : 0.0, &s, &c);
+  const double rr = (double)r;
+  *x = rr * c;
+  *y = rr * s;
+  *q = *x * *x + *y * *y;
+  *rec = make_float4((float)*x, (float)*y, r, ph);
+  A.hx[h] = *x;
+  A.hy[h] = *y;
+  A.hq[h] = *q;
+  A.hitB[h] = *rec;
+  A.owner_key[h] = 0ull;
+  A.out.hit_owner[h] = -1;
+  return ok;
+}
+
+// the candidates: the peaks of the list that are within its capacity
+__device__ __forceinline__ int peaks_of(const AssocArgs& A) {
+  const int np = *A.n_peaks;
+  return np < 0 ? 0 : (np > A.peak_cap ? A.peak_cap : np);
+}
+
+// what every call clears, by threads t0, t0 + step, ..
+__device__ __forceinline__ void prep_clear(const AssocArgs& A, int surv_groups, int64_t t0,
+                                           int64_t step) {
+  for (int64_t w = t0; w < kSpreadWords; w += step) A.spread[w] = 0ull;
+  for (int64_t w = t0; w < surv_groups; w += step) A.ctile_off[w] = 0;
+  const int ncell_v = A.cfg.n_rho * A.cfg.n_theta;
+  for (int64_t v = t0; v < ncell_v; v += step) A.vacc[v] = 0;
+}
+
 template <int NB>
-__global__ void init_kernel(AssocBatch<NB> AB, int words, int surv_groups) {
+__global__ void init_kernel(AssocBatch<NB> AB, int surv_groups) {
   const AssocArgs& A = event_args(AB);
   const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  if (tid < 16) A.sc[tid] = 0;
-  for (int64_t w = tid; w < kSpreadWords; w += stride) A.spread[w] = 0ull;
-  if (tid == 0) {
-    int np = *A.n_peaks;
-    np = np < 0 ? 0 : (np > A.peak_cap ? A.peak_cap : np);
-    A.sc[S_NP] = np;
-  }
-  for (int64_t w = tid; w < words; w += stride) A.pbits[w] = 0u;
-  for (int64_t w = tid; w < kClsSlots; w += stride) A.cls[w] = kRadEmpty;
+  prep_clear(A, surv_groups, tid, stride);
+  if (tid < 16) A.sc[tid] = tid == S_NP ? peaks_of(A) : 0;
+  if (tid < 3 * HT_MAX_LAYERS) A.lay[tid] = tid < HT_MAX_LAYERS ? 0x7fffffff : 0;
   for (int64_t w = tid; w < kBucketKeys; w += stride) A.bkt[w] = 0;
-  for (int64_t w = tid; w < surv_groups; w += stride) A.ctile_off[w] = 0;
   const int n_hits = hits_of(A);
   for (int64_t h = tid; h < n_hits; h += stride) {
-    const float r = A.r[h], ph = A.phi[h];
-    const bool ok = hit_ok(r, ph);
-    double s, c;
-    csincos(ok ? (double)ph : 0.0, &s, &c);
-    const double rr = (double)r;
-    const double x = rr * c;
-    const double y = rr * s;
-    const double q = x * x + y * y;
-    A.hx[h] = x;
-    A.hy[h] = y;
-    A.hq[h] = q;
-    A.hitB[h] = make_float4((float)x, (float)y, r, ph);
-    A.owner_key[h] = 0ull;
-    A.out.hit_owner[h] = -1;
-  }
-  const int ncell_v = A.cfg.n_rho * A.cfg.n_theta;
-  for (int64_t v = tid; v < ncell_v; v += stride) A.vacc[v] = 0;
-}
-
-__device__ void mark_peaks(const AssocArgs& A, int bid, int nblk) {
-  if (A.acc) {
-    const int n_hits = hits_of(A);
-    for (int h = bid * blockDim.x + threadIdx.x; h < n_hits; h += nblk * blockDim.x)
-      if (A.layer[h] >= HT_MAX_LAYERS && hit_ok(A.r[h], A.phi[h])) atomicAdd(&A.sc[S_NBAD], 1);
-  }
-  const int np = n_cands(A);
-  for (int p = bid * blockDim.x + threadIdx.x; p < np; p += nblk * blockDim.x) {
-    A.mcount[p] = 0;
-    const int lin = A.peaks[p].lin;
-    if (lin < 0 || lin >= A.n_cells) continue;
-    atomicOr(&A.pbits[lin >> 5], 1u << (lin & 31));
-    const int col = lin / A.n_phi;
-    bool first = p == 0;
-    if (!first) {
-      const int pl = A.peaks[p - 1].lin;
-      first = pl < 0 || pl >= A.n_cells || pl / A.n_phi != col;
-    }
-    if (first) A.col_first[col] = p;
+    double x, y, q;
+    float4 rec;
+    (void)prep_hit(A, (int)h, &x, &y, &q, &rec);
   }
 }
-
-// ---- member lists by candidate -------------------------------------------------
-// A hit of radius r is a member of the candidate at cell (i, j, k) when the
-// float32 coordinate x = ((phi - s) - phi_lo) invw of the vote (s the arcsine
-// of column (j, k) at radius r) lies within the member window w(r, j, k) of
-// the cell centre, on the periodic image of x nearest the cell.  x is a
-// monotone function of the azimuth, so a candidate's members of one radius
-// are the hits of that radius in one interval of azimuth (periodic).  When
-// the event's member-eligible hits (valid, layer below HT_MAX_LAYERS) have at
-// most kMaxClasses distinct radii, they are bucketed by (radius class,
-// azimuth bucket) and one wave per candidate tests, for each radius, only
-// the hits of the buckets its interval reaches (one bucket of margin on each
-// side, far above every rounding), with the very operations of the sweep
-// below, and writes its member list contiguously.  Otherwise the sweep runs.
 
 // inclusive prefix sum over the wave
 __device__ __forceinline__ int wave_incl_scan_i32(int v, int lane) {
@@ -421,21 +402,21 @@ __device__ __forceinline__ int wave_incl_scan_i32(int v, int lane) {
   return v;
 }
 
-// insert float bits k into a linear-probing hash of kClsSlots (LDS or
-// global); false when the hash is full
-__device__ __forceinline__ bool hash_insert(uint32_t* key, uint32_t k) {
-  uint32_t slot = rad_hash(k);
-  for (int p = 0; p < kClsSlots; ++p) {
-    const uint32_t v = __hip_atomic_load(&key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (v == k) return true;
-    if (v == kRadEmpty) {
-      const uint32_t old = atomicCAS(&key[slot], kRadEmpty, k);
-      if (old == kRadEmpty || old == k) return true;
-    }
-    slot = (slot + 1) & (kClsSlots - 1);
-  }
-  return false;
-}
+// ---- layer runs -----------------------------------------------------------------
+// A hit of radius r is a member of the candidate at cell (i, j, k) when the
+// float32 coordinate x = ((phi - s) - phi_lo) invw of the vote (s the arcsine
+// of column (j, k) at radius r) lies within the member window w(r, j, k) of
+// the cell centre, on the periodic image of x nearest the cell: for one radius
+// the hits of one (periodic) interval of azimuth.  A barrel layer's hits share
+// one radius or lie within a narrow range of radii, so a candidate's members
+// on a layer lie in one interval, and so do the hits on a seed circle's road.
+// The member-eligible hits (valid, layer below HT_MAX_LAYERS) are therefore
+// sorted by (layer, azimuth bucket), and one wave per candidate reads what it
+// needs of each layer's run of buckets (runs_kernel): no member lists are
+// written.  Events with a layer whose radii spread over more than a quarter
+// take the sweep (member_kernel, refine_kernel) instead: there a candidate's
+// interval is no longer narrow.
+constexpr float kLayerSpread = 1.25f;
 
 // azimuth in [-pi, pi) (up to rounding) and its bucket, the same function for
 // hits and interval ends (monotone in the wrapped azimuth)
@@ -450,248 +431,253 @@ __device__ __forceinline__ int bucket_of(float aw) {
   return t < 1.0f ? 0 : (t >= (float)(kBuckets - 1) ? kBuckets - 1 : (int)t);
 }
 
-// the event's distinct radii (each workgroup's, then merged into the event's hash)
-__device__ void radius_classes(const AssocArgs& A, int bid, int nblk) {
-  __shared__ uint32_t key[kClsSlots];
-  __shared__ int over;
-  if (threadIdx.x < kClsSlots) key[threadIdx.x] = kRadEmpty;
-  if (threadIdx.x == 0) over = 0;
+// each layer's radius range and hit count (each workgroup's, then the event's)
+template <int NB>
+__global__ __launch_bounds__(256) void layers_kernel(AssocBatch<NB> AB) {
+  const AssocArgs& A = event_args(AB);
+  __shared__ int32_t lo[HT_MAX_LAYERS], hi[HT_MAX_LAYERS], cnt[HT_MAX_LAYERS];
+  if (threadIdx.x < HT_MAX_LAYERS) {
+    lo[threadIdx.x] = 0x7fffffff;
+    hi[threadIdx.x] = 0;
+    cnt[threadIdx.x] = 0;
+  }
   __syncthreads();
   const int n = hits_of(A);
-  uint32_t last = kRadEmpty;
-  for (int h = bid * blockDim.x + threadIdx.x; h < n; h += nblk * blockDim.x) {
+  for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < n; h += gridDim.x * blockDim.x) {
     const float rv = A.r[h];
-    if (!hit_ok(rv, A.phi[h]) || A.layer[h] >= HT_MAX_LAYERS) continue;
-    const uint32_t k = __float_as_uint(rv);
-    if (k == last) continue;
-    last = k;
-    if (!hash_insert(key, k)) over = 1;
+    const int L = A.layer[h];
+    if (!hit_ok(rv, A.phi[h])) continue;
+    if (L >= HT_MAX_LAYERS) {
+      atomicAdd(&A.sc[S_NBAD], 1);
+      continue;
+    }
+    const int32_t k = __float_as_int(rv);  // positive: orders like the radius
+    if (k < lo[L]) atomicMin(&lo[L], k);
+    if (k > hi[L]) atomicMax(&hi[L], k);
+    atomicAdd(&cnt[L], 1);
   }
   __syncthreads();
-  if (threadIdx.x < kClsSlots) {
-    const uint32_t k = key[threadIdx.x];
-    if (k != kRadEmpty && !hash_insert(A.cls, k)) over = 1;
+  if (threadIdx.x < HT_MAX_LAYERS && cnt[threadIdx.x] > 0) {
+    atomicMin(&A.lay[threadIdx.x], lo[threadIdx.x]);
+    atomicMax(&A.lay[HT_MAX_LAYERS + threadIdx.x], hi[threadIdx.x]);
+    atomicAdd(&A.lay[2 * HT_MAX_LAYERS + threadIdx.x], cnt[threadIdx.x]);
   }
-  __syncthreads();
-  if (threadIdx.x == 0 && over) atomicOr(&A.sc[S_COVER], 1);
 }
 
-// the peak marks (workgroups below mark_blocks, 256 threads) and the radius
-// classes (the rest) in one launch
-template <int NB>
-__global__ __launch_bounds__(256) void mark_kernel(AssocBatch<NB> AB, int mark_blocks) {
-  const AssocArgs& A = event_args(AB);
-  if ((int)blockIdx.x < mark_blocks)
-    mark_peaks(A, blockIdx.x, mark_blocks);
-  else
-    radius_classes(A, blockIdx.x - mark_blocks, gridDim.x - mark_blocks);
-}
-
-// class index of each hash slot (rank among the filled slots, the same in
-// every workgroup); returns the class count, or -1 when the lists are built
-// by the sweep.  Whole workgroup; ends with a barrier.
-__device__ __forceinline__ int class_table(const AssocArgs& A, int32_t* idx, float* cr) {
-  __shared__ int ncls;
-  if (threadIdx.x < kWave) {
-    const int lane = threadIdx.x;
-    static_assert(kClsSlots == kWave, "one hash slot per lane");
-    const uint32_t k = A.cls[lane];
-    const bool full = k != kRadEmpty;
-    const uint64_t m = __ballot(full);
-    const int rank = __popcll(m & ((1ull << lane) - 1ull));
-    const int n = __popcll(m);
-    const bool on = n <= kMaxClasses && A.sc[S_COVER] == 0;
-    idx[lane] = full && on ? rank : -1;
-    if (full && on) cr[rank] = __uint_as_float(k);
-    if (lane == 0) ncls = on ? n : -1;
-  }
-  __syncthreads();
-  return ncls;
-}
-
-__device__ __forceinline__ int class_of(const AssocArgs& A, const int32_t* idx, uint32_t k) {
-  uint32_t slot = rad_hash(k);
-  for (int p = 0; p < kClsSlots; ++p) {
-    const uint32_t v = A.cls[slot];
-    if (v == k) return idx[slot];
-    if (v == kRadEmpty) return -1;
-    slot = (slot + 1) & (kClsSlots - 1);
-  }
-  return -1;
+// whether the event's layers are narrow enough for the runs (wave-uniform)
+__device__ __forceinline__ bool layer_mode(const AssocArgs& A) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int L = lane & (HT_MAX_LAYERS - 1);
+  const float lo = __int_as_float(A.lay[L]), hi = __int_as_float(A.lay[HT_MAX_LAYERS + L]);
+  const bool wide = A.lay[2 * HT_MAX_LAYERS + L] > 0 && !(hi <= kLayerSpread * lo);
+  return __ballot(wide) == 0ull;
 }
 
 // each member-eligible hit's bucket and slot in it
 template <int NB>
 __global__ __launch_bounds__(256) void bcount_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
-  __shared__ int32_t idx[kClsSlots];
-  __shared__ float cr[kMaxClasses];
-  const int ncls = class_table(A, idx, cr);
-  if (blockIdx.x == 0 && threadIdx.x == 0) A.sc[S_MODE] = ncls >= 0 ? 1 : 0;
-  if (ncls < 0) return;
+  const bool on = layer_mode(A);
+  if (blockIdx.x == 0 && threadIdx.x == 0) A.sc[S_MODE] = on ? 1 : 0;
+  const int t0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  if (!on) return;
   const int n = hits_of(A);
-  for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < n; h += gridDim.x * blockDim.x) {
+  for (int h = t0; h < n; h += step) {
     const float rv = A.r[h], ph = A.phi[h];
+    const int L = A.layer[h];
     int key = -1;
-    if (hit_ok(rv, ph) && A.layer[h] < HT_MAX_LAYERS) {
-      const int c = class_of(A, idx, __float_as_uint(rv));
-      if (c >= 0) {
-        const int b = c * kBuckets + bucket_of(wrap_pi_f(ph));
-        key = b | (atomicAdd(&A.bkt[b], 1) << 14);
-      }
+    if (hit_ok(rv, ph) && L < HT_MAX_LAYERS) {
+      const int b = L * kBuckets + bucket_of(wrap_pi_f(ph));
+      key = b | (atomicAdd(&A.bkt[b], 1) << 15);  // b < 2^15, slots < 2^16
     }
     A.hkey[h] = key;
   }
 }
 
+// one workgroup per layer: its row of bucket starts, both copies of its hits
+template <int NB>
+__global__ __launch_bounds__(256) void bscan_kernel(AssocBatch<NB> AB) {
+  const AssocArgs& A = event_args(AB);
+  if (A.sc[S_MODE] == 0) return;
+  __shared__ int32_t wsum[4];
+  constexpr int G = kBuckets / 256;  // buckets per thread
+  static_assert(G % 4 == 0, "whole 16-byte vectors per thread");
+  const int L = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int base = 0, cnt = 0;
+  for (int l = 0; l <= L; ++l) {
+    base += 2 * cnt;
+    cnt = A.lay[2 * HT_MAX_LAYERS + l];
+  }
+  int32_t c[G];
+  int sum = 0;
+#pragma unroll
+  for (int g = 0; g < G; g += 4) {
+    const int4 v = *reinterpret_cast<const int4*>(A.bkt + L * kBuckets + (int)threadIdx.x * G + g);
+    c[g] = v.x; c[g + 1] = v.y; c[g + 2] = v.z; c[g + 3] = v.w;
+    sum += v.x + v.y + v.z + v.w;
+  }
+  const int incl = wave_incl_scan_i32(sum, lane);
+  if (lane == kWave - 1) wsum[wave] = incl;
+  __syncthreads();
+  int run = base + incl - sum;
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+  int32_t* row = A.bkt_off + L * kRunRow + (int)threadIdx.x * G;
+#pragma unroll
+  for (int g = 0; g < G; g += 4) {
+    int4 o;
+    o.x = run; run += c[g];
+    o.y = run; run += c[g + 1];
+    o.z = run; run += c[g + 2];
+    o.w = run; run += c[g + 3];
+    *reinterpret_cast<int4*>(row + g) = o;
+    o.x += cnt; o.y += cnt; o.z += cnt; o.w += cnt;
+    *reinterpret_cast<int4*>(row + kBuckets + g) = o;
+  }
+  if (threadIdx.x == 255) A.bkt_off[L * kRunRow + 2 * kBuckets] = run + cnt;
+}
+
+// a hit's records at place e of its layer's row, and in the second copy cnt behind
+__device__ __forceinline__ void put_records(const AssocArgs& A, int h, int e, int cnt, double x,
+                                            double y, double q, float4 hb) {
+  const float ir = 1.0f / hb.z;
+  const float4 rec = make_float4(hb.x, hb.y, hb.w, __int_as_float(h));
+  const float4 rad = make_float4(hb.z, ir, member_e5(hb.z, ir, A.hd0, A.hk, A.invw), 0.0f);
+#pragma unroll
+  for (int copy = 0; copy < 2; ++copy, e += cnt) {
+    A.srec[e] = rec;
+    A.srad[e] = rad;
+    A.sphi[e] = hb.w;
+    A.sxy[e] = make_double2(x, y);
+    A.sq[e] = q;
+  }
+}
+
+// the hits' records in bucket order, both copies; events that take the sweep get
+// their member counts cleared instead
 template <int NB>
 __global__ __launch_bounds__(256) void bscatter_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
-  if (A.sc[S_MODE] == 0) return;
+  if (A.sc[S_MODE] == 0) {
+    const int np = n_cands(A);
+    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < np; q += gridDim.x * blockDim.x)
+      A.mcount[q] = 0;
+    return;
+  }
   const int n = hits_of(A);
   for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < n; h += gridDim.x * blockDim.x) {
     const int key = A.hkey[h];
     if (key < 0) continue;
-    const int e = A.bkt_off[key & (kBucketKeys - 1)] + (key >> 14);
-    A.shit[e] = h | ((int)A.layer[h] << 16);  // a member entry's first word
-    A.sphi[e] = A.phi[h];
+    const int L = (key & (kBucketKeys - 1)) / kBuckets, b = key & (kBuckets - 1);
+    const int e = A.bkt_off[L * kRunRow + b] + (key >> 15);
+    put_records(A, h, e, A.lay[2 * HT_MAX_LAYERS + L], A.hx[h], A.hy[h], A.hq[h], A.hitB[h]);
   }
 }
 
-// One wave per candidate: lane c < the class count works out class c's
-// arcsine, window and bucket ranges, then the wave tests the hits of each
-// class's ranges, 64 at a time, and appends the members (ballot prefix).
+// Small events (at most kPrepHits hits of the bound): everything above in one
+// launch, the sort by one workgroup per event with its bucket counters in LDS.
+// Five launches of 2 to 5 us each, nothing in them but latency, become one: 8.5 us
+// instead of 18 at 250 hits, 14 instead of 22 at 1500; at 3600 hits one workgroup
+// would take 28 us and the five launches 27.  Workgroup 0 sorts, the others clear.
+constexpr int kPrepHits = 2048;
+constexpr int kPrepThreads = 1024;
 template <int NB>
-__global__ __launch_bounds__(256) void mcand_kernel(AssocBatch<NB> AB) {
+__global__ __launch_bounds__(kPrepThreads) void prep_small_kernel(AssocBatch<NB> AB,
+                                                                  int surv_groups) {
   const AssocArgs& A = event_args(AB);
-  __shared__ int32_t idx[kClsSlots];
-  __shared__ float cr[kMaxClasses];
-  __shared__ float cir[kMaxClasses], ce5[kMaxClasses];  // 1 / r and the window's hit part
-  const int ncls = class_table(A, idx, cr);
-  if (ncls < 0) return;
-  if ((int)threadIdx.x < ncls) {
-    const float ir = 1.0f / cr[threadIdx.x];
-    cir[threadIdx.x] = ir;
-    ce5[threadIdx.x] = member_e5(cr[threadIdx.x], ir, A.hd0, A.hk, A.invw);
+  __shared__ uint32_t cnt2[kBucketKeys / 2];  // bucket counts, then starts within the layer, two a word
+  __shared__ int32_t lo[HT_MAX_LAYERS], hi[HT_MAX_LAYERS], cnt[HT_MAX_LAYERS];
+  __shared__ int32_t nbad;
+  if (blockIdx.x > 0) {
+    prep_clear(A, surv_groups, (int64_t)(blockIdx.x - 1) * kPrepThreads + threadIdx.x,
+               (int64_t)(gridDim.x - 1) * kPrepThreads);
+    return;
+  }
+  constexpr int kPer = kPrepHits / kPrepThreads;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+  const int n = hits_of(A);
+  for (int w = tid; w < kBucketKeys / 2; w += kPrepThreads) cnt2[w] = 0u;
+  if (tid < HT_MAX_LAYERS) {
+    lo[tid] = 0x7fffffff;
+    hi[tid] = 0;
+    cnt[tid] = 0;
+  }
+  if (tid == 0) nbad = 0;
+  __syncthreads();
+  double x[kPer], y[kPer], q[kPer];
+  float4 rec[kPer];
+  int key[kPer];  // bucket key | slot << 15, or -1
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int h = tid + u * kPrepThreads;
+    key[u] = -1;
+    if (h >= n) continue;
+    const int L = A.layer[h];
+    if (!prep_hit(A, h, &x[u], &y[u], &q[u], &rec[u])) continue;
+    if (L >= HT_MAX_LAYERS) {
+      atomicAdd(&nbad, 1);
+      continue;
+    }
+    const int32_t k = __float_as_int(rec[u].z);
+    if (k < lo[L]) atomicMin(&lo[L], k);
+    if (k > hi[L]) atomicMax(&hi[L], k);
+    atomicAdd(&cnt[L], 1);
+    const int b = L * kBuckets + bucket_of(wrap_pi_f(rec[u].w));
+    const int sh = (b & 1) * 16;
+    const uint32_t old = atomicAdd(&cnt2[b >> 1], 1u << sh);
+    key[u] = b | ((int)((old >> sh) & 0xffffu) << 15);
   }
   __syncthreads();
-  const int lane = threadIdx.x & (kWave - 1);
-  const int waves = (int)(blockDim.x / kWave);
-  const int np = n_cands(A);
-  const int cap = A.cfg.member_cap;
-  const int n_phi = A.n_phi;
-  const float wbase = 0.5f + (float)A.cfg.win_bins;
-  // bin width for the bucket ranges only (their margin is a whole bucket,
-  // far above this product's rounding)
-  const float binw = 1.0f / A.invw;
-  for (int p = blockIdx.x * waves + (int)(threadIdx.x / kWave); p < np; p += gridDim.x * waves) {
-    const int lin = A.peaks[p].lin;
-    if (lin < 0 || lin >= A.n_cells) continue;  // no members (mark_kernel set the count to 0)
-    const int col = lin / n_phi;
-    const int i = lin - col * n_phi;
-    const int j = col % A.n_qpt;
-    const int k = col / A.n_qpt;
-    float s = __builtin_nanf(""), w = 0.0f;
-    int st0 = 0, en0 = 0, st1 = 0, en1 = 0;
-    if (lane < ncls) {
-      const float rv = cr[lane];
-      const float ir = cir[lane];
-      float x = 0.0f, u = 0.0f;
-      const bool ok = phi0_coord(rv * rv, ir, 0.0f, A.kap[j], A.qt[(size_t)k * A.n_qpt + j],
-                                 A.tt[(size_t)k * A.n_qpt + j], A.phi_lo, A.invw, &x, &u);
-      if (ok) {
-        s = asin_f(u);
-        w = member_window(ce5[lane], u, wbase);
-        // azimuths whose x lies within w of the cell centre, as bucket
-        // coordinates: [lo, lo + len] (periodic), one bucket of margin
-        const float xc = (float)i + 0.5f;
-        const float a = ((xc - w) * binw + A.phi_lo) + s;
-        const float lo = bucket_coord(wrap_pi_f(a)) - 1.0f;
-        const float len = 2.0f * w * binw * ((float)kBuckets / k2PiF) + 2.0f;
-        const int base = lane * kBuckets;
-        if (!(len < (float)(kBuckets - 2)) || !(lo == lo)) {
-          st0 = A.bkt_off[base];
-          en0 = A.bkt_off[base + kBuckets];
-        } else {
-          const int b0 = (int)floorf(lo);
-          const int b1 = (int)floorf(lo + len) + 1;  // one past the last bucket
-          // b0 in [-2, kBuckets], b1 - b0 < kBuckets
-          const int c0 = b0 < 0 ? b0 + kBuckets : (b0 >= kBuckets ? b0 - kBuckets : b0);
-          const int c1 = c0 + (b1 - b0);
-          if (c1 <= kBuckets) {
-            st0 = A.bkt_off[base + c0];
-            en0 = A.bkt_off[base + c1];
-          } else {
-            st0 = A.bkt_off[base + c0];
-            en0 = A.bkt_off[base + kBuckets];
-            st1 = A.bkt_off[base];
-            en1 = A.bkt_off[base + c1 - kBuckets];
-          }
-        }
+  bool on;
+  {
+    const int L = lane & (HT_MAX_LAYERS - 1);
+    const bool wide = cnt[L] > 0 && !(__int_as_float(hi[L]) <= kLayerSpread * __int_as_float(lo[L]));
+    on = __ballot(wide) == 0ull;
+  }
+  if (tid < 3 * HT_MAX_LAYERS)
+    A.lay[tid] = tid < HT_MAX_LAYERS ? lo[tid]
+                                     : (tid < 2 * HT_MAX_LAYERS ? hi[tid - HT_MAX_LAYERS]
+                                                                : cnt[tid - 2 * HT_MAX_LAYERS]);
+  if (tid < 16)
+    A.sc[tid] = tid == S_NP ? peaks_of(A) : (tid == S_MODE ? (on ? 1 : 0) : (tid == S_NBAD ? nbad : 0));
+  if (!on) {
+    const int np = peaks_of(A);
+    for (int p = tid; p < np; p += kPrepThreads) A.mcount[p] = 0;
+    return;
+  }
+  // one wave per layer: its row of bucket starts, 128 buckets at a time
+  static_assert(kPrepThreads / kWave == HT_MAX_LAYERS, "one wave per layer");
+  {
+    const int L = wave;
+    int base = 0;
+    for (int l = 0; l < L; ++l) base += 2 * cnt[l];
+    const int c = cnt[L];
+    if (c > 0) {
+      int run = base;
+      int32_t* row = A.bkt_off + L * kRunRow;
+      for (int b0 = 0; b0 < kBuckets; b0 += 2 * kWave) {
+        const uint32_t w = cnt2[(L * kBuckets + b0) / 2 + lane];
+        const int a = (int)(w & 0xffffu), b = (int)(w >> 16);
+        const int incl = wave_incl_scan_i32(a + b, lane);
+        const int first = run + incl - a - b;
+        cnt2[(L * kBuckets + b0) / 2 + lane] =
+            (uint32_t)(first - base) | ((uint32_t)(first + a - base) << 16);
+        *reinterpret_cast<int2*>(row + b0 + 2 * lane) = make_int2(first, first + a);
+        *reinterpret_cast<int2*>(row + kBuckets + b0 + 2 * lane) =
+            make_int2(first + c, first + a + c);
+        run += __builtin_amdgcn_readlane(incl, kWave - 1);
       }
+      if (lane == 0) row[2 * kBuckets] = run + c;
     }
-    // The classes' ranges, range q = 2 c + part held by lane q, laid end to
-    // end: a sparse event's candidate (a few hits per class) reads them 64
-    // hits at a time whatever their lengths.
-    const int nr = 2 * ncls;
-    const int qc = lane >> 1;
-    const int rst0 = __shfl(st0, qc, kWave), ren0 = __shfl(en0, qc, kWave);
-    const int rst1 = __shfl(st1, qc, kWave), ren1 = __shfl(en1, qc, kWave);
-    const float rs = __shfl(s, qc, kWave);
-    const int rst = (lane & 1) ? rst1 : rst0;
-    const int rlen = lane < nr && rs == rs ? ((lane & 1) ? ren1 - rst1 : ren0 - rst0) : 0;
-    const int rend = wave_incl_scan_i32(rlen, lane);  // end of range q in the laid-out order
-    const int rbase = rst - (rend - rlen);  // position t of range q is hit rbase + t
-    const int total = __builtin_amdgcn_readlane(rend, kWave - 1);
-    int cnt = 0;
-    uint2* pool = A.pool + (size_t)p * cap;
-    auto test = [&](int e, bool in, float sc, float wc) {
-      bool mem = false;
-      int h = 0;
-      float adx = 0.0f;
-      if (in) {
-        h = A.shit[e];
-        const float x = ((A.sphi[e] - sc) - A.phi_lo) * A.invw;
-        adx = cell_adx(x, i, n_phi);
-        mem = adx <= wc;
-      }
-      const uint64_t m = __ballot(mem);
-      if (mem) {
-        const int slot = cnt + __popcll(m & ((1ull << lane) - 1ull));
-        if (slot < cap) pool[slot] = make_uint2((unsigned)h, __float_as_uint(adx));
-      }
-      cnt += __popcll(m);
-    };
-    if (total > 3 * kWave) {
-      // dense: class by class (the lookup of a hit's range costs more than
-      // the partly filled last pass of each range)
-      for (int c = 0; c < ncls; ++c) {
-        const float sc = bcastf(s, c);
-        if (!(sc == sc)) continue;
-        const float wc = bcastf(w, c);
+  }
+  __syncthreads();
 #pragma unroll
-        for (int part = 0; part < 2; ++part) {
-          const int st = bcasti(part ? st1 : st0, c);
-          const int en = bcasti(part ? en1 : en0, c);
-          for (int e0 = st; e0 < en; e0 += kWave) test(e0 + lane, e0 + lane < en, sc, wc);
-        }
-      }
-    } else for (int t0 = 0; t0 < total; t0 += kWave) {
-      const int t = t0 + lane;
-      // range of t: the number of ranges that end at or before it, by a
-      // binary search over the ends (non-decreasing in q, nr <= 32)
-      int q = 0;
-#pragma unroll
-      for (int step = 32; step > 0; step >>= 1) {
-        // every lane reads (a lane's value can only be read while it is active)
-        const int end = __shfl(rend, min(q + step - 1, kWave - 1), kWave);
-        if (q + step <= nr && end <= t) q += step;
-      }
-      const int qs = q < kWave ? q : kWave - 1;
-      const int e = __shfl(rbase, qs, kWave) + t;
-      test(e, t < total, __shfl(s, qs >> 1, kWave), __shfl(w, qs >> 1, kWave));
-    }
-    if (lane == 0) A.mcount[p] = cnt;
+  for (int u = 0; u < kPer; ++u) {
+    if (key[u] < 0) continue;
+    const int k = key[u] & (kBucketKeys - 1), L = k / kBuckets;
+    int base = 0;
+    for (int l = 0; l < L; ++l) base += 2 * cnt[l];
+    const int e = base + (int)((cnt2[k >> 1] >> ((k & 1) * 16)) & 0xffffu) + (key[u] >> 15);
+    put_records(A, tid + u * kPrepThreads, e, cnt[L], x[u], y[u], q[u], rec[u]);
   }
 }
 
@@ -982,7 +968,7 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
   const int n_slices = gridDim.z / NB;
   const int slice = (int)blockIdx.z % n_slices;
   const AssocArgs& A = AB.a[NB == 1 ? 0 : (int)blockIdx.z / n_slices];
-  if (A.sc[S_MODE] != 0) return;  // the lists are built by candidate
+  if (A.sc[S_MODE] != 0) return;  // the seed search reads the layer runs
   const int j0 = blockIdx.x * kWave;
   const int k = blockIdx.y;
   const int n_all = hits_of(A);
@@ -993,25 +979,36 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
   const int n_phi = A.n_phi;
   const int nwords = (n_phi + 31) >> 5;
   const int cap = A.cfg.member_cap;
-  // gather the column bitmaps (column bits are not word aligned in general)
-  for (int e = threadIdx.x; e < kWave * nwords; e += kSweepThreads) {
-    const int cl = e / nwords, w = e - cl * nwords;
-    const int j = j0 + cl;
-    uint32_t v = 0;
-    if (j < A.n_qpt) {
-      const int64_t bit0 = ((int64_t)k * A.n_qpt + j) * n_phi + (int64_t)w * 32;
-      const int nb = min(32, n_phi - w * 32);
-      const int64_t wi = bit0 >> 5;
-      const int sh = (int)(bit0 & 31);
-      uint64_t two = (uint64_t)A.pbits[wi];
-      if (sh + nb > 32) two |= (uint64_t)A.pbits[wi + 1] << 32;
-      v = (uint32_t)(two >> sh);
-      if (nb < 32) v &= (1u << nb) - 1u;
+  // the workgroup's peaks: its columns' cells are consecutive, so in a list in
+  // cell order they are the entries p_lo .. p_lo + np_wg - 1 (any other list leaves
+  // some of them out)
+  const int n_cols = min(kWave, A.n_qpt - j0);
+  const int64_t lin0 = ((int64_t)k * A.n_qpt + j0) * n_phi, lin1 = lin0 + (int64_t)n_cols * n_phi;
+  for (int e = threadIdx.x; e < kWave * nwords; e += kSweepThreads) S.cbits[e / nwords][e % nwords] = 0u;
+  if (threadIdx.x < 2) {
+    const int64_t want = threadIdx.x ? lin1 : lin0;
+    int a = 0, b = n_cands(A);  // the first entry at or beyond the cell
+    while (a < b) {
+      const int m = a + (b - a) / 2;
+      if (A.peaks[m].lin < want) a = m + 1;
+      else b = m;
     }
-    S.cbits[cl][w] = v;
-    S.lbits[cl][w] = v;
+    if (threadIdx.x) S.np_wg = a;
+    else S.p_lo = a;
   }
   __syncthreads();
+  const int p_lo = S.p_lo;
+  const int np_wg = S.np_wg - p_lo;
+  if (np_wg <= 0) return;
+  for (int q = threadIdx.x; q < np_wg; q += kSweepThreads) {
+    const int64_t c = (int64_t)A.peaks[p_lo + q].lin - lin0;
+    if (c < 0 || c >= lin1 - lin0) continue;
+    const int cl = (int)c / n_phi, ic = (int)c - cl * n_phi;
+    atomicOr(&S.cbits[cl][ic >> 5], 1u << (ic & 31));
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < kWave * nwords; e += kSweepThreads)
+    S.lbits[e / nwords][e % nwords] = S.cbits[e / nwords][e % nwords];
   if (threadIdx.x < kWave) {
     int s = 0;
     for (int w = 0; w < nwords; ++w) {
@@ -1019,29 +1016,8 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
       s += __popc(S.cbits[threadIdx.x][w]);
     }
     S.ccnt[threadIdx.x] = s;
-    // the first column with peaks gives the workgroup's first peak index
-    const uint64_t hasm = __ballot(s > 0);
-    int tot = s;
-    for (int d = 32; d > 0; d >>= 1) tot += __shfl_xor(tot, d);
-    if (threadIdx.x == 0) {
-      S.np_wg = tot;
-      S.p_lo = 0;
-      if (hasm) {
-        const int c0 = __builtin_ctzll(hasm);
-        S.p_lo = A.col_first[(size_t)k * A.n_qpt + j0 + c0];
-      }
-    }
-  }
-  __syncthreads();
-  const int np_wg = S.np_wg;
-  const int p_lo = S.p_lo;
-  // a cell-ordered peak list gives p_lo + np_wg <= n_peaks; anything else is
-  // a malformed list, whose candidates in these columns then get no members
-  if (np_wg == 0 || p_lo < 0 || p_lo + np_wg > n_cands(A)) return;
-  if (threadIdx.x < kWave) {
-    const int j = j0 + threadIdx.x;
-    S.cfirst[threadIdx.x] =
-        (j < A.n_qpt && S.ccnt[threadIdx.x] > 0) ? A.col_first[(size_t)k * A.n_qpt + j] - p_lo : 0;
+    S.cfirst[threadIdx.x] = wave_incl_scan_i32(s, threadIdx.x) - s;
+    if (threadIdx.x == 0) S.np_wg = np_wg;
   }
   __syncthreads();
   uint2* pool = A.pool + (size_t)p_lo * cap;
@@ -1064,7 +1040,7 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
     __syncthreads();
     for (int q = threadIdx.x; q < np_wg; q += kSweepThreads) A.mcount[p_lo + q] = S.cnt[q];
   } else {
-    // counters in global memory (zeroed by mark_kernel), shared by the hit
+    // counters in global memory (cleared before this launch), shared by the hit
     // slices; each slice drops a candidate at its first member past the cap
     int32_t* cnt = A.mcount + p_lo;
     sweep_members(A, S, k, j0, h0, h1, [&](int q, int hh, float adx) {
@@ -1391,6 +1367,13 @@ __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v)
   return r;
 }
 
+__device__ __forceinline__ double readlane_d(double v, int l) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
 // inclusive prefix sum within each row of 16 lanes (row_shr with zero fill)
 __device__ __forceinline__ int row_scan_incl(int v) {
   v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
@@ -1415,6 +1398,7 @@ template <int CAP, int NB>
 __global__ __launch_bounds__(RefineShape<CAP>::kWaves * kWave, RefineShape<CAP>::kMinWavesPerSimd) void
 refine_kernel(AssocBatch<NB> AB, int n_lo, int n_hi) {
   const AssocArgs& A = event_args(AB);
+  if (A.sc[S_MODE] != 0) return;  // the seed search reads the layer runs
   constexpr int W = RefineShape<CAP>::kWaves;
   // members per chunk of the road loop (registers: 4 per member); the
   // short member lists of caps up to 128 keep one member at a time, which
@@ -2013,6 +1997,1203 @@ refine_kernel(AssocBatch<NB> AB, int n_lo, int n_hi) {
   }
 }
 
+// ---- seed search on the layer runs -------------------------------------------
+// One wave per candidate.  The wave works out each layer's run of buckets (the
+// candidate's member interval and a bucket of margin; four candidates at a
+// time, 16 lanes each), tests the runs' hits with the vote's own operations,
+// ranks the seed layers' members, fits a circle per lane (lane = seed
+// combination) and visits the layers, fewest members first, until no lane can
+// reach min_layers.  Two launches:
+//
+// reject_kernel takes candidates with short runs, nearly all of which fail.  It
+// keeps the members in LDS, grouped by layer because the runs are, normalises
+// the circles with a float32 reciprocal square root (the numerators are the
+// float64 ones, so all four coefficients carry one common factor) and tests the
+// members in float32 with margins.  A candidate in which no lane reaches
+// min_layers that way is done; the others, and those with a box check within
+// its margin, are left for
+//
+// runs_kernel, which settles them in float64.  A layer's hits are staged in LDS
+// and each lane reads the buckets that its road reaches: on radius r the
+// circle's points within f of it satisfy cos(phi - phB) = -(A r + D / r) / R
+// within f / (r R), an arc on either side of phB.  Of the hits on its road a
+// lane needs the nearest, and the float32 distances decide unless two of them
+// lie within their error bounds, so one float64 distance per lane and layer is
+// computed, for the lanes that can still win, instead of one per hit on the
+// road.
+//
+// Bound by VALU issue (rocprofv3: 78% of the SIMDs' issue cycles on 55k-hit
+// events, about all of them on events of smeared radii; 576 instructions per
+// candidate in reject_kernel).  Member lists written to memory and read back,
+// gathered hit by hit, cost more than the search itself: with the hits sorted
+// once per event a candidate's members are contiguous runs.  Member lists and
+// seed search per event, before and after, in ms: 55k hits on ten radii (member_cap
+// 1024) 4.84 -> 1.78; 3000 tracks with smeared radii (member sweep before) 11.9 ->
+// 3.2; 3.6k hits (cap 128) 0.41 -> 0.29; four 2.5k-hit events in a batch (cap 256)
+// 1.43 -> 0.45.
+constexpr int kRunWaves = 4;
+constexpr int kRunWords = 64;    // member bits kept for 64 * 64 run hits; longer runs are tested again
+constexpr int kListRun = 256;    // run hits and
+constexpr int kListMembers = 128;  // members of a candidate that reject_kernel takes
+constexpr int kStage = 256;      // hits staged at a time
+constexpr int kTab = 256;        // buckets whose starts are staged
+constexpr int kScanAll = 16;     // runs of at most this many hits are read whole by every lane
+constexpr int kPending = -3;     // candidate status: not looked at by reject_kernel
+// Events with fewer candidates skip reject_kernel: both launches are then one or
+// two rounds of a single candidate's latency (about 30 us each), and all in
+// runs_kernel take 55 us at 11k candidates against 64 us in both.  So do events on
+// the prompt grid, where few candidates fail (5k candidates: 42 against 50 us).
+constexpr int kFewCands = 12288;
+
+// a listed member; the ranking key (|x - cell centre|, then the hit, whose index
+// is its own) is the upper half as one 64-bit word
+struct alignas(16) ListMem {
+  float x, y;
+  uint32_t hp;  // hit << 16 | place in the run
+  float adx;
+};
+struct RejectShared {
+  ListMem mem[kListMembers + 4];  // members by layer, and room to read past the last
+  double2 sxy[3][4];       // the seeds' coordinates
+};
+struct RunShared {
+  // staged hits (x, y) and, for layers of several radii, x^2 + y^2; no members
+  // carry infinities, and so do the four places behind each run
+  float2 xy[kStage + 4 * HT_MAX_LAYERS];
+  float q[kStage + 4 * HT_MAX_LAYERS];
+  uint16_t tab[kTab];
+  uint16_t hit[kWave][HT_MAX_LAYERS + 2];  // each lane's inlier per layer: its place in the run
+  double2 sxy[3][4];
+};
+
+// what a workgroup keeps of the event's layers
+struct alignas(16) RunLayer {
+  float rhi, rm, irm, hw;      // largest and middle radius, 1 / rm, half the spread (0: one radius)
+  float irlo, rlo, e5;         // 1 / rlo, smallest radius, the window's hit part (one radius)
+  int32_t cnt;
+};
+
+// arccosine for |x| <= 1, Abramowitz & Stegun 4.4.45 (error below 7e-5)
+__device__ __forceinline__ float acos_coarse(float x) {
+  const float a = fabsf(x);
+  float p = -0.0187293f;
+  p = __builtin_fmaf(p, a, 0.0742610f);
+  p = __builtin_fmaf(p, a, -0.2121144f);
+  p = __builtin_fmaf(p, a, 1.5707288f);
+  p *= __builtin_amdgcn_sqrtf(1.0f - a);
+  return x < 0.0f ? kPiF - p : p;
+}
+// direction of (x, y), Abramowitz & Stegun 4.4.47 (error below 2e-5)
+__device__ __forceinline__ float atan2_coarse(float y, float x) {
+  const float ax = fabsf(x), ay = fabsf(y);
+  const float t = fminf(ax, ay) * __builtin_amdgcn_rcpf(fmaxf(ax, ay));
+  const float t2 = t * t;
+  float p = 0.0208351f;
+  p = __builtin_fmaf(p, t2, -0.0851330f);
+  p = __builtin_fmaf(p, t2, 0.1801410f);
+  p = __builtin_fmaf(p, t2, -0.3302995f);
+  p = __builtin_fmaf(p, t2, 0.9998660f);
+  p *= t;
+  p = ay > ax ? 0.5f * kPiF - p : p;
+  p = x < 0.0f ? kPiF - p : p;
+  return y < 0.0f ? -p : p;
+}
+constexpr float kAcosPad = 2e-4f;  // radians: their errors, and every azimuth's rounding
+
+__device__ __forceinline__ int wave_min_i32(int v) {
+  return wave_reduce_i32(v, [](int a, int b) { return a < b ? a : b; });
+}
+
+// the lane with the smallest key (a, b), a >= 0 (0x7fffffff: no key), then b;
+// every lane calls it; -1 when no lane has a key
+__device__ __forceinline__ int wave_argmin(int a, int b) {
+  const int m = wave_min_i32(a);
+  if (m == 0x7fffffff) return -1;
+  uint64_t tie = __ballot(a == m);
+  if (tie & (tie - 1ull)) {
+    const int mb = wave_min_i32(a == m ? b : 0x7fffffff);
+    tie = __ballot(a == m && b == mb);
+  }
+  return __builtin_ctzll(tie);
+}
+
+// the event's layers as every workgroup keeps them (whole workgroup); returns the
+// largest radius
+__device__ __forceinline__ float load_layers(const AssocArgs& A, RunLayer* T) {
+  if (threadIdx.x < HT_MAX_LAYERS) {
+    const int L = threadIdx.x;
+    const int cnt = A.lay[2 * HT_MAX_LAYERS + L];
+    const float lo = cnt ? __int_as_float(A.lay[L]) : 1.0f;
+    const float hi = cnt ? __int_as_float(A.lay[HT_MAX_LAYERS + L]) : 1.0f;
+    const float m = 0.5f * (lo + hi);
+    const float ilo = 1.0f / lo;
+    RunLayer t;
+    t.rlo = lo;
+    t.rhi = hi;
+    t.rm = lo == hi ? lo : m;
+    t.irm = lo == hi ? ilo : 1.0f / m;
+    t.hw = lo == hi ? 0.0f : 0.5f * (hi - lo) + 1e-6f * hi;  // the rounding of m included
+    t.irlo = ilo;
+    t.e5 = member_e5(lo, ilo, A.hd0, A.hk, A.invw);
+    t.cnt = cnt;
+    T[L] = t;
+  }
+  __syncthreads();
+  float rmax = 0.0f;
+  for (int L = 0; L < HT_MAX_LAYERS; ++L) rmax = T[L].cnt > 0 ? fmaxf(rmax, T[L].rhi) : rmax;
+  return bcastf(rmax, 0);
+}
+
+// one layer's run for the candidate at cell lin (-1: none), on the lane that
+// calls it
+struct LayerRun {
+  float s, w;  // layers of one radius: arcsine (NaN: no votes) and window
+  int c0, nb;  // first bucket and bucket count
+  int st, len; // first hit and hit count
+  int i, col;  // the candidate's cell in its column, and the column
+  bool wide;   // several radii
+};
+__device__ __forceinline__ LayerRun layer_run(const AssocArgs& A, const RunLayer& t, int L,
+                                              int lin) {
+  LayerRun R;
+  R.s = __builtin_nanf("");
+  R.w = 0.0f;
+  R.c0 = R.nb = R.st = R.len = R.i = R.col = 0;
+  R.wide = false;
+  if (lin < 0) return R;
+  const int col = lin / A.n_phi;
+  const int i = lin - col * A.n_phi;
+  R.i = i;
+  R.col = col;
+  if (t.cnt <= 0) return R;
+  const float ck = A.kap[col % A.n_qpt], cq = A.qt[col], ct = A.tt[col];
+  const float wbase = 0.5f + (float)A.cfg.win_bins;
+  R.wide = t.hw > 0.0f;
+  bool have = false, all = false;
+  float slo = 0.0f, ds = 0.0f, w = 0.0f;
+  if (!R.wide) {
+    float x = 0.0f, u = 0.0f;
+    have = phi0_coord(t.rlo * t.rlo, t.irlo, 0.0f, ck, cq, ct, A.phi_lo, A.invw, &x, &u);
+    if (have) {
+      R.s = slo = asin_f(u);
+      R.w = w = member_window(t.e5, u, wbase);
+    }
+  } else {
+    // u over the layer's radii: within du of its value at the middle radius
+    const float um = ct * __builtin_fmaf(ck, t.rm, cq * t.irm);
+    const float slope = fabsf(ct) * (fabsf(ck) + fabsf(cq) * t.irlo * t.irlo);
+    const float du = slope * t.hw +
+                     1e-5f * fabsf(ct) * (fabsf(ck) * t.rhi + fabsf(cq) * t.irlo) + 1e-6f;
+    const float ulo = um - du, uhi = um + du;
+    const float ux = fmaxf(fabsf(ulo), fabsf(uhi));
+    have = !(ulo > 1.0f) && !(uhi < -1.0f);
+    all = !(ux <= 0.9995f);
+    if (have && !all) {
+      slo = asin_f(ulo);
+      ds = asin_f(uhi) - slo;
+      const float e5 = 1.0001f * A.invw * (A.hd0 * t.irlo + A.hk * t.rhi * 0.5f);
+      w = wbase + e5 * 1.5f * __builtin_amdgcn_rsqf(1.0f - ux * ux) * 1.001f;
+    }
+  }
+  if (have) {
+    // azimuths whose x lies within w of the cell centre, as bucket
+    // coordinates [lo, lo + len] (periodic), with a bucket of margin
+    const float binw = 1.0f / A.invw;
+    const float xc = (float)i + 0.5f;
+    const float a = ((xc - w) * binw + A.phi_lo) + slo;
+    const float lo = bucket_coord(wrap_pi_f(a)) - 1.0f;
+    const float len = (2.0f * w * binw + ds) * ((float)kBuckets / k2PiF) + 2.0f;
+    if (all || !(len < (float)(kBuckets - 2)) || !(lo == lo)) {
+      R.nb = kBuckets;
+    } else {
+      const int b0 = (int)floorf(lo);
+      R.nb = (int)floorf(lo + len) + 1 - b0;  // at most kBuckets
+      R.c0 = b0 < 0 ? b0 + kBuckets : (b0 >= kBuckets ? b0 - kBuckets : b0);
+    }
+    const int32_t* row = A.bkt_off + L * kRunRow;
+    R.st = row[R.c0];
+    R.len = row[R.c0 + R.nb] - R.st;
+  }
+  return R;
+}
+
+// The exact member test of hit e (azimuth ph) for the candidate at cell i of
+// column col, on a layer of arcsine s and window w (events with layers of
+// several radii: the hit's own); adx is the ranking key.
+__device__ __forceinline__ bool run_member(const AssocArgs& A, bool any_wide, int i, int col, int e,
+                                           float ph, float s, float w, float* adx) {
+  float x;
+  bool ok = true;
+  if (any_wide) {
+    const float4 h = A.srad[e];
+    float u = 0.0f;
+    x = 0.0f;
+    ok = phi0_coord(h.x * h.x, h.y, ph, A.kap[col % A.n_qpt], A.qt[col], A.tt[col], A.phi_lo,
+                    A.invw, &x, &u);
+    w = ok ? member_window(h.z, u, 0.5f + (float)A.cfg.win_bins) : -1.0f;
+  } else {
+    x = ((ph - s) - A.phi_lo) * A.invw;
+  }
+  *adx = cell_adx(x, i, A.n_phi);
+  return ok && *adx <= w;
+}
+
+// run of position t among the runs of a candidate's 16 lanes (from lane o), laid
+// end to end: the first that ends behind t
+__device__ __forceinline__ int run_of(int rend, int o, int t) {
+  int q = o;
+#pragma unroll
+  for (int step = HT_MAX_LAYERS / 2; step > 0; step >>= 1) {
+    const int end = __shfl(rend, q + step - 1, kWave);
+    if (end <= t) q += step;
+  }
+  return q;
+}
+
+// lane's share of a word of member bits m (positions t0 .. t0 + 63): the members
+// of its run, positions b .. e - 1
+__device__ __forceinline__ int run_share(uint64_t m, int t0, int b, int e) {
+  const int x = b > t0 ? b - t0 : 0, y = e - t0 < kWave ? e - t0 : kWave;
+  if (y <= x) return 0;
+  uint64_t f = m >> x;
+  if (y - x < kWave) f &= (1ull << (y - x)) - 1ull;
+  return __popcll(f);
+}
+
+// seed layers: innermost, middle and outermost of the outer min(nS, min_layers)
+__device__ __forceinline__ void seed_layers(unsigned lmask, int nS, int min_layers, int Ls[3]) {
+  const int span = nS < min_layers ? nS : min_layers;
+  unsigned m = lmask;
+  for (int q = nS - span; q > 0; --q) m &= m - 1u;
+  Ls[0] = __builtin_ctz(m);
+  for (int q = (span - 1) / 2; q > 0; --q) m &= m - 1u;
+  Ls[1] = __builtin_ctz(m);
+  Ls[2] = 31 - __builtin_clz(lmask);
+}
+
+// Visiting order: the layers that are not seed layers by increasing member count
+// (then index), so that lanes meet a layer without an inlier early; then the
+// seed layers.  A lane's outcome does not depend on it.  Lane i receives the i-th
+// of the former; cnt is the member count on lane o + L.
+__device__ __forceinline__ int visit_order(unsigned nsm, int o, int cnt) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const bool mine = (lane & 48) == o && ((nsm >> (lane & 15)) & 1u);
+  const int key = mine ? ((cnt << 4) | (lane & 15)) : 0x7fffffff;
+  int rank = 0;
+  for (unsigned m = nsm; m; m &= m - 1u) rank += bcasti(key, o + __builtin_ctz(m)) < key ? 1 : 0;
+  // a forward permute; the other lanes send to lane 63, whose value is never read
+  return __builtin_amdgcn_ds_permute((mine ? rank : kWave - 1) * 4, lane & 15);
+}
+
+// The workgroup's totals: tot[w][c] of its waves, one atomic per counter from
+// threads 0 .. 4 (road tests, refined candidates, over member_cap, pairs, exact
+// distances).  Whole workgroup.
+template <int W>
+__device__ __forceinline__ void add_totals(const AssocArgs& A, unsigned long long (*tot)[5]) {
+  __syncthreads();
+  if (threadIdx.x < 5) {
+    unsigned long long v = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) v += tot[w][threadIdx.x];
+    const int slot = blockIdx.x & (kSpread - 1);
+    if (v) atomicAdd(&A.spread[(size_t)(threadIdx.x * kSpread + slot) * kSpreadStride], v);
+  }
+}
+
+// a lane's seed circle for the float32 search: f = a q + b x + c y + d
+struct Circle32 {
+  float a, b, c, d;
+  bool ok;      // admissible: curvature and d0 within the box
+  bool unsure;  // the float64 circle may decide otherwise
+};
+// circle3's operations up to the normalisation, whose result differs by a common
+// factor 1 +- 3e-7, and the box check with margins; kc and dc are the column's
+// curvature and d0
+__device__ __forceinline__ Circle32 circle32(double2 pa, double2 pb, double2 pc, float kc, float dc,
+                                             float kt, float dt) {
+  const double X2 = pb.x - pa.x, Y2 = pb.y - pa.y, X3 = pc.x - pa.x, Y3 = pc.y - pa.y;
+  const double q2 = X2 * X2 + Y2 * Y2;
+  const double q3 = X3 * X3 + Y3 * Y3;
+  const double a = X2 * Y3 - Y2 * X3;
+  const double b = Y2 * q3 - q2 * Y3;
+  const double c = q2 * X3 - X2 * q3;
+  const double nrm2 = b * b + c * c;
+  const double q1 = pa.x * pa.x + pa.y * pa.y;
+  const float nf = (float)nrm2;
+  const float inv = __builtin_amdgcn_rsqf(nf);
+  Circle32 C;
+  C.a = (float)a * inv;
+  C.b = (float)(b - 2.0 * a * pa.x) * inv;
+  C.c = (float)(c - 2.0 * a * pa.y) * inv;
+  C.d = (float)(a * q1 - b * pa.x - c * pa.y) * inv;
+  const float d1 = C.c * (float)X3, d2 = C.b * (float)Y3;
+  const float dir = d2 - d1;
+  if (dir < 0.0f) { C.a = -C.a; C.b = -C.b; C.c = -C.c; C.d = -C.d; }
+  const float kap = 2.0f * C.a;
+  const float sq = __builtin_amdgcn_sqrtf(__builtin_fmaf(C.b, C.b, C.c * C.c));
+  const float d0 = 2.0f * C.d * __builtin_amdgcn_rcpf(1.0f + sq);
+  const float ek = fabsf(kap - kc) - kt, ed = fabsf(d0 - dc) - dt;
+  const float mk = 4e-6f * (fabsf(kap) + fabsf(kc) + kt);
+  const float md = 4e-6f * (fabsf(d0) + fabsf(dc) + dt);
+  C.ok = ek < 0.0f && ed < 0.0f;
+  // sure when a condition fails by more than its margin, or both hold so; an
+  // orientation or a norm near zero leaves the float64 circle to decide
+  const bool no = ek > mk || ed > md;
+  const bool yes = ek < -mk && ed < -md;
+  C.unsure = !(no || yes) || !(nf > 1e-20f && nf < 1e30f) ||
+             !(fabsf(dir) > 1e-4f * (fabsf(d1) + fabsf(d2)));
+  return C;
+}
+
+template <int NB>
+__global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch<NB> AB) {
+  const AssocArgs& A = event_args(AB);
+  const int np = n_cands(A);
+  if (A.sc[S_MODE] == 0 || np < kFewCands || (int)blockIdx.x * kRunWaves >= np) return;
+  __shared__ RejectShared RS[kRunWaves];
+  __shared__ RunLayer T[HT_MAX_LAYERS];
+  __shared__ unsigned long long tot[kRunWaves][5];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  RejectShared& S = RS[wave];
+  const float rmax = load_layers(A, T);
+  const ht_cluster_cfg& cfg = A.cfg;
+  const double road = (double)cfg.road_sigmas * (double)cfg.sigma_rphi;
+  double ktol = (0.5 + (double)cfg.box_margin) * A.kap_bin;
+  if (ktol < 1e-6) ktol = 1e-6;
+  const double dtol = (0.5 + (double)cfg.box_margin) * A.d0_bin + road;
+  if (lane < 5) tot[wave][lane] = 0;
+  unsigned long long tests = 0;
+  const int pstep = gridDim.x * kRunWaves;
+  for (int p4 = blockIdx.x * kRunWaves + wave; p4 < np; p4 += 4 * pstep) {
+    // lane 16 g + L: layer L of candidate p4 + g pstep
+    int lin_l = -1;
+    if (p4 + (lane >> 4) * pstep < np) lin_l = A.peaks[p4 + (lane >> 4) * pstep].lin;
+    if (lin_l >= A.n_cells) lin_l = -1;
+    const LayerRun R = layer_run(A, T[lane & 15], lane & 15, lin_l);
+    const float kc_l = (float)A.kapc[R.col % A.n_qpt], dc_l = (float)A.d0c[R.col / A.n_qpt];
+    const float rm2_l = T[lane & 15].rm * T[lane & 15].rm;
+    const bool any_wide = __ballot(R.wide) != 0ull;
+    const int rend_l = row_scan_incl(R.len);  // end of layer L's run, the runs laid end to end
+    const int bb_l = rend_l - R.len;
+    const int rbase = R.st - bb_l;
+    for (int g = 0; g < 4; ++g) {
+      const int p = p4 + g * pstep;
+      if (p >= np) break;
+      const int o = 16 * g;  // the candidate's first lane
+      const int total = bcasti(rend_l, o + HT_MAX_LAYERS - 1);
+      if (total > kListRun) {
+        if (lane == 0) A.cstat[p] = kPending;
+        continue;
+      }
+      const int i = bcasti(R.i, o), col = bcasti(R.col, o);
+      // ---- members, 64 run hits at a time whatever the runs' lengths
+      int cnt_l = 0;  // members of layer L
+      int n = 0;
+      for (int t0 = 0; t0 < total; t0 += kWave) {
+        const int t = t0 + lane;
+        const int q = run_of(rend_l, o, t);
+        const int e = __shfl(rbase, q, kWave) + t;
+        const int b0 = __shfl(bb_l, q, kWave);
+        const float s = __shfl(R.s, q, kWave), w = __shfl(R.w, q, kWave);
+        float adx = 0.0f;
+        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        bool mem = false;
+        if (t < total) {
+          v = A.srec[e];
+          mem = run_member(A, any_wide, i, col, e, v.z, s, w, &adx);
+        }
+        const uint64_t m = __ballot(mem);
+        const int slot = n + __popcll(m & ((1ull << lane) - 1ull));
+        if (mem && slot < kListMembers) {
+          ListMem r4;
+          r4.x = v.x;
+          r4.y = v.y;
+          r4.adx = adx;
+          r4.hp = ((uint32_t)__float_as_int(v.w) << 16) | (uint32_t)(t - b0);
+          S.mem[slot] = r4;
+        }
+        n += __popcll(m);
+        if ((lane >> 4) == g) cnt_l += run_share(m, t0, bb_l, rend_l);
+      }
+      // (a cell outside the grid has no runs)
+      const unsigned lmask = (unsigned)(__ballot(cnt_l > 0) >> o) & 0xffffu;
+      const int nS = __popc(lmask);
+      const bool over = n > cfg.member_cap;
+      if (over || nS < cfg.min_layers || nS < 3) {
+        if (lane == 0) {
+          A.cstat[p] = over ? -2 : -1;
+          A.cnl[p] = over ? 0 : nS;
+          tot[wave][over ? 2 : 3] += over ? 1ull : (unsigned long long)n;
+        }
+        wave_sync();
+        continue;
+      }
+      int Ls[3];
+      seed_layers(lmask, nS, cfg.min_layers, Ls);
+      const int n0 = bcasti(cnt_l, o + Ls[0]), n1 = bcasti(cnt_l, o + Ls[1]);
+      const int n2 = bcasti(cnt_l, o + Ls[2]);
+      if (n > kListMembers || n0 + n1 + n2 > kWave) {
+        if (lane == 0) A.cstat[p] = kPending;
+        wave_sync();
+        continue;
+      }
+      wave_sync();
+      // ---- the seed_k nearest members of each seed layer, by rank of (adx, hit)
+      const int kk = cfg.seed_k;
+      const int mend_l = row_scan_incl(cnt_l);  // end of layer L's members in the list
+      const int sst[3] = {bcasti(R.st, o + Ls[0]), bcasti(R.st, o + Ls[1]), bcasti(R.st, o + Ls[2])};
+      const int mst[3] = {bcasti(mend_l, o + Ls[0]) - n0, bcasti(mend_l, o + Ls[1]) - n1,
+                          bcasti(mend_l, o + Ls[2]) - n2};
+      // the three seed layers side by side: lane -> (seed layer, member)
+      int s = -1, st = 0, en = 0, q = 0;
+      if (lane < n0) { s = 0; st = mst[0]; en = st + n0; }
+      else if (lane < n0 + n1) { s = 1; st = mst[1]; en = st + n1; q = n0; }
+      else if (lane < n0 + n1 + n2) { s = 2; st = mst[2]; en = st + n2; q = n0 + n1; }
+      const int e = s < 0 ? 0 : st + lane - q;
+      const unsigned long long* keys =
+          reinterpret_cast<const unsigned long long*>(&S.mem[0]) + 1;  // every other word
+      const unsigned long long key = keys[2 * e];
+      // (the coordinates' load runs beside the ranking)
+      const int se = s == 0 ? sst[0] : (s == 1 ? sst[1] : sst[2]);
+      const double2 xy = A.sxy[se + (int)((unsigned)key & 0xffffu)];
+      const int nmax = max(n0, max(n1, n2));
+      int rank = 0;
+      // every lane reads every round; rounds past the lane's own layer read a
+      // record inside the list and do not count
+#pragma unroll 4
+      for (int t = 0; t < nmax; ++t) {
+        const int e2 = st + t;
+        const unsigned long long k2 = keys[2 * (e2 < n ? e2 : n - 1)];
+        rank += (e2 < en && k2 < key) ? 1 : 0;
+      }
+      if (s >= 0 && rank < kk) S.sxy[s][rank] = xy;
+      const unsigned smask = (1u << Ls[0]) | (1u << Ls[1]) | (1u << Ls[2]);
+      const unsigned nsm = lmask & ~smask;
+      const int n_ns = __popc(nsm);
+      const int orderv = visit_order(nsm, o, cnt_l);
+      wave_sync();
+      // ---- seed circles: lane = 16 a + 4 b + c (seed_k <= 4)
+      const int ia = lane >> 4, ib = (lane >> 2) & 3, ic = lane & 3;
+      const bool combo = ia < (A.origin_seed ? 1 : (n0 < kk ? n0 : kk)) &&
+                         ib < (n1 < kk ? n1 : kk) && ic < (n2 < kk ? n2 : kk);
+      Circle32 C = {0.0f, 0.0f, 0.0f, 0.0f, false, false};
+      if (combo)
+        C = circle32(A.origin_seed ? make_double2(0.0, 0.0) : S.sxy[0][ia], S.sxy[1][ib],
+                     S.sxy[2][ic], bcastf(kc_l, o), bcastf(dc_l, o), (float)ktol, (float)dtol);
+      if (__ballot(C.unsure) != 0ull) {
+        if (lane == 0) A.cstat[p] = kPending;
+        wave_sync();
+        continue;
+      }
+      const unsigned long long n_tests =
+          (unsigned long long)__popcll(__ballot(C.ok)) * (unsigned long long)n;
+      const float Af = C.a, Bf = C.b, Cf = C.c, Df = C.d;
+      // |dist| >= |f| / (1 + |A||f|), so a hit with |f| > road / (1 - road |A|)
+      // is off the road, and road / (1 - x) <= road (1 + 2x) for x <= 1/2.
+      // The float32 f is within 1e-6 of its terms' magnitudes of the float64
+      // one; the threshold allows twice that.
+      const float ra = (float)road * fabsf(Af);
+      const float pre = ra <= 0.49f ? (float)road * (1.0f + 2.0f * ra) * 1.00001f : __builtin_inff();
+      const float thr = pre + 2e-6f * (fabsf(Af) * rmax * rmax +
+                                       (fabsf(Bf) + fabsf(Cf)) * rmax + fabsf(Df));
+      int c = C.ok ? 0 : -64;
+      unsigned sseq = smask;
+      int remaining = nS;
+      for (int it = 0; it < nS; ++it) {
+        int L;
+        if (it < n_ns) {
+          L = __builtin_amdgcn_readlane(orderv, it);
+        } else {
+          L = __builtin_ctz(sseq);
+          sseq &= sseq - 1u;
+        }
+        // lanes that cannot reach min_layers any more
+        if (__ballot(c + remaining >= cfg.min_layers) == 0ull) break;
+        --remaining;
+        const int me = bcasti(mend_l, o + L), ms = me - bcasti(cnt_l, o + L);
+        const float base = __builtin_fmaf(Af, bcastf(rm2_l, L), Df);  // layers of one radius
+        bool hit = false;
+        for (int m = ms; m < me; m += 4) {
+          // four members at a time (those past the layer's last do not count)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float2 v = *reinterpret_cast<const float2*>(&S.mem[m + u]);
+            float f = base;
+            if (any_wide) f = __builtin_fmaf(Af, __builtin_fmaf(v.x, v.x, v.y * v.y), Df);
+            f = __builtin_fmaf(Bf, v.x, __builtin_fmaf(Cf, v.y, f));
+            hit = hit || (m + u < me && fabsf(f) <= thr);
+          }
+        }
+        c += hit ? 1 : 0;
+      }
+      // lanes without an admissible circle cannot reach it
+      const bool fail = __ballot(c >= cfg.min_layers) == 0ull;
+      if (fail) tests += n_tests;
+      if (lane == 0) {
+        A.cstat[p] = -1;
+        A.cnl[p] = nS;
+        if (fail)
+          tot[wave][3] += (unsigned long long)n;
+        else
+          A.mcount[atomicAdd(&A.sc[S_QUEUE], 1)] = p;  // few: the candidates of true tracks
+      }
+      wave_sync();
+    }
+  }
+  if (lane == 0) tot[wave][0] = tests;
+  add_totals<kRunWaves>(A, tot);
+}
+
+template <int NB>
+__global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<NB> AB) {
+  const AssocArgs& A = event_args(AB);
+  if (A.sc[S_MODE] == 0) return;
+  __shared__ RunShared RS[kRunWaves];
+  __shared__ RunLayer T[HT_MAX_LAYERS];
+  __shared__ unsigned long long tot[kRunWaves][5];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  RunShared& S = RS[wave];
+  const int np = n_cands(A);
+  const bool every = np < kFewCands || A.origin_seed;  // reject_kernel took none
+  const int nq = A.sc[S_QUEUE];
+  if ((int)blockIdx.x * kRunWaves >= np) return;
+  // the wave's candidates: entries w, w + pstep, .. of the queue, then those not
+  // looked at among w + l pstep, 64 statuses read at a time
+  const int pstep = gridDim.x * kRunWaves;
+  int qi = blockIdx.x * kRunWaves + wave;
+  int p0 = qi, pbase = qi;
+  uint64_t pend = 0;
+  auto next_pending = [&]() {
+    for (; pend == 0 && p0 < np; p0 += kWave * pstep) {
+      const int q = p0 + lane * pstep;
+      pend = __ballot(q < np && (every || A.cstat[q] == kPending));
+      pbase = p0;
+    }
+  };
+  next_pending();
+  if (!__syncthreads_or(qi < nq || pend != 0)) return;  // nothing for this workgroup
+  load_layers(A, T);
+  const ht_cluster_cfg& cfg = A.cfg;
+  const int cap = cfg.member_cap;
+  const double road = (double)cfg.road_sigmas * (double)cfg.sigma_rphi;
+  double ktol = (0.5 + (double)cfg.box_margin) * A.kap_bin;
+  if (ktol < 1e-6) ktol = 1e-6;
+  const double dtol = (0.5 + (double)cfg.box_margin) * A.d0_bin + road;
+  if (lane < 5) tot[wave][lane] = 0;
+  unsigned long long tests = 0;
+  uint32_t exec = 0;
+  constexpr float kInf = __builtin_inff();
+  // a hit that is no member is on nobody's road: its f is infinite or not a
+  // number, on layers of one radius from x, on others from x^2 + y^2
+  auto put = [&](int at, bool mem, float x, float y) {
+    S.xy[at] = make_float2(mem ? x : kInf, mem ? y : 0.0f);
+    return mem ? __builtin_fmaf(x, x, y * y) : kInf;
+  };
+  {
+    for (;;) {
+      // lane 16 g + L: layer L of the g-th of up to four candidates
+      int pg[4] = {-1, -1, -1, -1};
+      if (qi < nq) {
+        pg[0] = A.mcount[qi];
+        qi += pstep;
+      } else {
+        next_pending();
+        if (!pend) break;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          pg[g] = pend ? pbase + __builtin_ctzll(pend) * pstep : -1;
+          pend &= pend - 1ull;
+        }
+      }
+      const int g4 = lane >> 4;
+      const int pl4 = g4 == 0 ? pg[0] : (g4 == 1 ? pg[1] : (g4 == 2 ? pg[2] : pg[3]));
+      int lin_l = -1;
+      if (pl4 >= 0) lin_l = A.peaks[pl4].lin;
+      if (lin_l >= A.n_cells) lin_l = -1;
+      const LayerRun R = layer_run(A, T[lane & 15], lane & 15, lin_l);
+      const bool any_wide = __ballot(R.wide) != 0ull;
+      const int rend_l = row_scan_incl(R.len);  // end of layer L's run, the runs laid end to end
+#pragma unroll 1
+      for (int g = 0; g < 4; ++g) {
+        const int o = 16 * g;  // the candidate's first lane
+        const int p = bcasti(pl4, o);
+        if (p < 0) break;
+        const int i = bcasti(R.i, o), col = bcasti(R.col, o);
+        wave_sync();  // (the previous candidate's LDS is read)
+        // ---- members: a bit for each run hit, and their counts
+        const int total = bcasti(rend_l, o + HT_MAX_LAYERS - 1);
+        // short runs are staged all at once, layer L's from position bb_l on, four
+        // infinities behind each
+        const bool shortr = total <= kStage;
+        int bb_l = rend_l - R.len;  // first bit of layer L's run
+        int cnt_l = 0;              // its members
+        int n = 0;
+        bool keep_bits = true;
+        int wlo = 0, whi = 0;  // long runs: lane b holds word b of the bits
+        if (shortr) {
+          const int rbase = R.st - bb_l;
+          for (int t0 = 0; t0 < total; t0 += kWave) {
+            const int t = t0 + lane;
+            const int q = run_of(rend_l, o, t);
+            const int e = __shfl(rbase, q, kWave) + t;
+            const float s = __shfl(R.s, q, kWave), w = __shfl(R.w, q, kWave);
+            float adx = 0.0f;
+            bool mem = false;
+            if (t < total) {
+              const float4 v = A.srec[e];
+              mem = run_member(A, any_wide, i, col, e, v.z, s, w, &adx);
+              const float r2 = put(t + 4 * (q & 15), mem, v.x, v.y);
+              if (any_wide) S.q[t + 4 * (q & 15)] = r2;
+            }
+            const uint64_t m = __ballot(mem);
+            n += __popcll(m);
+            if (g4 == g) cnt_l += run_share(m, t0, bb_l, rend_l);
+          }
+          // lane 4 L + u: infinity u behind layer L's run
+          const int pad = __shfl(rend_l, o + (lane >> 2), kWave) + lane;
+          const float r2 = put(pad, false, 0.0f, 0.0f);
+          if (any_wide) S.q[pad] = r2;
+          bb_l += 4 * (lane & 15);
+        } else {
+          // layer by layer, each run from a bit position of its own word
+          const int words = (R.len + kWave - 1) / kWave;
+          const int wend = row_scan_incl(words);
+          bb_l = (wend - words) * kWave;
+          keep_bits = bcasti(wend, o + HT_MAX_LAYERS - 1) <= kRunWords;
+          unsigned layers = (unsigned)(__ballot(R.len > 0) >> o) & 0xffffu;
+          for (; layers && n <= cap; layers &= layers - 1u) {
+            const int L = o + __builtin_ctz(layers);
+            const int st = bcasti(R.st, L), len = bcasti(R.len, L), wb = bcasti(bb_l, L) >> 6;
+            const float s = bcastf(R.s, L), w = bcastf(R.w, L);
+            int c = 0;
+            for (int t0 = 0; t0 < len; t0 += 2 * kWave) {
+              // two words at a time, their loads in flight together
+              const int t = t0 + lane;
+              const int e0 = st + min(t, len - 1), e1 = st + min(t + kWave, len - 1);
+              const float ph0 = A.sphi[e0], ph1 = A.sphi[e1];
+              float adx;
+              const bool m0 = run_member(A, any_wide, i, col, e0, ph0, s, w, &adx) && t < len;
+              const uint64_t w0 = __ballot(m0);
+              c += __popcll(w0);
+              const int b = wb + (t0 >> 6);
+              if (keep_bits) {
+                if (lane == b) wlo = (int)(unsigned)w0;
+                if (lane == b) whi = (int)(unsigned)(w0 >> 32);
+              }
+              if (t0 + kWave < len) {
+                const bool m1 =
+                    run_member(A, any_wide, i, col, e1, ph1, s, w, &adx) && t + kWave < len;
+                const uint64_t w1 = __ballot(m1);
+                c += __popcll(w1);
+                if (keep_bits) {
+                  if (lane == b + 1) wlo = (int)(unsigned)w1;
+                  if (lane == b + 1) whi = (int)(unsigned)(w1 >> 32);
+                }
+              }
+            }
+            if (lane == L) cnt_l = c;
+            n += c;
+          }
+        }
+        const unsigned lmask = (unsigned)(__ballot(cnt_l > 0) >> o) & 0xffffu;
+        const int nS = __popc(lmask);
+        const bool over = n > cap;
+        if (lane == 0) tot[wave][over ? 2 : 3] += over ? 1ull : (unsigned long long)n;
+        if (over || nS < cfg.min_layers || nS < 3) {
+          if (lane == 0) {
+            A.cstat[p] = over ? -2 : -1;
+            A.cnl[p] = over ? 0 : nS;
+          }
+          continue;
+        }
+        // ---- the seed_k nearest members of each seed layer by (adx, hit): the
+        // smallest keys one after another
+        int Ls[3];
+        seed_layers(lmask, nS, cfg.min_layers, Ls);
+        const int kk = cfg.seed_k;
+        int ns[3];
+        int seed_l = 0;  // lane 4 s + r: the r-th seed of layer s
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+          const int c = bcasti(cnt_l, o + Ls[s]);
+          ns[s] = c < kk ? c : kk;
+        }
+#pragma unroll 1
+        for (int s = 0; s < 3; ++s) {
+          const int L = o + (s == 0 ? Ls[0] : (s == 1 ? Ls[1] : Ls[2]));
+          const int nsd = s == 0 ? ns[0] : (s == 1 ? ns[1] : ns[2]);
+          const int st = bcasti(R.st, L), len = bcasti(R.len, L);
+          const float sv = bcastf(R.s, L), wv = bcastf(R.w, L);
+          const int none = 0x7fffffff;
+          if (len <= 2 * kWave) {
+            // two hits per lane, the nearer first
+            float adx;
+            int a0 = none, h0 = 0, t0 = st + lane, a1 = none, h1 = 0, t1 = st + kWave + lane;
+#pragma unroll 1
+            for (int q = 0; q < len; q += kWave) {
+              const int e = st + min(q + lane, len - 1);
+              const float4 v = A.srec[e];
+              const int h = __float_as_int(v.w);
+              const bool mem = run_member(A, any_wide, i, col, e, v.z, sv, wv, &adx);
+              const int ka = mem && q + lane < len ? __float_as_int(adx) : none;
+              if (q == 0) {
+                a0 = ka;
+                h0 = h;
+              } else {
+                a1 = ka;
+                h1 = h;
+                if (a1 < a0 || (a1 == a0 && h1 < h0)) {
+                  int x = a0; a0 = a1; a1 = x;
+                  x = h0; h0 = h1; h1 = x;
+                  x = t0; t0 = t1; t1 = x;
+                }
+              }
+            }
+            for (int r = 0; r < nsd; ++r) {
+              const int win = wave_argmin(a0, h0);
+              const int t = bcasti(t0, win);
+              if (lane == 4 * s + r) seed_l = t;
+              if (lane == win) { a0 = a1; h0 = h1; t0 = t1; a1 = none; }
+            }
+          } else {
+            int pa = -1, ph = -1;  // the last key taken
+            for (int r = 0; r < nsd; ++r) {
+              int a = none, h = 0, t = 0;
+              for (int q = lane; q < len; q += kWave) {
+                const float4 v = A.srec[st + q];
+                float adx;
+                if (!run_member(A, any_wide, i, col, st + q, v.z, sv, wv, &adx)) continue;
+                const int ka = __float_as_int(adx), kh = __float_as_int(v.w);
+                if (!(ka > pa || (ka == pa && kh > ph))) continue;
+                if (ka < a || (ka == a && kh < h)) { a = ka; h = kh; t = st + q; }
+              }
+              const int win = wave_argmin(a, h);
+              pa = bcasti(a, win);
+              ph = bcasti(h, win);
+              const int e = bcasti(t, win);
+              if (lane == 4 * s + r) seed_l = e;
+            }
+          }
+        }
+        if (lane < 12) {
+          const int s = lane >> 2;
+          if ((lane & 3) < (s == 0 ? ns[0] : (s == 1 ? ns[1] : ns[2])))
+            S.sxy[s][lane & 3] = A.sxy[seed_l];
+        }
+        const unsigned smask = (1u << Ls[0]) | (1u << Ls[1]) | (1u << Ls[2]);
+        const unsigned nsm = lmask & ~smask;
+        const int n_ns = __popc(nsm);
+        const int orderv = visit_order(nsm, o, cnt_l);
+        if (A.origin_seed) ns[0] = 1;
+        wave_sync();
+        // ---- seed circles: lane = 16 a + 4 b + c (seed_k <= 4), in float32 for the
+        // search, in float64 where the box check needs it
+        const int ia = lane >> 4, ib = (lane >> 2) & 3, ic = lane & 3;
+        const bool combo = ia < ns[0] && ib < ns[1] && ic < ns[2];
+        double cA = 0.0, cB = 0.0, cC = 0.0, cD = 0.0;
+        auto circle64 = [&]() {
+          const double2 qa = A.origin_seed ? make_double2(0.0, 0.0) : S.sxy[0][ia];
+          const double2 qb = S.sxy[1][ib], qc = S.sxy[2][ic];
+          return circle3(qa.x, qa.y, qb.x, qb.y, qc.x, qc.y, &cA, &cB, &cC, &cD);
+        };
+        Circle32 C = {0.0f, 0.0f, 0.0f, 0.0f, false, false};
+        const double kapc = A.kapc[col % A.n_qpt], d0c = A.d0c[col / A.n_qpt];
+        if (combo)
+          C = circle32(A.origin_seed ? make_double2(0.0, 0.0) : S.sxy[0][ia], S.sxy[1][ib],
+                       S.sxy[2][ic], (float)kapc, (float)d0c, (float)ktol, (float)dtol);
+        bool active = C.ok;
+        if (__ballot(C.unsure)) {
+          if (C.unsure) {
+            active = circle64();
+            if (active) {
+              const double kap = 2.0 * cA;
+              const double sq = sqrt(cB * cB + cC * cC);
+              const double d0 = 2.0 * cD / (1.0 + sq);
+              active = (fabs(kap - kapc) <= ktol) && (fabs(d0 - d0c) <= dtol);
+              C.a = (float)cA;
+              C.b = (float)cB;
+              C.c = (float)cC;
+              C.d = (float)cD;
+            }
+          }
+        }
+        tests += (unsigned long long)__popcll(__ballot(active)) * (unsigned long long)n;
+        // |dist| >= |f| / (1 + |A||f|), so a hit with |f| > road / (1 - road |A|) is
+        // off the road, and road / (1 - x) <= road (1 + 2x) for x <= 1/2 (pre).  The
+        // float32 f is within 1.5e-6 of the sum of its terms' magnitudes of the
+        // float64 one (the common factor, the coefficients', the coordinates', q's and
+        // three fused multiply-adds' rounding is below 1e-6 of it).  With |A f| <= 1/40
+        // the distance is f - A f^2 within 2.2 A^2 |f|^3 and its slope in f at most 1.06.
+        float Af = 0.0f, Bf = 0.0f, Cf = 0.0f, Df = 0.0f, pre = 0.0f;
+        float iR = 0.0f, tB = 0.0f;  // 1 / |(B, C)|, and its direction as a bucket coordinate
+        if (active) {
+          Af = C.a;
+          Bf = C.b;
+          Cf = C.c;
+          Df = C.d;
+          const float ra = (float)road * fabsf(Af);
+          pre = ra <= 0.49f ? (float)road * (1.0f + 2.0f * ra) * 1.00001f : kInf;
+          iR = __builtin_amdgcn_rsqf(Bf * Bf + Cf * Cf);
+          tB = bucket_coord(atan2_coarse(Cf, Bf));
+        }
+        // ---- road search
+#pragma unroll
+        for (int L = 0; L < HT_MAX_LAYERS; L += 2)
+          *reinterpret_cast<uint32_t*>(&S.hit[lane][L]) = 0xffffffffu;
+        int on_road = 0;     // layers with a hit that may be on the road
+        int amb2 = -1;       // layer << 16 | place of a second hit that may be nearer
+        unsigned ambm = 0u;  // layers with more hits that may be the nearest
+        unsigned sseq = smask;
+        int remaining = nS;
+#pragma unroll 1
+        for (int it = 0; it < nS; ++it) {
+          int L;
+          if (it < n_ns) {
+            L = __builtin_amdgcn_readlane(orderv, it);
+          } else {
+            L = __builtin_ctz(sseq);
+            sseq &= sseq - 1u;
+          }
+          // lanes that cannot reach min_layers any more
+          active = active && on_road + remaining >= cfg.min_layers;
+          --remaining;
+          if (__ballot(active) == 0ull) break;
+          const int st = bcasti(R.st, o + L), len = bcasti(R.len, o + L);
+          const int bb = bcasti(bb_l, o + L);
+          const RunLayer t = T[L];
+          const float mag = __builtin_fmaf(
+              fabsf(Af), t.rhi * t.rhi,
+              __builtin_fmaf(fabsf(Bf) + fabsf(Cf), t.rhi, fabsf(Df)));
+          const float epsf = 1.5e-6f * mag;
+          const float thr = pre + epsf;
+          const bool one_r = t.hw == 0.0f;
+          const float base = __builtin_fmaf(Af, t.rm * t.rm, Df);  // layers of one radius
+          const int c0 = bcasti(R.c0, o + L);
+          const int32_t* row = A.bkt_off + L * kRunRow + c0;
+          const int nb = bcasti(R.nb, o + L);
+          const bool tab = nb < kTab && len > kScanAll;
+          if (tab)
+            for (int q = lane; q <= nb; q += kWave) S.tab[q] = (uint16_t)(row[q] - st);
+          // hits [g0, g0 + kStage) of a long run into LDS
+          auto stage = [&](int g0) {
+            wave_sync();
+            const int ge = min(len, g0 + kStage);
+#pragma unroll 1
+            for (int q0 = g0; q0 < ge; q0 += kWave) {
+              const int q = q0 + lane;
+              const float4 v = A.srec[st + min(q, len - 1)];
+              bool mem;
+              if (keep_bits) {
+                const int b = (bb + q0) >> 6;
+                mem = __builtin_amdgcn_inverse_ballot_w64(
+                    ((uint64_t)(unsigned)bcasti(whi, b) << 32) | (unsigned)bcasti(wlo, b));
+              } else {
+                float adx;
+                mem = run_member(A, any_wide, i, col, st + min(q, len - 1), v.z, bcastf(R.s, o + L),
+                                 bcastf(R.w, o + L), &adx);
+              }
+              // (the places behind the last hit, at most 63, are no members)
+              const float r2 = put(q - g0, mem && q < ge, v.x, v.y);
+              if (!one_r) S.q[q - g0] = r2;
+            }
+            if (lane < 4) {
+              const float r2 = put(ge - g0 + lane, false, 0.0f, 0.0f);
+              if (!one_r) S.q[ge - g0 + lane] = r2;
+            }
+            wave_sync();
+          };
+          // the places of the run in the buckets that the lane's road reaches
+          int ea = 0, eb = 0, ec = 0, ed = 0;  // [ea, eb) and [ec, ed)
+          if (active && len <= kScanAll) {
+            eb = len;
+          } else if (active) {
+            const float x0 = -(__builtin_fmaf(Af, t.rm, Df * t.irm)) * iR;
+            const float d = ((thr + 1e-5f * mag) * t.irlo +
+                             __builtin_fmaf(fabsf(Df), t.irlo * t.irlo, fabsf(Af)) * t.hw) * iR +
+                            1e-6f;
+            const float ax = fabsf(x0), xm = ax + d;
+            if (!(ax - d > 1.0f)) {
+              constexpr float kPerRad = (float)kBuckets / k2PiF;
+              const bool one = !(xm <= 0.9995f);  // the arcs meet at tB or opposite it
+              const float ac = acos_coarse(one ? fmaxf(ax - d, -1.0f) : x0);
+              const float h = one ? ac : d * __builtin_amdgcn_rsqf(1.0f - xm * xm) * 1.001f;
+              const float hb = __builtin_fmaf(h, kPerRad, kAcosPad * kPerRad + 0.02f);
+              const float off = one ? (x0 < 0.0f ? 0.5f * (float)kBuckets : 0.0f) : ac * kPerRad;
+              int lo0 = 0, hi0 = nb - 1, lo1 = 1, hi1 = 0;
+              if (hb < 0.25f * (float)kBuckets && nb <= kBuckets / 2) {
+                // the arcs' middles relative to the run, on the image nearest its middle
+                const float mid = 0.5f * (float)nb;
+                const float tc = tB - ((float)c0 + mid);
+                auto rel = [&](float z) {
+                  return __builtin_fmaf(-(float)kBuckets,
+                                        __builtin_rintf(z * (1.0f / (float)kBuckets)), z) + mid;
+                };
+                const float z0 = rel(tc - off), z1 = rel(tc + off);
+                lo0 = max((int)floorf(z0 - hb), 0);
+                hi0 = min((int)floorf(z0 + hb), nb - 1);
+                lo1 = max((int)floorf(z1 - hb), 0);
+                hi1 = one ? -1 : min((int)floorf(z1 + hb), nb - 1);
+                // overlapping arcs become one
+                if (lo0 <= hi0 && lo1 <= hi1 && lo1 <= hi0 && lo0 <= hi1) {
+                  lo0 = min(lo0, lo1);
+                  hi0 = max(hi0, hi1);
+                  hi1 = -1;
+                }
+              }
+              if (tab) {
+                if (lo0 <= hi0) { ea = S.tab[lo0]; eb = S.tab[hi0 + 1]; }
+                if (lo1 <= hi1) { ec = S.tab[lo1]; ed = S.tab[hi1 + 1]; }
+              } else {
+                if (lo0 <= hi0) { ea = row[lo0] - st; eb = row[hi0 + 1] - st; }
+                if (lo1 <= hi1) { ec = row[lo1] - st; ed = row[hi1 + 1] - st; }
+              }
+            }
+          }
+          // The smallest |f| among the hits of the lane's places, where it stands, and
+          // the second smallest, four hits at a time (those behind the last are hits
+          // of the run or no members: visiting them changes nothing).  |f| and the
+          // visit's number share a word, the number in the low 9 bits: the order of
+          // the words is the order of |f| to 2^-14, and infinities and what is not a
+          // number come last.
+          constexpr unsigned kNum = 511u;
+          const int at0 = shortr ? bb : 0;
+          const unsigned top = __float_as_uint(thr) & ~kNum;  // no hit at or beyond it
+          float b1 = thr, b2 = thr, b3 = thr;
+          int be = -1, be2 = -1;
+#pragma unroll 1
+          for (int g0 = 0; g0 < len; g0 += kStage) {
+            if (!shortr) stage(g0);
+            // the lower arc first, the other from behind what that visit reads (a hit
+            // visited twice would look like two)
+            const bool swap = ec < ed && ec < ea;
+            const int fa = swap ? ec : ea, fb = swap ? ed : eb;
+            const int ga = max(swap ? ea : ec, fa < fb ? fa + ((fb - fa + 3) & ~3) : 0);
+            const int gb = swap ? eb : ed;
+            unsigned k1 = top, k2 = top, k3 = top;
+            int num = 0, num1 = 0;
+#pragma unroll 1
+            for (int arc = 0; arc < 2; ++arc) {
+              int e = max(arc ? ga : fa, g0) - g0;
+              const int end = min(arc ? gb : fb, g0 + kStage) - g0;
+              while (__ballot(e < end)) {
+                if (e < end) {
+                  constexpr int kW = 4;
+                  float f[kW];
+                  float2 v[kW];
+#pragma unroll
+                  for (int u = 0; u < kW; ++u) v[u] = S.xy[at0 + e + u];
+                  if (one_r) {
+#pragma unroll
+                    for (int u = 0; u < kW; ++u) f[u] = base;
+                  } else {
+#pragma unroll
+                    for (int u = 0; u < kW; ++u) f[u] = __builtin_fmaf(Af, S.q[at0 + e + u], Df);
+                  }
+#pragma unroll
+                  for (int u = 0; u < kW; ++u) {
+                    f[u] = __builtin_fmaf(Bf, v[u].x, __builtin_fmaf(Cf, v[u].y, f[u]));
+                    const unsigned key =
+                        (__float_as_uint(f[u]) & (0x7fffffffu & ~kNum)) | (unsigned)(num + u);
+                    // (medians: k1 <= k2 <= k3)
+                    k3 = max(min(k2, k3), min(max(k2, k3), key));
+                    k2 = max(min(k1, k2), min(max(k1, k2), key));
+                    k1 = min(k1, key);
+                  }
+                  e += kW;
+                }
+                num += 4;
+              }
+              if (arc == 0) num1 = num;
+            }
+            // this stage's three smallest into the run's
+            auto place = [&](unsigned key) {
+              const int x = (int)(key & kNum);
+              return x < num1 ? max(fa, g0) + x : max(ga, g0) + x - num1;
+            };
+            auto insert = [&](unsigned key) {
+              if (key >= top) return;
+              const float f = __uint_as_float(key & ~kNum);
+              if (f < b1) {
+                b3 = b2; b2 = b1; be2 = be;
+                b1 = f; be = place(key);
+              } else if (f < b2) {
+                b3 = b2;
+                b2 = f; be2 = place(key);
+              } else {
+                b3 = fminf(b3, f);
+              }
+            };
+            insert(k1);
+            insert(k2);
+            insert(k3);
+          }
+          // The hit of the smallest |f| is the nearest when the second smallest is
+          // farther by twice the errors: 1.1 epsf of f, the words' 2^-14, and |A| f^2
+          // (with the expansion's rest) between |f| and the distance.  Where the
+          // expansion does not hold nothing is far enough.
+          const float aw = fabsf(Af) * thr;
+          auto far = [&](float f) {
+            return aw <= 0.025f &&
+                   (f >= thr || f > b1 + __builtin_fmaf(2.2f, epsf, (1.2f * aw + 1.3e-4f) * (b1 + f)) +
+                                        1e-6f * thr);
+          };
+          if (be >= 0 && !far(b2)) {
+            if (amb2 < 0 && far(b3))
+              amb2 = (L << 16) | be2;
+            else
+              ambm |= 1u << L;
+          }
+          if (active && be >= 0) {
+            S.hit[lane][L] = (uint16_t)be;
+            ++on_road;
+          }
+          wave_sync();
+        }
+        active = active && on_road >= cfg.min_layers;
+        if (__ballot(active) == 0ull) {
+          if (lane == 0) { A.cstat[p] = -1; A.cnl[p] = nS; }
+          continue;
+        }
+        if (active) (void)circle64();
+        // ---- a lane's ambiguous layer: the second hit when it is nearer (or as near
+        // with a lower index)
+        if (!active) amb2 = -1;
+        if (__ballot(amb2 >= 0)) {
+          const int st = __shfl(R.st, o + (amb2 >= 0 ? amb2 >> 16 : 0), kWave);
+          if (amb2 >= 0) {
+            exec += 2;
+            const int L = amb2 >> 16, e2 = st + (amb2 & 0xffff), e1 = st + S.hit[lane][L];
+            const double2 xy1 = A.sxy[e1], xy2 = A.sxy[e2];
+            const double q1 = A.sq[e1], q2 = A.sq[e2];
+            const double d1 = fabs(circle_dist(cA, cB, cC, cD, xy1.x, xy1.y, q1));
+            const double d2 = fabs(circle_dist(cA, cB, cC, cD, xy2.x, xy2.y, q2));
+            if (d2 < d1 || (d2 == d1 && __float_as_int(A.srec[e2].w) < __float_as_int(A.srec[e1].w)))
+              S.hit[lane][L] = (uint16_t)(amb2 & 0xffff);
+          }
+        }
+        // ---- other ambiguous layers: a lane's layer at a time, its run's hits over the
+        // wave's lanes
+        if (!active) ambm = 0u;
+        for (uint64_t al = __ballot(ambm != 0u); al; al &= al - 1ull) {
+          const int ln = __builtin_ctzll(al);
+          const double A1 = readlane_d(cA, ln), B1 = readlane_d(cB, ln);
+          const double C1 = readlane_d(cC, ln), D1 = readlane_d(cD, ln);
+          for (unsigned am = (unsigned)bcasti((int)ambm, ln); am; am &= am - 1u) {
+            const int L = __builtin_ctz(am);
+            const int st = bcasti(R.st, o + L), len = bcasti(R.len, o + L);
+            int be = -1, bh = 0;
+            double bd = 0.0;
+            for (int t = lane; t < len; t += kWave) {
+              const float4 v = A.srec[st + t];
+              float adx;
+              if (!run_member(A, any_wide, i, col, st + t, v.z, bcastf(R.s, o + L),
+                              bcastf(R.w, o + L), &adx))
+                continue;
+              ++exec;
+              const double2 xy = A.sxy[st + t];
+              const double dist = fabs(circle_dist(A1, B1, C1, D1, xy.x, xy.y, A.sq[st + t]));
+              const int h = __float_as_int(v.w);
+              if (dist <= road && (be < 0 || dist < bd || (dist == bd && h < bh))) {
+                be = t;
+                bh = h;
+                bd = dist;
+              }
+            }
+            // the nearest, then the lowest hit index
+            const long long db = __double_as_longlong(bd);
+            const int m = wave_min_i32(be < 0 ? 0x7fffffff : (int)(db >> 32));
+            const bool top = be >= 0 && (int)(db >> 32) == m;
+            const int lo = (int)((unsigned)db ^ 0x80000000u);
+            const int m2 = wave_min_i32(top ? lo : 0x7fffffff);
+            const int win = wave_argmin(top && lo == m2 ? bh : 0x7fffffff, 0);
+            const int pl = win < 0 ? (int)kNoHit : bcasti(be, win);
+            if (lane == ln) S.hit[lane][L] = (uint16_t)pl;
+          }
+        }
+        // ---- float64 distances of the lanes still in question, four layers at a
+        // time (their loads in flight together), and the sum of squares in layer order
+        int n_in = active ? 0 : -1;
+        double ss = 0.0;
+#pragma unroll 1
+        for (unsigned lm = lmask; lm;) {
+          int e[4], Lu[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            e[u] = -1;
+            Lu[u] = 0;
+            if (lm) {
+              Lu[u] = __builtin_ctz(lm);
+              lm &= lm - 1u;
+              const int pl = S.hit[lane][Lu[u]];
+              if (active && pl != kNoHit) e[u] = bcasti(R.st, o + Lu[u]) + pl;
+            }
+          }
+          double2 xy[4];
+          double q[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            xy[u] = make_double2(0.0, 0.0);
+            q[u] = 0.0;
+            if (e[u] >= 0) {
+              xy[u] = A.sxy[e[u]];
+              q[u] = A.sq[e[u]];
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (e[u] < 0) continue;
+            ++exec;
+            const double d = fabs(circle_dist(cA, cB, cC, cD, xy[u].x, xy[u].y, q[u]));
+            if (d <= road) {
+              ++n_in;
+              ss += d * d;
+            } else {
+              S.hit[lane][Lu[u]] = kNoHit;
+            }
+          }
+        }
+        // best lane: most inliers, then smallest sum, then lowest combination index
+        const int best_n = wave_max_i32(n_in);
+        if (best_n < cfg.min_layers) {
+          if (lane == 0) { A.cstat[p] = -1; A.cnl[p] = nS; }
+          continue;
+        }
+        const long long sb = __double_as_longlong(ss);  // positive: orders like ss
+        const bool best = n_in == best_n;
+        const int win = wave_argmin(best ? (int)(sb >> 32) : 0x7fffffff,
+                                    (int)((unsigned)sb ^ 0x80000000u));
+        const double best_ss = readlane_d(ss, win);
+        if (lane == win) {
+          A.cstat[p] = best_n;
+          A.cnl[p] = nS;
+          double* geo = A.cgeo + (size_t)p * 5;
+          geo[0] = ss; geo[1] = cA; geo[2] = cB; geo[3] = cC; geo[4] = cD;
+        }
+        if (lane == 0) tot[wave][1] += 1;
+        wave_sync();
+        const int my_st = __shfl(R.st, o + (lane & 15), kWave);
+        if (lane < HT_MAX_LAYERS) {
+          const int pl = S.hit[win][lane];
+          const int h = pl == kNoHit ? -1 : __float_as_int(A.srec[my_st + pl].w);
+          A.chit[(size_t)p * HT_MAX_LAYERS + lane] = h;
+          if (h >= 0)
+            atomicMax(&A.owner_key[h],
+                      own_key(best_n, best_ss, p));
+        }
+      }
+    }
+  }
+  unsigned long long ex = exec;
+  for (int off = kWave / 2; off > 0; off >>= 1) ex += __shfl_xor(ex, off);
+  if (lane == 0) {
+    tot[wave][0] = tests;
+    tot[wave][4] = ex;
+  }
+  add_totals<kRunWaves>(A, tot);
+}
+
 // ---- ownership -----------------------------------------------------------------
 // (the seed search offers each inlier hit its candidate's key, own_key)
 __device__ __forceinline__ int owned_count(const AssocArgs& A, int p) {
@@ -2240,18 +3421,27 @@ __device__ void fit_tracks(const AssocArgs& A, int bid, int nblk) {
 // A fixed parameter (one-column grid axis) keeps a zero row and column in
 // the covariance, so its gain is zero and it never moves.  Status 1 when a
 // hit has |u| >= 1, 2 when an innovation variance is not positive.  The
-// filter is sequential in the hits, so one thread owns one track.
+// filter is sequential in the hits, but the model of a pass is not: 16 lanes
+// per track evaluate it, one layer each, and then all step through the hits
+// with the same numbers (one thread per track evaluated every arcsine in the
+// sequential chain; 116 tracks of ten hits: 31 -> 15 us).
+struct KfHit {
+  double res, h1, h2, var;  // residual, Jacobian (its first entry is 1), variance
+};
 template <int NB>
 __global__ __launch_bounds__(64) void kf_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
+  __shared__ KfHit m[64];
   const int ntrk = min(A.sc[S_NTRK], A.out.track_cap);
-  const int t = blockIdx.x * 64 + threadIdx.x;
-  if (t >= ntrk) return;
+  const int lane = threadIdx.x, L0 = lane & (HT_MAX_LAYERS - 1), g = lane & ~(HT_MAX_LAYERS - 1);
+  const int t = blockIdx.x * (64 / HT_MAX_LAYERS) + lane / HT_MAX_LAYERS;
+  if ((int)blockIdx.x * (64 / HT_MAX_LAYERS) >= ntrk) return;
+  const bool there = t < ntrk;
   const bool fk = A.n_qpt > 1, fd = A.n_d0 > 1;
-  ht_track& tr = A.out.tracks[t];
-  const int p = A.trk_peak[t];
-  const double* g = A.cgeo + (size_t)p * 5;
-  const double gA = g[1], gB = g[2], gC = g[3], gD = g[4];
+  ht_track& tr = A.out.tracks[there ? t : 0];
+  const int p = A.trk_peak[there ? t : 0];
+  const double* geo = A.cgeo + (size_t)p * 5;
+  const double gA = geo[1], gB = geo[2], gC = geo[3], gD = geo[4];
   const int lin = tr.lin;
   const int i = lin % A.n_phi, col = lin / A.n_phi, j = col % A.n_qpt, k = col / A.n_qpt;
   const double kap_c = A.kapc[j];
@@ -2263,54 +3453,75 @@ __global__ __launch_bounds__(64) void kf_kernel(AssocBatch<NB> AB) {
   x[2] = fd ? 2.0 * gD / (1.0 + sq0) : d0_c;
   const double prior[3] = {0.01, fk ? 1e-4 : 0.0, fd ? 100.0 : 0.0};
   const double s2 = (double)A.cfg.sigma_rphi * (double)A.cfg.sigma_rphi;
-  int hit[HT_MAX_LAYERS];
-  for (int L = 0; L < HT_MAX_LAYERS; ++L) hit[L] = tr.hits[L];
+  const int h = there ? tr.hits[L0] : -1;
+  const double rr = h >= 0 ? (double)A.r[h] : 1.0, ph = h >= 0 ? (double)A.phi[h] : 0.0;
+  // this lane's hit at the state x; false when |u| >= 1
+  auto model = [&](double* u_out) {
+    const double den = 1.0 + x[1] * x[2];
+    const double u = (x[1] * (rr * rr + x[2] * x[2]) + 2.0 * x[2]) / (2.0 * rr * den);
+    *u_out = u;
+    return fabs(u) < 1.0;
+  };
+  const unsigned have = (unsigned)(__ballot(h >= 0) >> g) & 0xffffu;  // the track's layers
   int status = 0;
-  for (int it = 0; it < A.cfg.fit_iters && status == 0; ++it) {
-    double P[3][3];
-    double dp[3] = {0.0, 0.0, 0.0};
-    for (int a = 0; a < 3; ++a)
-      for (int b = 0; b < 3; ++b) P[a][b] = a == b ? prior[a] : 0.0;
-    for (int L = 0; L < HT_MAX_LAYERS; ++L) {
-      const int h = hit[L];
-      if (h < 0) continue;
-      const double rr = (double)A.r[h], ph = (double)A.phi[h];
+  for (int it = 0; it < A.cfg.fit_iters; ++it) {
+    double u;
+    const bool good = h < 0 || model(&u);
+    const unsigned bad = (unsigned)(__ballot(!good) >> g) & 0xffffu;
+    __syncthreads();
+    if (h >= 0 && good) {
       const double kap = x[1], d0 = x[2];
       const double den = 1.0 + kap * d0;
-      const double u = (kap * (rr * rr + d0 * d0) + 2.0 * d0) / (2.0 * rr * den);
-      if (!(fabs(u) < 1.0)) { status = 1; break; }
       const double sq = sqrt(1.0 - u * u);
-      const double res = wrap_pi(ph - (x[0] + asin(u)));
-      double H[3];
-      H[0] = 1.0;
-      H[1] = fk ? (rr * rr - d0 * d0) / (2.0 * rr * den * den) / sq : 0.0;
-      H[2] = fd ? (den * den + 1.0 - kap * kap * rr * rr) / (2.0 * rr * den * den) / sq : 0.0;
-      double PH[3];
-      for (int a = 0; a < 3; ++a) PH[a] = P[a][0] * H[0] + P[a][1] * H[1] + P[a][2] * H[2];
-      const double S = s2 / (rr * rr) + H[0] * PH[0] + H[1] * PH[1] + H[2] * PH[2];
-      if (!(S > 0.0)) { status = 2; break; }
-      const double innov = res - H[0] * dp[0] - H[1] * dp[1] - H[2] * dp[2];
-      double K[3];
-      for (int a = 0; a < 3; ++a) K[a] = PH[a] / S;
-      for (int a = 0; a < 3; ++a) dp[a] += K[a] * innov;
-      for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) P[a][b] -= K[a] * PH[b];
+      KfHit v;
+      v.res = wrap_pi(ph - (x[0] + asin(u)));
+      v.h1 = fk ? (rr * rr - d0 * d0) / (2.0 * rr * den * den) / sq : 0.0;
+      v.h2 = fd ? (den * den + 1.0 - kap * kap * rr * rr) / (2.0 * rr * den * den) / sq : 0.0;
+      v.var = s2 / (rr * rr);
+      m[lane] = v;
     }
-    if (status != 0) break;
-    for (int a = 0; a < 3; ++a) x[a] += dp[a];
+    __syncthreads();
+    if (status == 0) {
+      double P[3][3];
+      double dp[3] = {0.0, 0.0, 0.0};
+      for (int a = 0; a < 3; ++a)
+        for (int b = 0; b < 3; ++b) P[a][b] = a == b ? prior[a] : 0.0;
+      for (unsigned lm = have; lm; lm &= lm - 1u) {
+        const int L = __builtin_ctz(lm);
+        if ((bad >> L) & 1u) { status = 1; break; }
+        const KfHit v = m[g + L];
+        const double H[3] = {1.0, v.h1, v.h2};
+        double PH[3];
+        for (int a = 0; a < 3; ++a) PH[a] = P[a][0] * H[0] + P[a][1] * H[1] + P[a][2] * H[2];
+        const double S = v.var + H[0] * PH[0] + H[1] * PH[1] + H[2] * PH[2];
+        if (!(S > 0.0)) { status = 2; break; }
+        const double innov = v.res - H[0] * dp[0] - H[1] * dp[1] - H[2] * dp[2];
+        double K[3];
+        for (int a = 0; a < 3; ++a) K[a] = PH[a] / S;
+        for (int a = 0; a < 3; ++a) dp[a] += K[a] * innov;
+        for (int a = 0; a < 3; ++a)
+          for (int b = 0; b < 3; ++b) P[a][b] -= K[a] * PH[b];
+      }
+      if (status == 0)
+        for (int a = 0; a < 3; ++a) x[a] += dp[a];
+    }
   }
+  // chi2 at the final state, summed in layer order
+  double u, z2 = 0.0;
+  const bool good = h < 0 || model(&u);
+  const unsigned bad = (unsigned)(__ballot(!good) >> g) & 0xffffu;
+  __syncthreads();
+  if (h >= 0 && good) {
+    const double z = rr * wrap_pi(ph - (x[0] + asin(u))) / (double)A.cfg.sigma_rphi;
+    z2 = z * z;
+  }
+  m[lane].res = z2;
+  __syncthreads();
   double chi2 = 0.0;
   if (status == 0) {
-    for (int L = 0; L < HT_MAX_LAYERS; ++L) {
-      const int h = hit[L];
-      if (h < 0) continue;
-      const double rr = (double)A.r[h], ph = (double)A.phi[h];
-      const double den = 1.0 + x[1] * x[2];
-      const double u = (x[1] * (rr * rr + x[2] * x[2]) + 2.0 * x[2]) / (2.0 * rr * den);
-      if (!(fabs(u) < 1.0)) { status = 1; break; }
-      const double z = rr * wrap_pi(ph - (x[0] + asin(u))) / (double)A.cfg.sigma_rphi;
-      chi2 += z * z;
-    }
+    if (bad) status = 1;
+    else
+      for (unsigned lm = have; lm; lm &= lm - 1u) chi2 += m[g + __builtin_ctz(lm)].res;
   }
   if (status != 0) {
     x[0] = -kPi + ((double)i + 0.5) * (2.0 * kPi / (double)A.n_phi);
@@ -2318,11 +3529,13 @@ __global__ __launch_bounds__(64) void kf_kernel(AssocBatch<NB> AB) {
     x[2] = d0_c;
     chi2 = -1.0;
   }
-  tr.status = status;
-  tr.phi0 = (float)wrap_pi(x[0]);
-  tr.qpt = (float)(-x[1] / A.cb);
-  tr.d0 = (float)x[2];
-  tr.chi2 = (float)chi2;
+  if (there && L0 == 0) {
+    tr.status = status;
+    tr.phi0 = (float)wrap_pi(x[0]);
+    tr.qpt = (float)(-x[1] / A.cb);
+    tr.d0 = (float)x[2];
+    tr.chi2 = (float)chi2;
+  }
 }
 
 // ---- second transform --------------------------------------------------------------
@@ -2597,13 +3810,6 @@ __device__ void write_counts(const AssocArgs& A, int n_mem) {
   c[7] = 0;
 }
 
-__device__ __forceinline__ double readlane_d(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 // pass 2: members in track order and the isotropy, one wave per object.  An
 // object's members start after those of the objects before it (the wave sums
 // their counts).  The tracks are tested kVGroup chunks of 64 at a time (their
@@ -2678,7 +3884,8 @@ template <int CAP, int NB>
 void launch_refine(const AssocBatch<NB>& AB, int peak_cap, hipStream_t s, int n_lo = 0,
                    int n_hi = 0x7fffffff) {
   constexpr int W = RefineShape<CAP>::kWaves;
-  refine_kernel<CAP, NB><<<dim3(blocks_for(peak_cap, W), 1, NB), W * kWave, 0, s>>>(AB, n_lo, n_hi);
+  const int blocks = blocks_for(peak_cap, W);
+  refine_kernel<CAP, NB><<<dim3(blocks < kSweepGrid ? blocks : kSweepGrid, 1, NB), W * kWave, 0, s>>>(AB, n_lo, n_hi);
 }
 
 // The arguments of one event's assoc_cluster.
@@ -2723,8 +3930,6 @@ AssocArgs make_args(const Plan& P, const float* r, const float* phi, const uint8
   A.n_peaks = n_peaks;
   A.peak_cap = peak_cap;
   A.cfg = cfg;
-  A.pbits = P.d_pbits;
-  A.col_first = P.d_col_first;
   A.mcount = P.d_mcount;
   A.pool = P.d_mem;
   A.cstat = P.d_cstat;
@@ -2745,12 +3950,15 @@ AssocArgs make_args(const Plan& P, const float* r, const float* phi, const uint8
   A.vtile = P.d_vtile;
   A.sc = P.d_scalars;
   A.spread = P.d_spread;
-  A.cls = P.d_cls;
+  A.lay = P.d_lay;
   A.bkt = P.d_bkt;
   A.bkt_off = P.d_bkt_off;
   A.hkey = P.d_hkey;
-  A.shit = P.d_shit;
+  A.srec = P.d_srec;
+  A.srad = P.d_srad;
   A.sphi = P.d_sphi;
+  A.sxy = P.d_sxy;
+  A.sq = P.d_sq;
   A.out = out;
   return A;
 }
@@ -2767,46 +3975,43 @@ int assoc_sequence(const AssocBatch<NB>& AB, const Plan* const* P, int32_t n_hit
   const ht_cluster_cfg& cfg = AB.a[0].cfg;
   const ht_cluster_out& out = AB.a[0].out;
   if (cfg.member_cap > kMaxMembers) return HT_EUNSUPPORTED;
-  const int words = P0.n_tiles * 8 + 2;
-  const int64_t init_n = words > n_hits ? words : n_hits;
   P0.prof_mark(HT_STAGE_ASSOC, 0, s);
   const int surv_tiles = (peak_cap + 255) / 256 > 0 ? (peak_cap + 255) / 256 : 1;
-  init_kernel<NB><<<dim3(blocks_for(init_n, 256), 1, NB), 256, 0, s>>>(AB, words,
-                                                                      (surv_tiles + 63) / 64);
-  HT_CHECK(hipGetLastError());
-  const int hblocks = blocks_for(n_hits, 256) < 256 ? blocks_for(n_hits, 256) : 256;
-  {
-    const int mblocks = blocks_for(peak_cap, 256);
-    mark_kernel<NB><<<dim3(mblocks + hblocks, 1, NB), 256, 0, s>>>(AB, mblocks);
-    HT_CHECK(hipGetLastError());
-  }
+  const int surv_groups = (surv_tiles + 63) / 64;
   const int col_tiles = (g.n_qpt + kWave - 1) / kWave;
   dim3 sweep(col_tiles, g.n_d0, hit_slices(col_tiles * g.n_d0, n_hits) * NB);
-  P0.prof_mark(HT_STAGE_MEMBERS, 0, s);
-  {
+  if (n_hits <= kPrepHits) {
+    P0.prof_mark(HT_STAGE_MEMBERS, 0, s);
+    prep_small_kernel<NB><<<dim3(9, 1, NB), kPrepThreads, 0, s>>>(AB, surv_groups);
+    HT_CHECK(hipGetLastError());
+  } else {
+    const int64_t init_n = kBucketKeys > n_hits ? kBucketKeys : n_hits;
+    init_kernel<NB><<<dim3(blocks_for(init_n, 256), 1, NB), 256, 0, s>>>(AB, surv_groups);
+    HT_CHECK(hipGetLastError());
+    const int hblocks = blocks_for(n_hits, 256) < 256 ? blocks_for(n_hits, 256) : 256;
     const dim3 hgrid(hblocks, 1, NB);
+    P0.prof_mark(HT_STAGE_MEMBERS, 0, s);
+    layers_kernel<NB><<<hgrid, 256, 0, s>>>(AB);
+    HT_CHECK(hipGetLastError());
     bcount_kernel<NB><<<hgrid, 256, 0, s>>>(AB);
     HT_CHECK(hipGetLastError());
-    const int32_t* bc[NB];
-    int32_t* bo[NB];
-    int32_t* bt[NB];
-    for (int b = 0; b < NB; ++b) {
-      bc[b] = P[b]->d_bkt;
-      bo[b] = P[b]->d_bkt_off;
-      bt[b] = P[b]->d_bkt_off + kBucketKeys;
-    }
-    const int brc = NB == 1 ? launch_scan(bc[0], bo[0], kBucketKeys, bt[0], s)
-                            : launch_scan_batch(NB, bc, bo, kBucketKeys, bt, s);
-    if (brc != HT_OK) return brc;
-    bscatter_kernel<NB><<<hgrid, 256, 0, s>>>(AB);
+    bscan_kernel<NB><<<dim3(HT_MAX_LAYERS, 1, NB), 256, 0, s>>>(AB);
     HT_CHECK(hipGetLastError());
-    mcand_kernel<NB><<<dim3(blocks_for(peak_cap, 4), 1, NB), 256, 0, s>>>(AB);
+    bscatter_kernel<NB><<<hgrid, 256, 0, s>>>(AB);
     HT_CHECK(hipGetLastError());
   }
   member_kernel<NB><<<sweep, kSweepThreads, 0, s>>>(AB);
   HT_CHECK(hipGetLastError());
   P0.prof_mark(HT_STAGE_MEMBERS, 1, s);
   P0.prof_mark(HT_STAGE_REFINE, 0, s);
+  // one wave per 16 entries of the peak list's capacity (a list is rarely full)
+  const dim3 cgrid(blocks_for(peak_cap, 16 * kRunWaves), 1, NB);
+  if (peak_cap >= kFewCands && !AB.a[0].origin_seed) {
+    reject_kernel<NB><<<cgrid, kRunWaves * kWave, 0, s>>>(AB);
+    HT_CHECK(hipGetLastError());
+  }
+  runs_kernel<NB><<<cgrid, kRunWaves * kWave, 0, s>>>(AB);
+  HT_CHECK(hipGetLastError());
   if (cfg.member_cap <= 128)
     launch_refine<128, NB>(AB, peak_cap, s);
   else if (cfg.member_cap <= 256)
@@ -2832,7 +4037,7 @@ int assoc_sequence(const AssocBatch<NB>& AB, const Plan* const* P, int32_t n_hit
   if (out.track_cap > 0) {
     const int vblocks = blocks_for((int64_t)tcap * cfg.n_rho, 256);
     if (cfg.fit_kind == 1) {
-      kf_kernel<NB><<<dim3(blocks_for(tcap, 64), 1, NB), 64, 0, s>>>(AB);
+      kf_kernel<NB><<<dim3((tcap + 3) / 4, 1, NB), 64, 0, s>>>(AB);
       HT_CHECK(hipGetLastError());
       vvote_kernel<NB><<<dim3(vblocks, 1, NB), 256, 0, s>>>(AB);
     } else {

@@ -14,13 +14,13 @@ namespace ht {
 // five groups of 64 counters, one 128-byte line each (the seed search's totals)
 constexpr int kSpreadWords = 5 * 64 * 16;
 
-// member lists by candidate: the distinct radii of an event's member-eligible
-// hits go into a hash of kClsSlots; with at most kMaxClasses of them the hits
-// are bucketed by (radius class, one of kBuckets azimuth buckets)
-constexpr int kClsSlots = 64;
-constexpr int kMaxClasses = 16;
-constexpr int kBuckets = 1024;
-constexpr int kBucketKeys = kMaxClasses * kBuckets;
+// layer runs: an event's hits grouped by (layer, one of kBuckets azimuth
+// buckets).  Every layer's hits are stored twice in a row, so that a window of
+// azimuth is one contiguous run also where it passes +-pi; a layer's row of the
+// bucket table holds the starts of 2 kBuckets buckets and the end
+constexpr int kBuckets = 2048;
+constexpr int kBucketKeys = HT_MAX_LAYERS * kBuckets;
+constexpr int kRunRow = 2 * kBuckets + 4;  // row stride (entries 0 .. 2 kBuckets are used)
 
 // Hit slices for launches of one workgroup per 64-column tile: grids with
 // fewer than 128 tiles also split the hits, so that about 256 workgroups run,
@@ -62,8 +62,6 @@ struct Plan {
   int32_t* d_tile_off;   // [n_tiles]
   int32_t n_tiles;
   // refinement scratch
-  uint32_t* d_pbits;     // [n_cells / 32 + 1] bitmap of the peaks handed to assoc_cluster
-  int32_t* d_col_first;  // [n_qpt * n_d0] first peak index of each column
   double* d_hx;          // [max_hits] hit x, y, x^2+y^2
   double* d_hy;
   double* d_hq;
@@ -88,13 +86,16 @@ struct Plan {
   int32_t* d_vtile;      // [max_vertex_cells / 1024 + 1] vertex peaks per 1024-cell tile
   int32_t* d_scalars;    // [16] device counters
   unsigned long long* d_spread;  // [kSpreadWords] counters spread over 128-byte lines
-  // member lists by candidate
-  uint32_t* d_cls;      // [kClsSlots] hash of the hits' radii (float bits)
-  int32_t* d_bkt;       // [kBucketKeys] hits per (class, bucket)
-  int32_t* d_bkt_off;   // [kBucketKeys + 1] bucket starts; the bucketed hit count last
-  int32_t* d_hkey;      // [max_hits] bucket key | slot << 14 of each hit, -1 if none
-  int32_t* d_shit;      // [max_hits] hits in bucket order (hit | layer << 16)
-  float* d_sphi;        // [max_hits] their azimuths
+  // layer runs
+  int32_t* d_lay;       // [3 HT_MAX_LAYERS] smallest and largest radius (float bits), hits of each layer
+  int32_t* d_bkt;       // [kBucketKeys] hits per (layer, bucket)
+  int32_t* d_bkt_off;   // [HT_MAX_LAYERS][kRunRow] bucket starts in the records below
+  int32_t* d_hkey;      // [max_hits] bucket key | slot << 15 of each hit, -1 if none
+  float4* d_srec;       // [2 max_hits] by bucket: x, y (float32), azimuth, hit
+  float4* d_srad;       // [2 max_hits] r, 1/r, the window's hit part
+  float* d_sphi;        // [2 max_hits] azimuth
+  double2* d_sxy;       // [2 max_hits] x, y
+  double* d_sq;         // [2 max_hits] x^2+y^2
   // stage timing (ht_profile_*): HIP events recorded around the stages of
   // later calls; plan calls are ordered, so the counters need no locking
   mutable int32_t prof_depth;          // 0: off
