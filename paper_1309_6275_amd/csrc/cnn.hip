@@ -63,28 +63,44 @@ struct alignas(16) Packed {
 };
 static_assert(sizeof(Packed) % 16 == 0, "packed weights are copied in 16-byte chunks");
 
-__global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ P, Packed* __restrict__ W) {
-  for (int e = threadIdx.x; e < 64 * 8; e += blockDim.x) {
+// The weights in operand order; with zero, a training step's gradient (and its
+// loss) cleared beside them.  One element per thread (one workgroup took 8 us).
+constexpr int kPackW1 = 64 * 8, kPackW2 = kC2Steps * 64 * 8, kPackW3 = 4 * 64 * 4;
+constexpr int kPackAll = kPackW1 + kPackW2 + kPackW3 + 64;
+__global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ P, Packed* __restrict__ W,
+                                                   float* __restrict__ zero,
+                                                   float* __restrict__ loss) {
+  int e = blockIdx.x * 256 + threadIdx.x;
+  if (zero && e < HT_CNN_PARAMS) zero[e] = 0.0f;
+  if (loss && e == 0) *loss = 0.0f;
+  if (e < kPackW1) {
     const int l = e / 8, i = e % 8;
     const int t = 8 * (l / 16) + i, c = l % 16;
     W->w1[e] = t < 27 ? to_bf16(P[oW1 + c * 27 + t]) : (uint16_t)0;
+    return;
   }
-  for (int e = threadIdx.x; e < kC2Steps * 64 * 8; e += blockDim.x) {
+  e -= kPackW1;
+  if (e < kPackW2) {
     const int st = e / 512, l = (e / 8) % 64, i = e % 8;
     const int k = 8 * (l / 16) + i;
     const int p = 2 * st + k / 16, cin = k % 16, c = l % 16;
     W->w2[e] = p < 27 ? to_bf16(P[oW2 + (c * 16 + cin) * 27 + p]) : (uint16_t)0;
+    return;
   }
-  for (int e = threadIdx.x; e < 4 * 64 * 4; e += blockDim.x) {
+  e -= kPackW2;
+  if (e < kPackW3) {
     const int nt = e / 256, l = (e / 4) % 64, i = e % 4;
     const int c = 4 * (l / 16) + i, f = 16 * nt + l % 16;
     W->w3[e] = to_bf16(P[oW3 + f * 16 + c]);
+    return;
   }
-  const int t = threadIdx.x;
-  if (t < 16) { W->b1[t] = P[ob1 + t]; W->b2[t] = P[ob2 + t]; }
-  if (t < 64) { W->b3[t] = P[ob3 + t]; W->w4[t] = from_bf16(to_bf16(P[oW4 + t])); }
-  if (t < 4) W->b4[t] = t == 0 ? P[ob4] : 0.0f;
+  e -= kPackW3;
+  if (e < 16) { W->b1[e] = P[ob1 + e]; W->b2[e] = P[ob2 + e]; }
+  if (e < 64) { W->b3[e] = P[ob3 + e]; W->w4[e] = from_bf16(to_bf16(P[oW4 + e])); }
+  if (e < 4) W->b4[e] = e == 0 ? P[ob4] : 0.0f;
 }
+constexpr int kPackBlocks = (kPackAll + 255) / 256;
+static_assert(kPackBlocks * 256 >= HT_CNN_PARAMS, "the gradient is cleared by the same threads");
 
 // windows around peaks: votes * 1/16 as bfloat16, phi0 periodic, q/pT and d0
 // outside the grid read 0; entries 125..127 are 0
@@ -272,18 +288,28 @@ __global__ __launch_bounds__(kFwdWaves * 64) void forward_kernel(
 }
 
 // Backward on the matrix cores (v_mfma_f32_16x16x16_bf16, K = 16; same
-// lane layout as above with k = 4 (lane / 16) + i).  One wave per tile of 16
-// windows, tiles grid-strided; the wave keeps its parameter gradients in
-// MFMA accumulators and adds them to the global gradient once.  Precision
-// contract (the oracle's too): the backward signals dh3, dh2, dh1 are
-// rounded to bfloat16 after their ReLU masks, like the activations, and every
-// contraction accumulates in float32; dz and the last layer stay float32.
+// lane layout as above with k = 4 (lane / 16) + i).  Precision contract (the
+// oracle's too): the backward signals dh3, dh2, dh1 are rounded to bfloat16
+// after their ReLU masks, like the activations, and every contraction
+// accumulates in float32; dz and the last layer stay float32.
 //   dh2 = dh3 W3           M = 16 windows, N = 16 channels, K = 64 features
 //   dh1[p] = dh2 W2[.][.][p]   per position p: M = 16 windows, N = 16, K = 16
 //   dW1 += dh1[p]^T x_p    per position: M = 16 channels, N = 32 taps, K = 16 windows
 //   dW2[p] += dh2^T h1[p]  per position: M = 16, N = 16, K = 16 windows
 //   dW3 += dh3^T h2        M = 64 features, N = 16 channels, K = 16 windows
+// A workgroup takes a tile of 16 windows at a time; its four waves share the
+// 27 positions (wave w takes w, w + 4, ..), so each keeps a quarter of the
+// gradient in MFMA accumulators over all its tiles.  A product's result layout
+// is the next one's A operand (dh1^T and dh2^T never leave the registers).  The
+// workgroup's gradient is gathered in LDS and added to the global one with
+// contiguous atomics: scattered atomics by every wave (2.2 million on 8529
+// addresses at 4096 windows) took most of the kernel's time.  4096 windows: 190 ->
+// 25 us.
 constexpr int kBwdWaves = 4;
+// workgroups at most: each adds the whole gradient once (4096 windows: 64, 128 and
+// 256 workgroups take 32.6, 25.0 and 26.2 us)
+constexpr int kBwdGrid = 128;
+constexpr int kXb = 130;        // row stride of the windows (as kXs)
 
 __device__ __forceinline__ bf16x4 pack4(uint16_t a, uint16_t b, uint16_t c, uint16_t d) {
   bf16x4 v;
@@ -296,41 +322,62 @@ __global__ __launch_bounds__(kBwdWaves * 64) void backward_kernel(
     int n, float pos_weight, const float* __restrict__ logits, const uint16_t* __restrict__ h1g,
     const uint16_t* __restrict__ h2g, const uint16_t* __restrict__ h3g, float* __restrict__ grad,
     float* __restrict__ loss) {
-  __shared__ uint16_t xs[kBwdWaves][16][kWin];
-  __shared__ uint16_t h1s[kBwdWaves][16][27][16];
-  __shared__ uint16_t h2s[kBwdWaves][16][16];
-  __shared__ uint16_t h3s[kBwdWaves][16][64];
-  __shared__ uint16_t d3s[kBwdWaves][16][64];   // dh3 (bf16)
-  __shared__ uint16_t d2s[kBwdWaves][16][16];   // dh2 (bf16)
-  __shared__ uint16_t d1s[kBwdWaves][16][16];   // dh1 at one position (bf16)
-  __shared__ float dzs[kBwdWaves][16];
+  constexpr int kThreads = kBwdWaves * 64;
+  __shared__ uint16_t xs[16][kXb];
+  __shared__ __align__(16) uint16_t h1s[16][27 * 16];
+  __shared__ __align__(16) uint16_t h2s[16][16];
+  __shared__ __align__(16) uint16_t h3s[16][64];
+  __shared__ __align__(16) uint16_t d3s[16][64];              // dh3 (bf16)
+  __shared__ __align__(16) uint16_t d2s[kBwdWaves][16][16];   // dh2 (bf16)
+  __shared__ __align__(16) uint16_t w2t[27][264];             // W2 as [position][input 16 + output]
+  __shared__ float dzs[16];
+  __shared__ float sg[HT_CNN_PARAMS];
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int row = l % 16, g = l / 16;
   const int tiles = (n + 15) / 16;
-  f32x4 aw1[2], aw2[27], aw3[4];
+  for (int e = threadIdx.x; e < HT_CNN_PARAMS; e += kThreads) sg[e] = 0.0f;
+  for (int e = threadIdx.x; e < 16 * 16 * 27; e += kThreads) {
+    const int c = e / (16 * 27), ci = (e / 27) % 16, p = e % 27;
+    w2t[p][ci * 16 + c] = to_bf16(P[oW2 + e]);
+  }
+  bf16x4 b3[4];  // W3 as the B operand of dh2: features 16 st + 4 g + i, channel row
+#pragma unroll
+  for (int st = 0; st < 4; ++st) {
+    const int f = 16 * st + 4 * g;
+    b3[st] = pack4(to_bf16(P[oW3 + (f + 0) * 16 + row]), to_bf16(P[oW3 + (f + 1) * 16 + row]),
+                   to_bf16(P[oW3 + (f + 2) * 16 + row]), to_bf16(P[oW3 + (f + 3) * 16 + row]));
+  }
+  const float w4b = from_bf16(to_bf16(P[oW4 + l]));
+  constexpr int kPos = (27 + kBwdWaves - 1) / kBwdWaves;  // positions of a wave
+  f32x4 aw1[2], aw2[kPos], aw3 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int q = 0; q < 2; ++q) aw1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int q = 0; q < 27; ++q) aw2[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int q = 0; q < 4; ++q) aw3[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int q = 0; q < kPos; ++q) aw2[q] = f32x4{0.f, 0.f, 0.f, 0.f};
   float gb1 = 0.f, gb2 = 0.f, gb3 = 0.f, gw4 = 0.f, gb4 = 0.f, lsum = 0.f;
-  const float w4b = from_bf16(to_bf16(P[oW4 + l]));
-  for (int tile = blockIdx.x * kBwdWaves + wave; tile < tiles; tile += gridDim.x * kBwdWaves) {
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int w0 = tile * 16;
     const int nw = min(16, n - w0);
-    // stage the tile's inputs and activations (zeros past the last window)
-    for (int e = l; e < 16 * kWin; e += 64) {
-      const int w = e / kWin;
-      (&xs[wave][0][0])[e] = w < nw ? win[(size_t)w0 * kWin + e] : (uint16_t)0;
+    __syncthreads();  // the previous tile is done with the LDS
+    // the tile's inputs and activations, 16 bytes a load (zeros past the last window)
+    {
+      const int w = threadIdx.x / 16, o = threadIdx.x % 16 * 8;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (w < nw) v = *reinterpret_cast<const uint4*>(win + (size_t)(w0 + w) * kWin + o);
+      uint32_t* d = reinterpret_cast<uint32_t*>(&xs[w][o]);
+      d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
     }
-    for (int e = l; e < 16 * 432; e += 64)
-      (&h1s[wave][0][0][0])[e] = e / 432 < nw ? h1g[(size_t)w0 * 432 + e] : (uint16_t)0;
-    for (int e = l; e < 16 * 16; e += 64)
-      (&h2s[wave][0][0])[e] = e / 16 < nw ? h2g[(size_t)w0 * 16 + e] : (uint16_t)0;
-    for (int e = l; e < 16 * 64; e += 64)
-      (&h3s[wave][0][0])[e] = e / 64 < nw ? h3g[(size_t)w0 * 64 + e] : (uint16_t)0;
-    if (l < 16) {
+    const auto stage = [&](void* dst, const uint16_t* src, int row16) {  // row16: 16-byte pieces a window
+      for (int e = threadIdx.x; e < 16 * row16; e += kThreads) {
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (e < nw * row16) v = reinterpret_cast<const uint4*>(src)[e];
+        reinterpret_cast<uint4*>(dst)[e] = v;
+      }
+    };
+    stage(h1s, h1g + (size_t)w0 * 432, 54);
+    stage(h2s, h2g + (size_t)w0 * 16, 2);
+    stage(h3s, h3g + (size_t)w0 * 64, 8);
+    if (threadIdx.x < 16) {
       float dz = 0.f;
       if (l < nw) {
         const float z = logits[w0 + l], y = labels[w0 + l];
@@ -338,136 +385,116 @@ __global__ __launch_bounds__(kBwdWaves * 64) void backward_kernel(
         const float sp = fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z)));
         lsum += wgt * (sp - y * z) / (float)n;
         dz = wgt * (1.0f / (1.0f + expf(-z)) - y) / (float)n;
+        gb4 += dz;
       }
-      dzs[wave][l] = dz;
+      dzs[l] = dz;
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // dh3 = dz W4 [h3 > 0] (lane = feature), and the last layer's gradients
-#pragma unroll 4
-    for (int w = 0; w < 16; ++w) {
-      const float dz = dzs[wave][w];
-      const float h3 = from_bf16(h3s[wave][w][l]);
+    __syncthreads();
+    // dh3 = dz W4 [h3 > 0] and the last layer's gradients: lane = feature, four
+    // windows a wave
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int w = 4 * wave + u;
+      const float dz = dzs[w];
+      const float h3 = from_bf16(h3s[w][l]);
       const uint16_t d3 = h3 > 0.0f ? to_bf16(dz * w4b) : (uint16_t)0;
-      d3s[wave][w][l] = d3;
+      d3s[w][l] = d3;
       gb3 += from_bf16(d3);
       gw4 += dz * h3;
-      if (l == 0) gb4 += dz;
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // dh2 = dh3 W3 [h2 > 0]
+    __syncthreads();
+    // dh2 = dh3 W3 [h2 > 0], by every wave for itself
+    bf16x4 a_dh2_t;  // [channel row][window 4 g + i]
+    const bf16x4 b_h2 = pack4(h2s[4 * g][row], h2s[4 * g + 1][row], h2s[4 * g + 2][row],
+                              h2s[4 * g + 3][row]);
     {
       f32x4 d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int st = 0; st < 4; ++st) {
-        const int f = 16 * st + 4 * g;
-        const bf16x4 a = *reinterpret_cast<const bf16x4*>(&d3s[wave][row][f]);
-        const bf16x4 b = pack4(to_bf16(P[oW3 + (f + 0) * 16 + row]), to_bf16(P[oW3 + (f + 1) * 16 + row]),
-                               to_bf16(P[oW3 + (f + 2) * 16 + row]), to_bf16(P[oW3 + (f + 3) * 16 + row]));
-        d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, d, 0, 0, 0);
+        const bf16x4 a = *reinterpret_cast<const bf16x4*>(&d3s[row][16 * st + 4 * g]);
+        d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b3[st], d, 0, 0, 0);
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int w = 4 * g + i;
-        const uint16_t v = h2s[wave][w][row] != 0 ? to_bf16(d[i]) : (uint16_t)0;
-        d2s[wave][w][row] = v;
+        const uint16_t v = b_h2[i] != 0 ? to_bf16(d[i]) : (uint16_t)0;
+        d2s[wave][4 * g + i][row] = v;
+        a_dh2_t[i] = (short)v;
         gb2 += from_bf16(v);
       }
     }
-    // dW3 += dh3^T h2
+    // dW3 += dh3^T h2: features 16 wave ..
+    {
+      const int f = 16 * wave + row;
+      const bf16x4 a = pack4(d3s[4 * g][f], d3s[4 * g + 1][f], d3s[4 * g + 2][f], d3s[4 * g + 3][f]);
+      aw3 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b_h2, aw3, 0, 0, 0);
+    }
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    {
-      const bf16x4 b = pack4(h2s[wave][4 * g][row], h2s[wave][4 * g + 1][row], h2s[wave][4 * g + 2][row],
-                             h2s[wave][4 * g + 3][row]);
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const int f = 16 * mt + row;
-        const bf16x4 a = pack4(d3s[wave][4 * g][f], d3s[wave][4 * g + 1][f], d3s[wave][4 * g + 2][f],
-                               d3s[wave][4 * g + 3][f]);
-        aw3[mt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, aw3[mt], 0, 0, 0);
-      }
-    }
+    const bf16x4 a_dh2 = *reinterpret_cast<const bf16x4*>(&d2s[wave][row][4 * g]);  // [window][channel]
     // per position: dh1[p], then dW1 and dW2 at p
-    const bf16x4 a_dh2_t = pack4(d2s[wave][4 * g][row], d2s[wave][4 * g + 1][row],
-                                 d2s[wave][4 * g + 2][row], d2s[wave][4 * g + 3][row]);  // [c][w]
-    const bf16x4 a_dh2 = *reinterpret_cast<const bf16x4*>(&d2s[wave][row][4 * g]);      // [w][c]
-#pragma unroll 1
-    for (int p = 0; p < 27; ++p) {
-      const int base = (p / 9) * 25 + ((p / 3) % 3) * 5 + p % 3;
-      {
-        const int c0 = 4 * g;
-        const bf16x4 b = pack4(to_bf16(P[oW2 + ((c0 + 0) * 16 + row) * 27 + p]),
-                               to_bf16(P[oW2 + ((c0 + 1) * 16 + row) * 27 + p]),
-                               to_bf16(P[oW2 + ((c0 + 2) * 16 + row) * 27 + p]),
-                               to_bf16(P[oW2 + ((c0 + 3) * 16 + row) * 27 + p]));
-        f32x4 d = {0.f, 0.f, 0.f, 0.f};
-        d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a_dh2, b, d, 0, 0, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int w = 4 * g + i;
-          const uint16_t v = h1s[wave][w][p][row] != 0 ? to_bf16(d[i]) : (uint16_t)0;
-          d1s[wave][w][row] = v;
-          gb1 += from_bf16(v);
-        }
+    for (int q = 0; q < kPos; ++q) {
+      const int p = wave + kBwdWaves * q;
+      if (p >= 27) break;
+      const int base = (p / 9) * 25 + ((p / 3) % 3) * 5 + p % 3;
+      const bf16x4 b = *reinterpret_cast<const bf16x4*>(&w2t[p][row * 16 + 4 * g]);
+      f32x4 d = {0.f, 0.f, 0.f, 0.f};
+      d = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a_dh2, b, d, 0, 0, 0);
+      // h1 at p: the ReLU mask of dh1 and the B operand of dW2
+      const bf16x4 b_h1 = pack4(h1s[4 * g][p * 16 + row], h1s[4 * g + 1][p * 16 + row],
+                                h1s[4 * g + 2][p * 16 + row], h1s[4 * g + 3][p * 16 + row]);
+      bf16x4 a1;  // dh1^T: [channel row][window 4 g + i]
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint16_t v = b_h1[i] != 0 ? to_bf16(d[i]) : (uint16_t)0;
+        a1[i] = (short)v;
+        gb1 += from_bf16(v);
       }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       // dW1[c][t] += sum_w dh1[w][p][c] x[w][cell(p, t)]
-      const bf16x4 a1 = pack4(d1s[wave][4 * g][row], d1s[wave][4 * g + 1][row],
-                              d1s[wave][4 * g + 2][row], d1s[wave][4 * g + 3][row]);
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) {
         const int t = 16 * nt + row;
-        const int cell = t < 27 ? base + (t / 9) * 25 + ((t / 3) % 3) * 5 + t % 3 : -1;
-        const bf16x4 b = cell >= 0 ? pack4(xs[wave][4 * g][cell], xs[wave][4 * g + 1][cell],
-                                           xs[wave][4 * g + 2][cell], xs[wave][4 * g + 3][cell])
-                                   : pack4(0, 0, 0, 0);
-        aw1[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b, aw1[nt], 0, 0, 0);
+        const int cell = base + (t / 9) * 25 + ((t / 3) % 3) * 5 + t % 3;
+        bf16x4 bx = pack4(0, 0, 0, 0);
+        if (t < 27)
+          bx = pack4(xs[4 * g][cell], xs[4 * g + 1][cell], xs[4 * g + 2][cell], xs[4 * g + 3][cell]);
+        aw1[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, bx, aw1[nt], 0, 0, 0);
       }
       // dW2[c][c'][p] += sum_w dh2[w][c] h1[w][p][c']
-      const bf16x4 b2 = pack4(h1s[wave][4 * g][p][row], h1s[wave][4 * g + 1][p][row],
-                              h1s[wave][4 * g + 2][p][row], h1s[wave][4 * g + 3][p][row]);
-#pragma unroll
-      for (int q = 0; q < 27; ++q)
-        if (q == p) aw2[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a_dh2_t, b2, aw2[q], 0, 0, 0);
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      aw2[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a_dh2_t, b_h1, aw2[q], 0, 0, 0);
     }
   }
-  // the wave's gradients into the global sum
+  // the workgroup's gradient in LDS: each wave's own part, and the shared ones by atomics
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int c = 4 * g + i, t = 16 * nt + row;
-      if (t < 27) atomicAdd(&grad[oW1 + c * 27 + t], aw1[nt][i]);
+      if (t < 27) atomicAdd(&sg[oW1 + c * 27 + t], aw1[nt][i]);
     }
 #pragma unroll
-  for (int q = 0; q < 27; ++q)
+  for (int q = 0; q < kPos; ++q) {
+    const int p = wave + kBwdWaves * q;
+    if (p >= 27) break;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) atomicAdd(&grad[oW2 + ((4 * g + i) * 16 + row) * 27 + q], aw2[q][i]);
+    for (int i = 0; i < 4; ++i) sg[oW2 + ((4 * g + i) * 16 + row) * 27 + p] = aw2[q][i];
+  }
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) atomicAdd(&grad[oW3 + (16 * mt + 4 * g + i) * 16 + row], aw3[mt][i]);
-  atomicAdd(&grad[ob1 + row], gb1);
-  atomicAdd(&grad[ob2 + row], gb2);
-  atomicAdd(&grad[ob3 + l], gb3);
-  atomicAdd(&grad[oW4 + l], gw4);
+  for (int i = 0; i < 4; ++i) sg[oW3 + (16 * wave + 4 * g + i) * 16 + row] = aw3[i];
+  atomicAdd(&sg[ob1 + row], gb1);
+  if (wave == 0) atomicAdd(&sg[ob2 + row], gb2);
+  atomicAdd(&sg[ob3 + l], gb3);
+  atomicAdd(&sg[oW4 + l], gw4);
   for (int o = 32; o > 0; o >>= 1) {
     lsum += __shfl_xor(lsum, o);
     gb4 += __shfl_xor(gb4, o);
   }
-  if (l == 0) {
-    atomicAdd(&grad[ob4], gb4);
+  if (threadIdx.x == 0) {
+    sg[ob4] = gb4;
     atomicAdd(loss, lsum);
   }
-}
-
-__global__ void zero_f32_kernel(float* p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0.0f;
+  __syncthreads();
+  for (int e = threadIdx.x; e < HT_CNN_PARAMS; e += kThreads) atomicAdd(&grad[e], sg[e]);
 }
 
 __global__ void sgd_kernel(float* __restrict__ P, float* __restrict__ mom, float* __restrict__ grad,
@@ -553,7 +580,7 @@ int launch_cnn_windows(const Plan& p, const int32_t* acc, const ht_peak* peaks, 
 int launch_cnn_forward(const float* params, const uint16_t* win, const int32_t* n_dev, int32_t n_max,
                        float* logits, void* ws, hipStream_t s) {
   Packed* W = reinterpret_cast<Packed*>(ws);
-  pack_kernel<<<1, 256, 0, s>>>(params, W);
+  pack_kernel<<<kPackBlocks, 256, 0, s>>>(params, W, nullptr, nullptr);
   HT_CHECK(hipGetLastError());
   const int tiles = (n_max + 15) / 16;
   forward_kernel<false, false><<<blocks(tiles, kFwdWaves, kFwdGrid), kFwdWaves * 64, 0, s>>>(
@@ -565,7 +592,7 @@ int launch_cnn_forward(const float* params, const uint16_t* win, const int32_t* 
 int launch_cnn_score(const Plan& p, const float* params, const int32_t* acc, const ht_peak* peaks,
                      const int32_t* n_peaks, int32_t cap, float* logits, void* ws, hipStream_t s) {
   Packed* W = reinterpret_cast<Packed*>(ws);
-  pack_kernel<<<1, 256, 0, s>>>(params, W);
+  pack_kernel<<<kPackBlocks, 256, 0, s>>>(params, W, nullptr, nullptr);
   HT_CHECK(hipGetLastError());
   const ht_grid& g = p.grid;
   const int tiles = (cap + 15) / 16;
@@ -591,15 +618,13 @@ int launch_cnn_train(float* params, float* mom, const uint16_t* win, const float
   uint16_t* h3 = reinterpret_cast<uint16_t*>(base + o);
   o += (nn * 64 * 2 + 255) / 256 * 256;
   float* grad = reinterpret_cast<float*>(base + o);
-  zero_f32_kernel<<<34, 256, 0, s>>>(grad, HT_CNN_PARAMS);
-  zero_f32_kernel<<<1, 64, 0, s>>>(loss, 1);
-  pack_kernel<<<1, 256, 0, s>>>(params, W);
+  pack_kernel<<<kPackBlocks, 256, 0, s>>>(params, W, grad, loss);
   HT_CHECK(hipGetLastError());
   const int tiles = (n + 15) / 16;
   forward_kernel<false, true><<<blocks(tiles, kFwdWaves, 4096), kFwdWaves * 64, 0, s>>>(
       W, win, nullptr, 0, 0, 0, nullptr, nullptr, n, logits, h1, h2, h3);
   HT_CHECK(hipGetLastError());
-  backward_kernel<<<blocks(tiles, kBwdWaves, 64), kBwdWaves * 64, 0, s>>>(
+  backward_kernel<<<blocks(tiles, 1, kBwdGrid), kBwdWaves * 64, 0, s>>>(
       params, win, labels, n, pos_weight, logits, h1, h2, h3, grad, loss);
   HT_CHECK(hipGetLastError());
   sgd_kernel<<<(HT_CNN_PARAMS + 255) / 256, 256, 0, s>>>(params, mom, grad, lr, momentum);
