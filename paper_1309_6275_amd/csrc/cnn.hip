@@ -10,20 +10,17 @@
 // (A: 16 x 32 bf16 with row m = lane % 16 and k = 8 (lane / 16) + i in
 // element i; B likewise with column n = lane % 16; D: row 4 (lane / 16) + i,
 // column lane % 16; checked on the device against a host product).  One
-// wave scores 16 windows:
-//   conv1  one k-step per output position (27 taps padded to 32): M = the 16
-//          windows, N = 16 channels; the A operand gathers the window's
-//          cells at per-lane tap offsets;
-//   conv2  14 k-steps of two positions x 16 input channels each, each step
-//          right after the conv1 of its two positions (their activations
-//          pass through a 1 KB LDS buffer, not a 27-position one);
-//   fc1    4 n-tiles of 16 features with the K = 16 instruction; fc2 a dot
+// wave scores 16 windows, the columns of every product:
+//   conv1  one k-step per output position (27 taps padded to 32): M = 16
+//          channels, the B operand built from the window's rows;
+//   conv2  14 k-steps of two positions x 16 input channels each, right after
+//          the conv1 of its two positions and from their registers;
+//   fc1    4 m-tiles of 16 features with the K = 16 instruction; fc2 a dot
 //          product on the VALU.
-// The packed weights (B-operand order) are copied into LDS once per
-// workgroup.  ht_cnn_score builds each wave's 16 windows in LDS straight
-// from the accumulator (no window buffer in HBM).  Training (offline) runs
-// the same forward, keeps the activations, and computes the gradients with
-// the matrix cores as well (see backward_kernel).
+// ht_cnn_score builds each wave's 16 windows in LDS straight from the
+// accumulator (no window buffer in HBM).  Training (offline) runs the same
+// forward, keeps the activations, and computes the gradients with the matrix
+// cores as well (see backward_kernel).
 #include "ht_internal.h"
 
 namespace ht {
@@ -31,6 +28,9 @@ namespace {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
@@ -56,12 +56,22 @@ static_assert(ob4 + 1 == HT_CNN_PARAMS, "parameter layout");
 constexpr int kC2Steps = 14;  // conv2 k-steps: two positions x 16 channels (position 27 zero)
 
 struct alignas(16) Packed {
-  uint16_t w1[64 * 8];             // conv1 B operand per lane (K = 32: taps, padded)
-  uint16_t w2[kC2Steps * 64 * 8];  // conv2 B operand per k-step and lane (K = 32)
-  uint16_t w3[4 * 64 * 4];         // fc1 B operand per n-tile and lane (K = 16)
+  uint16_t w1[64 * 8];             // conv1 operand per lane (K = 32: taps, padded)
+  uint16_t w2[kC2Steps * 64 * 8];  // conv2 operand per k-step and lane (K = 32)
+  uint16_t w3[4 * 64 * 4];         // fc1 operand per feature tile and lane (K = 16)
   float b1[16], b2[16], b3[64], w4[64], b4[4];
 };
 static_assert(sizeof(Packed) % 16 == 0, "packed weights are copied in 16-byte chunks");
+
+// conv1's order within a lane's eight taps (lane group g holds taps 8 g .. 8 g +
+// 7; -1: zero weight): two rows of three cells and two single cells, so that
+// the window's rows are read whole (see forward_kernel)
+__device__ constexpr int8_t kTap[4][8] = {{0, 1, 3, 4, 2, 5, 6, 7},
+                                          {9, 10, 12, 13, 11, 14, 8, 15},
+                                          {18, 19, 21, 22, 20, 23, 16, 17},
+                                          {24, 25, -1, -1, 26, -1, -1, -1}};
+// conv1's result row 4 g + i is channel chan_of(g) + i
+__device__ __forceinline__ int chan_of(int g) { return 8 * (g & 1) + 4 * (g >> 1); }
 
 // The weights in operand order; with zero, a training step's gradient (and its
 // loss) cleared beside them.  One element per thread (one workgroup took 8 us).
@@ -75,8 +85,8 @@ __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ P, 
   if (loss && e == 0) *loss = 0.0f;
   if (e < kPackW1) {
     const int l = e / 8, i = e % 8;
-    const int t = 8 * (l / 16) + i, c = l % 16;
-    W->w1[e] = t < 27 ? to_bf16(P[oW1 + c * 27 + t]) : (uint16_t)0;
+    const int t = kTap[l / 16][i], c = chan_of(l % 16 / 4) + l % 4;
+    W->w1[e] = t >= 0 ? to_bf16(P[oW1 + c * 27 + t]) : (uint16_t)0;
     return;
   }
   e -= kPackW1;
@@ -129,159 +139,237 @@ __global__ __launch_bounds__(256) void windows_kernel(const int32_t* __restrict_
 }
 
 constexpr int kFwdWaves = 4;
-// LDS row stride of a window (bf16): 130 = 65 dwords, odd, so the 16 rows a
-// conv1 gather reads at one column fall in different banks
-constexpr int kXs = 130;
+// A window in LDS: its 25 rows (dk, dj) of 5 cells, 8 cells (16 bytes) apart.
+// 16 windows are 100 dwords apart: the 16-byte reads of a row of all of them
+// meet no bank conflict.  One row more is read (with zero weights) after the last.
+constexpr int kRowsLds = 16 * 25 + 1;
 
-// One window into LDS: votes * 1/16 as bfloat16 around a peak cell, phi0
-// periodic, q/pT and d0 outside the grid 0, entries 125..127 0.  The wave
-// fills 16 windows, a lane per (window, dk, dj) row of 5 cells at a time.
+__device__ __forceinline__ uint32_t pk_bf16(float a, float b) {  // round to nearest even
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+typedef int32_t Cells4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// 16 windows into LDS: votes * 1/16 as bfloat16 around a peak cell, phi0
+// periodic, q/pT and d0 outside the grid 0.  A lane stays with one window (its
+// cell is decoded once) and takes every fourth row; a row away from the phi0 seam
+// is one 16-byte and one 4-byte load.
 __device__ __forceinline__ void build_windows(const int32_t* __restrict__ acc, int n_phi, int n_qpt,
                                               int n_d0, const ht_peak* __restrict__ peaks, int w0,
-                                              int n, int l, uint16_t (*xs)[kXs]) {
+                                              int n, int l, uint16_t (*xs)[8]) {
   const int64_t n_cells = (int64_t)n_phi * n_qpt * n_d0;
-  for (int e = l; e < 16 * 25; e += 64) {
-    const int w = e / 25, r = e % 25;
-    const int dk = r / 5 - 2, dj = r % 5 - 2;
-    uint16_t v[5] = {0, 0, 0, 0, 0};
-    const int lin = w0 + w < n ? peaks[w0 + w].lin : -1;
-    if (lin >= 0 && lin < n_cells) {
-      const int i = lin % n_phi, col = lin / n_phi, j = col % n_qpt, k = col / n_qpt;
-      const int kk = k + dk, jj = j + dj;
-      if (kk >= 0 && kk < n_d0 && jj >= 0 && jj < n_qpt) {
-        const int32_t* row = acc + ((size_t)kk * n_qpt + jj) * n_phi;
+  const int w = l % 16;
+  const int lin = w0 + w < n ? peaks[w0 + w].lin : -1;
+  const bool ok = lin >= 0 && lin < n_cells;
+  const int i = ok ? lin % n_phi : 0, col = ok ? lin / n_phi : 0;
+  const int j = col % n_qpt, k = col / n_qpt;
+  Cells4 q[7];
+  int32_t c4[7];
+  const int32_t* base = acc + ((int64_t)(k - 2) * n_qpt + (j - 2)) * n_phi + (i - 2);
+  const auto inside = [&](int r) {
+    const int kk = k + r / 5 - 2, jj = j + r % 5 - 2;
+    return ok && r < 25 && kk >= 0 && kk < n_d0 && jj >= 0 && jj < n_qpt;
+  };
+  if (__all(!ok || (i >= 2 && i + 2 < n_phi))) {
 #pragma unroll
-        for (int d = 0; d < 5; ++d) {
-          int ii = i + d - 2;
-          ii = ii < 0 ? ii + n_phi : (ii >= n_phi ? ii - n_phi : ii);
-          v[d] = to_bf16((float)row[ii] * 0.0625f);
-        }
+    for (int u = 0; u < 7; ++u) {
+      const int r = l / 16 + 4 * u;
+      q[u] = Cells4{0, 0, 0, 0};
+      c4[u] = 0;
+      if (inside(r)) {
+        const int32_t* at = base + (r / 5 * n_qpt + r % 5) * (int64_t)n_phi;
+        q[u] = *reinterpret_cast<const Cells4*>(at);
+        c4[u] = at[4];
       }
     }
+  } else {
+    int at[5];
 #pragma unroll
-    for (int d = 0; d < 5; ++d) xs[w][r * 5 + d] = v[d];
+    for (int d = 0; d < 5; ++d) {
+      const int ii = i + d - 2;
+      at[d] = ii < 0 ? d + n_phi : (ii >= n_phi ? d - n_phi : d);
+    }
+#pragma unroll
+    for (int u = 0; u < 7; ++u) {
+      const int r = l / 16 + 4 * u;
+      q[u] = Cells4{0, 0, 0, 0};
+      c4[u] = 0;
+      if (inside(r)) {
+        const int32_t* row = base + (r / 5 * n_qpt + r % 5) * (int64_t)n_phi;
+        q[u] = Cells4{row[at[0]], row[at[1]], row[at[2]], row[at[3]]};
+        c4[u] = row[at[4]];
+      }
+    }
   }
-  if (l < 16 * 3) xs[l / 3][125 + l % 3] = 0;
+#pragma unroll
+  for (int u = 0; u < 7; ++u) {
+    const int r = l / 16 + 4 * u;
+    uint4 o;
+    o.x = pk_bf16((float)q[u].x * 0.0625f, (float)q[u].y * 0.0625f);
+    o.y = pk_bf16((float)q[u].z * 0.0625f, (float)q[u].w * 0.0625f);
+    o.z = pk_bf16((float)c4[u] * 0.0625f, 0.0f);
+    o.w = 0;
+    if (r < 25) *reinterpret_cast<uint4*>(xs[w * 25 + r]) = o;
+  }
 }
 
 // Forward of 16 windows per wave.  FUSED: the windows come from the
 // accumulator and peak list (ht_cnn_score), else from a window buffer.
 // ACT keeps the activations for training.
+//
+// Every product has the weights as the first operand and the windows as the
+// second (N = 16 windows), so a lane's results are four channels of its own
+// window, which are the next layer's operand: conv1's two positions of a step
+// become conv2's K = 32 by one exchange between the wave's halves, and conv2's
+// result is fc1's K = 16 as it stands.  Only the windows pass through LDS.
+// The matrix cores add a lane's eight products exactly, so the order of the taps
+// within a lane group is free (the groups' order is not): group g's taps 8 g ..
+// are two whole rows of three cells and two single cells.  A row is read once
+// for its three phi0 offsets and as the first and the second row: 12 row reads
+// and 54 reads of one cell per tile, where every tap of every position was read
+// by itself (216) and conv1 went through LDS.  480 thousand windows: 195 -> 69 us
+// (before: 2175 vector instructions and 1800 LDS cycles a tile).
 template <bool FUSED, bool ACT>
-__global__ __launch_bounds__(kFwdWaves * 64) void forward_kernel(
-    const Packed* __restrict__ Wg, const uint16_t* __restrict__ win,
+__global__ __launch_bounds__(kFwdWaves * 64, 4) void forward_kernel(
+    const Packed* __restrict__ W, const uint16_t* __restrict__ win,
     const int32_t* __restrict__ acc, int n_phi, int n_qpt, int n_d0,
     const ht_peak* __restrict__ peaks, const int32_t* __restrict__ n_dev, int n_max,
     float* __restrict__ logits, uint16_t* __restrict__ h1o, uint16_t* __restrict__ h2o,
     uint16_t* __restrict__ h3o) {
-  __shared__ Packed W;
-  __shared__ uint16_t xs[kFwdWaves][16][kXs];
-  __shared__ uint16_t hb[kFwdWaves][2][2][16][16];  // [step parity][position of the pair][window][channel]
-  __shared__ uint16_t h2s[kFwdWaves][16][16];
-  {
-    const uint4* src = reinterpret_cast<const uint4*>(Wg);
-    uint4* dst = reinterpret_cast<uint4*>(&W);
-    for (int e = threadIdx.x; e < (int)(sizeof(Packed) / 16); e += blockDim.x) dst[e] = src[e];
-  }
-  __syncthreads();
+  __shared__ __align__(16) uint16_t xl[kFwdWaves][kRowsLds][8];
+  __shared__ uint4 w2[kC2Steps * 64];
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int n = n_dev ? min(max(*n_dev, 0), n_max) : n_max;
   const int tiles = (n + 15) / 16;
   const int row = l % 16, g = l / 16;
-  // this lane's conv1 taps: t = 8 g + i, cell offset (dk, dj, di) in the window
-  int off[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int t = 8 * g + i;
-    off[i] = t < 27 ? (t / 9) * 25 + ((t / 3) % 3) * 5 + t % 3 : -1;
-  }
-  const bf16x8 b1v = as_bf16x8(*reinterpret_cast<const uint4*>(&W.w1[l * 8]));
-  const int c = l % 16;
-  for (int tile = blockIdx.x * kFwdWaves + wave; tile < tiles; tile += gridDim.x * kFwdWaves) {
+  uint16_t (*xs)[8] = xl[wave];
+  if (l < 8) xs[kRowsLds - 1][l] = 0;
+  // where this lane's taps lie at position 0: the first of its rows, its two cells
+  const uint16_t* ra = xs[row * 25 + (g < 3 ? 5 * g : 12)];
+  const uint16_t* e0 = xs[row * 25] + (g == 0 ? 16 : g == 1 ? 18 : g == 2 ? 57 : 0);
+  const uint16_t* e1 = xs[row * 25] + (g == 0 ? 17 : g == 1 ? 56 : g == 2 ? 58 : 0);
+  const bf16x8 w1 = as_bf16x8(reinterpret_cast<const uint4*>(W->w1)[l]);
+  for (int e = threadIdx.x; e < kC2Steps * 64; e += kFwdWaves * 64)
+    w2[e] = reinterpret_cast<const uint4*>(W->w2)[e];
+  __syncthreads();
+  const int ch = chan_of(g);
+  const float4 b1 = *reinterpret_cast<const float4*>(&W->b1[ch]);
+  const float4 b2 = *reinterpret_cast<const float4*>(&W->b2[4 * g]);
+  // A workgroup takes consecutive tiles and workgroups of one XCD (dispatched
+  // round robin) neighbouring ones: their windows overlap in its L2.
+  const int per = (tiles + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int lb = gridDim.x % 8 == 0 ? blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8 : blockIdx.x;
+  const int last = min(tiles, (lb + 1) * per);
+  for (int tile = lb * per + wave; tile < last; tile += kFwdWaves) {
     const int w0 = tile * 16;
     if constexpr (FUSED) {
-      build_windows(acc, n_phi, n_qpt, n_d0, peaks, w0, n, l, xs[wave]);
+      build_windows(acc, n_phi, n_qpt, n_d0, peaks, w0, n, l, xs);
     } else {
-      // 16 windows x 256 bytes, 16-byte global reads, 4-byte LDS writes (odd row stride)
-      for (int ch = l; ch < 16 * 16; ch += 64) {
-        const int w = ch / 16, o = (ch % 16) * 8;
+      // 16 windows x 256 bytes, 16-byte global reads
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int w = l / 16 + 4 * u, o = (l % 16) * 8;
         uint4 v = make_uint4(0, 0, 0, 0);
         if (w0 + w < n) v = *reinterpret_cast<const uint4*>(win + (size_t)(w0 + w) * kWin + o);
-        uint32_t* d = reinterpret_cast<uint32_t*>(&xs[wave][w][o]);
-        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+        const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+          const int cell = o + h;
+          if (cell < 125)
+            xs[w * 25 + cell / 5][cell % 5] = (uint16_t)(h & 1 ? d[h / 2] >> 16 : d[h / 2] & 0xFFFFu);
+        }
       }
     }
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const bool valid = w0 + row < n;
     f32x4 acc2 = {0.f, 0.f, 0.f, 0.f};
-    for (int st = 0; st < kC2Steps; ++st) {
-      const int par = st & 1;
-      // conv1 at positions 2 st and 2 st + 1 (27: zero)
+    uint32_t even0 = 0, even1 = 0;  // conv1 at the step's first position
+    uint4 r[4];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int p = 2 * st + h;
-        uint16_t outv[4] = {0, 0, 0, 0};
-        if (p < 27) {
-          const int base = (p / 9) * 25 + ((p / 3) % 3) * 5 + p % 3;
-          bf16x8 a;
+    for (int p = 0; p < 2 * kC2Steps; ++p) {
+      uint32_t o0 = 0, o1 = 0;  // conv1 at p: four channels of the lane's window
+      if (p < 27) {
+        const int pk = p / 9, pj = p / 3 % 3, pi = p % 3;
+        if (p % 9 == 0) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const uint16_t x = off[i] >= 0 ? xs[wave][row][base + off[i]] : (uint16_t)0;
-            a[i] = __builtin_bit_cast(__bf16, x);
-          }
-          f32x4 z = {0.f, 0.f, 0.f, 0.f};
-          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1v, z, 0, 0, 0);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) outv[i] = to_bf16(fmaxf(z[i] + W.b1[c], 0.0f));
+          for (int q = 0; q < 4; ++q) r[q] = *reinterpret_cast<const uint4*>(ra + 8 * (5 * pk + q));
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          hb[wave][par][h][4 * g + i][c] = outv[i];
-          if (ACT && p < 27 && w0 + 4 * g + i < n)
-            h1o[(size_t)(w0 + 4 * g + i) * 432 + p * 16 + c] = outv[i];
+        const uint4 &A = r[pj], &B = r[pj + 1];
+        uint4 x;
+        if (pi == 0) {
+          x.x = A.x;
+          x.y = B.x;
+          x.z = __builtin_amdgcn_perm(B.y, A.y, 0x05040100u);
+        } else if (pi == 1) {
+          x.x = __builtin_amdgcn_alignbit(A.y, A.x, 16);
+          x.y = __builtin_amdgcn_alignbit(B.y, B.x, 16);
+          x.z = __builtin_amdgcn_perm(B.y, A.y, 0x07060302u);
+        } else {
+          x.x = A.y;
+          x.y = B.y;
+          x.z = __builtin_amdgcn_perm(B.z, A.z, 0x05040100u);
         }
+        const int at = 40 * pk + 8 * pj + pi;
+        x.w = (uint32_t)e0[at] | (uint32_t)e1[at] << 16;
+        if constexpr (!FUSED) {  // a caller's window can hold what no zero weight cancels
+          x.y = g < 3 ? x.y : 0u;
+          x.z = g < 3 ? x.z : x.z & 0xFFFFu;
+          x.w = g < 3 ? x.w : 0u;
+        }
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
+        z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1, as_bf16x8(x), z, 0, 0, 0);
+        o0 = pk_bf16(fmaxf(z[0] + b1.x, 0.0f), fmaxf(z[1] + b1.y, 0.0f));
+        o1 = pk_bf16(fmaxf(z[2] + b1.z, 0.0f), fmaxf(z[3] + b1.w, 0.0f));
+        if (ACT && valid)
+          *reinterpret_cast<uint2*>(h1o + (size_t)(w0 + row) * 432 + p * 16 + ch) = make_uint2(o0, o1);
       }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      // conv2 k-step: lane (row, g) takes position 2 st + g / 2, channels 8 (g % 2) .. + 7
-      const bf16x8 a2 = as_bf16x8(*reinterpret_cast<const uint4*>(&hb[wave][par][g >> 1][row][8 * (g & 1)]));
-      const bf16x8 b2 = as_bf16x8(*reinterpret_cast<const uint4*>(&W.w2[(st * 64 + l) * 8]));
-      acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a2, b2, acc2, 0, 0, 0);
+      if (p % 2 == 0) {
+        even0 = o0;
+        even1 = o1;
+      } else {
+        // conv2 k-step: lane group g takes position p - 1 + g / 2, channels
+        // 8 (g % 2) .. + 7: the halves of the wave exchange what they lack
+        const auto s0 = __builtin_amdgcn_permlane32_swap(even0, o0, false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(even1, o1, false, false);
+        const uint4 x = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+        acc2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(w2[p / 2 * 64 + l]), as_bf16x8(x), acc2, 0, 0, 0);
+      }
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) h2s[wave][4 * g + i][c] = to_bf16(fmaxf(acc2[i] + W.b2[c], 0.0f));
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const uint2 h2 = make_uint2(pk_bf16(fmaxf(acc2[0] + b2.x, 0.0f), fmaxf(acc2[1] + b2.y, 0.0f)),
+                                pk_bf16(fmaxf(acc2[2] + b2.z, 0.0f), fmaxf(acc2[3] + b2.w, 0.0f)));
+    if (ACT && valid) *reinterpret_cast<uint2*>(h2o + (size_t)(w0 + row) * 16 + 4 * g) = h2;
     // fc1 (K = 16) and fc2
-    const int kq = 4 * g;
-    const bf16x4 a3 = *reinterpret_cast<const bf16x4*>(&h2s[wave][row][kq]);
     float part[4] = {0.f, 0.f, 0.f, 0.f};
+    // opaque: these 40 values a lane are read per tile, not held in registers
+    typedef const __attribute__((address_space(1))) Packed* GlobalPacked;
+    GlobalPacked Wt = (GlobalPacked)W;
+    asm volatile("" : "+s"(Wt));
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
-      const bf16x4 b = *reinterpret_cast<const bf16x4*>(&W.w3[(nt * 64 + l) * 4]);
+      const bf16x4 a = __builtin_bit_cast(bf16x4, reinterpret_cast<const __attribute__((address_space(1))) u32x2*>(Wt->w3)[nt * 64 + l]);
       f32x4 z = {0.f, 0.f, 0.f, 0.f};
-      z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a3, b, z, 0, 0, 0);
-      const int f = 16 * nt + c;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint16_t hv = to_bf16(fmaxf(z[i] + W.b3[f], 0.0f));
-        part[i] += W.w4[f] * from_bf16(hv);
-        if (ACT && w0 + kq + i < n) h3o[(size_t)(w0 + kq + i) * 64 + f] = hv;
-      }
+      z = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, __builtin_bit_cast(bf16x4, h2), z, 0, 0, 0);
+      const int f = 16 * nt + 4 * g;
+      const f32x4 b3 = *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(&Wt->b3[f]);
+      const f32x4 w4 = *reinterpret_cast<const __attribute__((address_space(1))) f32x4*>(&Wt->w4[f]);
+      const uint2 h3 = make_uint2(pk_bf16(fmaxf(z[0] + b3.x, 0.0f), fmaxf(z[1] + b3.y, 0.0f)),
+                                  pk_bf16(fmaxf(z[2] + b3.z, 0.0f), fmaxf(z[3] + b3.w, 0.0f)));
+      part[0] += w4.x * __uint_as_float(h3.x << 16);
+      part[1] += w4.y * __uint_as_float(h3.x & 0xFFFF0000u);
+      part[2] += w4.z * __uint_as_float(h3.y << 16);
+      part[3] += w4.w * __uint_as_float(h3.y & 0xFFFF0000u);
+      if (ACT && valid) *reinterpret_cast<uint2*>(h3o + (size_t)(w0 + row) * 64 + f) = h3;
     }
-    // sum over the 16 lanes of a row (the 64 features of one window)
+    // sum of the 64 features of a window: lane groups, then the lane's own four
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float v = part[i];
-      for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 16);
-      if (c == 0 && w0 + kq + i < n) logits[w0 + kq + i] = v + W.b4[0];
+      part[i] += __shfl_xor(part[i], 32);
+      part[i] += __shfl_xor(part[i], 16);
     }
-    if (ACT) {
-      for (int e = l; e < 16 * 16; e += 64) {
-        const int w = e / 16;
-        if (w0 + w < n) h2o[(size_t)(w0 + w) * 16 + e % 16] = (&h2s[wave][0][0])[e];
-      }
-    }
+    const float v = (part[0] + part[2]) + (part[1] + part[3]);
+    if (g == 0 && valid) logits[w0 + row] = v + W->b4[0];
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
@@ -309,7 +397,9 @@ constexpr int kBwdWaves = 4;
 // workgroups at most: each adds the whole gradient once (4096 windows: 64, 128 and
 // 256 workgroups take 32.6, 25.0 and 26.2 us)
 constexpr int kBwdGrid = 128;
-constexpr int kXb = 130;        // row stride of the windows (as kXs)
+// row stride of the windows: 130 = 65 dwords, odd, so that 16 rows read at one
+// column fall in different banks
+constexpr int kXb = 130;
 
 __device__ __forceinline__ bf16x4 pack4(uint16_t a, uint16_t b, uint16_t c, uint16_t d) {
   bf16x4 v;
@@ -543,10 +633,9 @@ __global__ __launch_bounds__(256) void keep_emit_kernel(const float* __restrict_
   }
 }
 
-// inference grid: the workgroups that fit the chip at once (3 per CU by LDS),
-// each wave looping over tiles, so the weights are copied into LDS once per
-// resident workgroup
-constexpr int kFwdGrid = 768;
+// forward grid: the workgroups that fit the chip at once (4 per CU by
+// registers), one tile each while there are fewer tiles than workgroups
+constexpr int kFwdGrid = 1024;
 
 int blocks(int64_t n, int per, int cap = 8192) {
   int64_t b = (n + per - 1) / per;
@@ -583,7 +672,7 @@ int launch_cnn_forward(const float* params, const uint16_t* win, const int32_t* 
   pack_kernel<<<kPackBlocks, 256, 0, s>>>(params, W, nullptr, nullptr);
   HT_CHECK(hipGetLastError());
   const int tiles = (n_max + 15) / 16;
-  forward_kernel<false, false><<<blocks(tiles, kFwdWaves, kFwdGrid), kFwdWaves * 64, 0, s>>>(
+  forward_kernel<false, false><<<blocks(tiles, 1, kFwdGrid), kFwdWaves * 64, 0, s>>>(
       W, win, nullptr, 0, 0, 0, nullptr, n_dev, n_max, logits, nullptr, nullptr, nullptr);
   HT_CHECK(hipGetLastError());
   return HT_OK;
@@ -596,7 +685,7 @@ int launch_cnn_score(const Plan& p, const float* params, const int32_t* acc, con
   HT_CHECK(hipGetLastError());
   const ht_grid& g = p.grid;
   const int tiles = (cap + 15) / 16;
-  forward_kernel<true, false><<<blocks(tiles, kFwdWaves, kFwdGrid), kFwdWaves * 64, 0, s>>>(
+  forward_kernel<true, false><<<blocks(tiles, 1, kFwdGrid), kFwdWaves * 64, 0, s>>>(
       W, nullptr, acc, g.n_phi, g.n_qpt, g.n_d0, peaks, n_peaks, cap, logits, nullptr, nullptr,
       nullptr);
   HT_CHECK(hipGetLastError());
@@ -621,7 +710,7 @@ int launch_cnn_train(float* params, float* mom, const uint16_t* win, const float
   pack_kernel<<<kPackBlocks, 256, 0, s>>>(params, W, grad, loss);
   HT_CHECK(hipGetLastError());
   const int tiles = (n + 15) / 16;
-  forward_kernel<false, true><<<blocks(tiles, kFwdWaves, 4096), kFwdWaves * 64, 0, s>>>(
+  forward_kernel<false, true><<<blocks(tiles, 1, kFwdGrid), kFwdWaves * 64, 0, s>>>(
       W, win, nullptr, 0, 0, 0, nullptr, nullptr, n, logits, h1, h2, h3);
   HT_CHECK(hipGetLastError());
   backward_kernel<<<blocks(tiles, 1, kBwdGrid), kBwdWaves * 64, 0, s>>>(
