@@ -5,7 +5,7 @@
 // gfx950 mapping.  One workgroup owns a tile of 64 consecutive q/pT columns
 // at one d0 (lane = column), so a tile's accumulator rows are one contiguous
 // block of the output.  The tile's counters live in LDS: 32-bit counters
-// when 64 rows fit in the 160 KiB of a gfx950 CU (n_phi <= 639), otherwise
+// when 64 rows fit in the 160 KiB of a gfx950 CU (n_phi <= 620), otherwise
 // 16-bit halves of 32 rows, column c in the low half of row c and column
 // c + 32 in the high half (a column holds at most n_hits <= 65535 votes per
 // bin, so a ds_add_u32 of 1 or 1 << 16 never carries across the halves; a
@@ -13,14 +13,18 @@
 // as with 32-bit counters).  The row stride is odd in dwords so neighbouring
 // columns fall in different banks.  Waves of
 // the workgroup split the hits: each wave loads 64 hits with one coalesced
-// load, keeps them in VGPRs and broadcasts them one at a time through SGPRs
-// (v_readlane), so the per-evaluation work is pure VALU with scalar hit
+// load, keeps them in VGPRs and broadcasts them through SGPRs (v_readlane, eight
+// hits a turn), so the per-evaluation work is pure VALU with scalar hit
 // operands plus one LDS atomic.  The arcsine and the |u| <= 1 test depend on
 // the hit only through its radius: the workgroup first collects the distinct
 // radii of its hits (the layers of a barrel tracker) and computes them once
-// per radius and column into an LDS table, so a hit on a known radius costs
-// one table read, three operations, the wrap and the atomic.  The tile is written to HBM once, by
-// contiguous stores, so no clearing pass is needed.  No MFMA: the vote is a
+// per radius and column into a table, so a hit on a known radius costs one
+// indexed register read, three operations, the wrap and the atomic, without a
+// branch: 12 vector instructions, whose issue bounds the kernel (3600 hits 49 ->
+// 32 us, 31 thousand 303 -> 197, 55 thousand 503 -> 312 against a loop that took one
+// hit at a time with a branch on its radius and on its vote).  A hit of its own
+// radius takes about 45 (100 thousand on single radii: 911 -> 847 us).  The tile is
+// written to HBM once, by contiguous stores, so no clearing pass is needed.  No MFMA: the vote is a
 // scatter, not a contraction.
 //
 // Grids with few tiles (the 2D grid has four) would leave most CUs idle, so
@@ -39,6 +43,7 @@ namespace {
 
 constexpr int kVoteWaves = 16;
 constexpr int kVoteThreads = kVoteWaves * kWave;
+constexpr int kCast = 8;  // hits of known radius in flight per wave (64 % kCast == 0)
 
 __device__ __forceinline__ float bcast(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
@@ -63,6 +68,7 @@ __global__ __launch_bounds__(kVoteThreads) void vote_kernel(
     float phi_lo, float invw, int stride) {
   extern __shared__ uint32_t lds[];
   __shared__ RadiusSet R;
+  __shared__ unsigned long long s_votes[kVoteWaves];
   __shared__ float s_tab[kMaxRadii][kWave];  // arcsine per (radius, column), NaN: no vote
   // blockIdx.z = event * slices + slice of the event's hits
   const int n_slices = gridDim.z / NB;
@@ -110,10 +116,12 @@ __global__ __launch_bounds__(kVoteThreads) void vote_kernel(
   }
   __syncthreads();
   // the lane's column of the table in registers, indexed by the
-  // wave-uniform radius index (no LDS round trip per hit)
-  float sreg[kMaxRadii];
+  // wave-uniform radius index (no LDS round trip per hit); the last entry is
+  // the invalid hit's
+  float sreg[kMaxRadii + 1];
 #pragma unroll
-  for (int a = 0; a < kMaxRadii; ++a) sreg[a] = a < R.n ? s_tab[a][lane] : __builtin_nanf("");
+  for (int a = 0; a <= kMaxRadii; ++a)
+    sreg[a] = a < kMaxRadii && a < R.n ? s_tab[a % kMaxRadii][lane] : __builtin_nanf("");
 
   uint32_t* col = lds + (lane % kRows) * stride;
   const uint32_t inc = WIDE || lane < kRows ? 1u : 65536u;
@@ -126,47 +134,69 @@ __global__ __launch_bounds__(kVoteThreads) void vote_kernel(
       hp = phi[h];
       hv = hit_ok(hr, hp);
     }
-    const float hr2 = hr * hr;
-    const float hir = 1.0f / hr;
-    const int hri = hv ? radius_index(R, hr) : -1;
+    const int hri = hv ? radius_index(R, hr) : kMaxRadii;
     uint64_t todo = __ballot(hv);
-    while (todo) {
-      const int src = __builtin_ctzll(todo);
-      todo &= todo - 1;
-      const int ri = __builtin_amdgcn_readlane(hri, src);
-      const float ph = bcast(hp, src);
-      bool ok;
-      float s;
-      if (ri >= 0) {
-        s = sreg[ri];
-        ok = s == s;
-      } else {
-        const float r2 = bcast(hr2, src);
-        const float ir = bcast(hir, src);
-        const float a = ck * r2;
-        const float b = a + cq;
-        const float c = b * ir;
-        const float u = c * ct;
-        ok = col_ok && (fabsf(u) <= 1.0f);
-        s = asin_f(u);
-      }
-      const float phi0 = ph - s;
+    if (!todo) continue;
+    // The bin of a vote.  x lies in [-n_phi, 2 n_phi) (|phi| <= 4, |asin| <= pi/2):
+    // one period of correction is enough; a power of two wraps with a mask;
+    // floor and conversion in one instruction (x is finite and in range
+    // whenever the vote counts).
+    const auto bin = [&](float ph, float sv) {
+      const float phi0 = ph - sv;
       const float d = phi0 - phi_lo;
       const float x = d * invw;
-      // x lies in [-n_phi, 2 n_phi) (|phi| <= 4, |asin| <= pi/2): one
-      // period of correction is enough; a power of two wraps with a mask
-      // floor and conversion in one instruction (x is finite and in range
-      // whenever the vote counts)
       int i;
       asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(x));
-      if (POW2) {
-        i &= n_phi - 1;
-      } else {
-        i = i < 0 ? i + n_phi : i;
-        i = i >= n_phi ? i - n_phi : i;
+      if (POW2) return i & (n_phi - 1);
+      i = i < 0 ? i + n_phi : i;
+      return i >= n_phi ? i - n_phi : i;
+    };
+    // kCast hits at a time from fixed lanes (a read of a lane that a register
+    // names takes twice as long)
+    const int m = kWave - __builtin_clzll(todo);
+    if (__ballot(hri < 0) == 0) {
+      // Every radius is in the table: no test per hit, several hits' chains of
+      // reads, arithmetic and the atomic run side by side.  A hit that casts no
+      // vote adds to the word after the row, which is never read: no branch.
+#pragma unroll 1
+      for (int h8 = 0; h8 < m; h8 += kCast) {
+        const float p8 = __shfl(hp, h8 + lane);
+        const int r8 = __shfl(hri, h8 + lane);
+#pragma unroll
+        for (int u = 0; u < kCast; ++u) {
+          const float sv = sreg[__builtin_amdgcn_readlane(r8, u)];
+          const int i = bin(bcast(p8, u), sv);
+          atomicAdd(&col[sv == sv ? i : n_phi], inc);
+        }
       }
-      if (ok) {
-        atomicAdd(&col[i], inc);
+      continue;
+    }
+    const float hr2 = hr * hr;
+    const float hir = 1.0f / hr;
+#pragma unroll 1
+    for (int h8 = 0; h8 < m; h8 += kCast) {
+      const float p8 = __shfl(hp, h8 + lane);
+      const int r8 = __shfl(hri, h8 + lane);
+      const float rr8 = __shfl(hr2, h8 + lane);
+      const float ir8 = __shfl(hir, h8 + lane);
+#pragma unroll
+      for (int u = 0; u < kCast; ++u) {
+        const int ri = __builtin_amdgcn_readlane(r8, u);
+        float sv;
+        bool ok;
+        if (ri >= 0) {
+          sv = sreg[ri];
+          ok = sv == sv;
+        } else {
+          const float a = ck * bcast(rr8, u);
+          const float b = a + cq;
+          const float c = b * bcast(ir8, u);
+          const float uu = c * ct;
+          ok = col_ok && (fabsf(uu) <= 1.0f);
+          sv = asin_f(uu);
+        }
+        const int i = bin(bcast(p8, u), sv);
+        if (ok) atomicAdd(&col[i], inc);
       }
     }
   }
@@ -175,27 +205,17 @@ __global__ __launch_bounds__(kVoteThreads) void vote_kernel(
   // write the tile: rows j0 .. j0+ncol-1 of plane k are contiguous
   const int ncol = min(kWave, n_qpt - j0);
   int32_t* out = acc + ((size_t)k * n_qpt + j0) * n_phi;
-  const int total = ncol * n_phi;
-  auto tile = [&](int e) {
-    const int cj = e / n_phi;
-    const int i = e - cj * n_phi;
-    if (WIDE) return (int32_t)lds[cj * stride + i];
-    const uint32_t w = lds[(cj % kRows) * stride + i];
-    return (int32_t)(cj >= kRows ? (w >> 16) : (w & 0xFFFFu));
-  };
   // the vote count, when asked for, is the sum of the tile's counters (the
   // loop above keeps no count of its own)
   uint32_t votes = 0;
-  if (n_slices == 1) {
-    for (int e = threadIdx.x; e < total; e += kVoteThreads) {
-      const int32_t v = tile(e);
-      out[e] = v;
-      votes += (uint32_t)v;
-    }
-  } else {
-    for (int e = threadIdx.x; e < total; e += kVoteThreads) {
-      const int32_t v = tile(e);
-      if (v) atomicAdd(&out[e], v);
+  for (int cj = wave; cj < ncol; cj += kVoteWaves) {  // a column per wave: no division per cell
+    const uint32_t* row = lds + cj % kRows * stride;
+    for (int i = lane; i < n_phi; i += kWave) {
+      const int32_t v = (int32_t)(WIDE ? row[i] : (cj >= kRows ? row[i] >> 16 : row[i] & 0xFFFFu));
+      if (n_slices == 1)
+        out[cj * n_phi + i] = v;
+      else if (v)
+        atomicAdd(&out[cj * n_phi + i], v);
       votes += (uint32_t)v;
     }
   }
@@ -203,7 +223,13 @@ __global__ __launch_bounds__(kVoteThreads) void vote_kernel(
   if (n_votes) {
     unsigned long long v = votes;
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if (lane == 0 && v) atomicAdd(n_votes, v);
+    // one global atomic per workgroup: one per wave to the same word took 10 ns each
+    if (lane == 0) s_votes[wave] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < kVoteWaves; ++w) v += s_votes[w];
+      if (v) atomicAdd(n_votes, v);
+    }
   }
 }
 
@@ -225,10 +251,12 @@ __global__ void zero_i32_kernel(int32_t* __restrict__ p, int64_t n) {
     p[e] = 0;
 }
 
-// LDS of a CU less the kernel's static arrays (radius set and table)
-constexpr int kLdsBytes = 160 * 1024 - (int)sizeof(RadiusSet) - kMaxRadii * kWave * 4;
-bool vote_wide(int n_phi) { return (size_t)kWave * (size_t)(n_phi | 1) * 4 <= (size_t)kLdsBytes; }
-int vote_stride(int n_phi) { return n_phi | 1; }  // odd dword stride
+// LDS of a CU less the kernel's static arrays (radius set, table and vote sums)
+constexpr int kLdsBytes =
+    160 * 1024 - (int)sizeof(RadiusSet) - kMaxRadii * kWave * 4 - 8 * kVoteWaves;
+// odd dword stride, with a word to spare after the row
+int vote_stride(int n_phi) { return (n_phi + 1) | 1; }
+bool vote_wide(int n_phi) { return (size_t)kWave * vote_stride(n_phi) * 4 <= (size_t)kLdsBytes; }
 // LDS bytes of a tile: 64 rows of 32-bit counters, or 32 rows of 16-bit pairs
 size_t vote_lds_bytes(int n_phi, bool wide) {
   return (size_t)(wide ? kWave : kWave / 2) * vote_stride(n_phi) * 4;
