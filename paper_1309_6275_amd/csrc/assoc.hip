@@ -327,6 +327,13 @@ template <int NB>
 __device__ __forceinline__ const AssocArgs& event_args(const AssocBatch<NB>& B) {
   return B.a[NB == 1 ? 0 : blockIdx.z];
 }
+// The same where registers are short: the index is not known to be 0, so the
+// arguments are read where they are used instead of held (and spilled) from the
+// start.
+template <int NB>
+__device__ __forceinline__ const AssocArgs& event_args_late(const AssocBatch<NB>& B) {
+  return B.a[blockIdx.z];
+}
 
 // first word of a member entry: the hit (< 65536) and its layer (< 16)
 __device__ __forceinline__ unsigned member_word(const AssocArgs& A, int h) {
@@ -2028,9 +2035,12 @@ refine_kernel(AssocBatch<NB> AB, int n_lo, int n_hi) {
 // gathered hit by hit, cost more than the search itself: with the hits sorted
 // once per event a candidate's members are contiguous runs.  Member lists and
 // seed search per event, before and after, in ms: 55k hits on ten radii (member_cap
-// 1024) 4.84 -> 1.78; 3000 tracks with smeared radii (member sweep before) 11.9 ->
-// 3.2; 3.6k hits (cap 128) 0.41 -> 0.29; four 2.5k-hit events in a batch (cap 256)
-// 1.43 -> 0.45.
+// 1024) 4.84 -> 1.69; 3000 tracks with smeared radii (member sweep before) 11.9 ->
+// 3.2; 3.6k hits (cap 128) 0.41 -> 0.27; four 2.5k-hit events in a batch (cap 256)
+// 1.43 -> 0.44.  A lane read whose lane is in a register takes twice the issue
+// time of other instructions: each layer's place in the list is packed into one
+// word in visiting order (3.6k hits: 236 -> 227 us), and arguments read at their
+// use instead of spilled at the start took off another 3 to 8% (221 us).
 constexpr int kRunWaves = 4;
 constexpr int kRunWords = 64;    // member bits kept for 64 * 64 run hits; longer runs are tested again
 constexpr int kListRun = 256;    // run hits and
@@ -2053,7 +2063,7 @@ struct alignas(16) ListMem {
   float adx;
 };
 struct RejectShared {
-  ListMem mem[kListMembers + 4];  // members by layer, and room to read past the last
+  ListMem mem[kListMembers + kWave];  // members by layer, and room to read past the last
   double2 sxy[3][4];       // the seeds' coordinates
 };
 struct RunShared {
@@ -2273,16 +2283,20 @@ __device__ __forceinline__ void seed_layers(unsigned lmask, int nS, int min_laye
 
 // Visiting order: the layers that are not seed layers by increasing member count
 // (then index), so that lanes meet a layer without an inlier early; then the
-// seed layers.  A lane's outcome does not depend on it.  Lane i receives the i-th
-// of the former; cnt is the member count on lane o + L.
-__device__ __forceinline__ int visit_order(unsigned nsm, int o, int cnt) {
+// seed layers.  A lane's outcome does not depend on it.  Lane i receives the
+// value of the i-th layer; cnt is the member count on lane o + L.
+__device__ __forceinline__ int visit_order(unsigned nsm, unsigned smask, int o, int cnt, int value) {
   const int lane = threadIdx.x & (kWave - 1);
-  const bool mine = (lane & 48) == o && ((nsm >> (lane & 15)) & 1u);
-  const int key = mine ? ((cnt << 4) | (lane & 15)) : 0x7fffffff;
+  const int L = lane & 15;
+  const bool row = (lane & 48) == o;
+  const bool mine = row && ((nsm >> L) & 1u);
+  const int key = mine ? ((cnt << 4) | L) : 0x7fffffff;
   int rank = 0;
   for (unsigned m = nsm; m; m &= m - 1u) rank += bcasti(key, o + __builtin_ctz(m)) < key ? 1 : 0;
+  if (!mine) rank = __popc(nsm) + __popc(smask & ((1u << L) - 1u));
   // a forward permute; the other lanes send to lane 63, whose value is never read
-  return __builtin_amdgcn_ds_permute((mine ? rank : kWave - 1) * 4, lane & 15);
+  const bool any = mine || (row && ((smask >> L) & 1u));
+  return __builtin_amdgcn_ds_permute((any ? rank : kWave - 1) * 4, value);
 }
 
 // The workgroup's totals: tot[w][c] of its waves, one atomic per counter from
@@ -2347,7 +2361,7 @@ __device__ __forceinline__ Circle32 circle32(double2 pa, double2 pb, double2 pc,
 
 template <int NB>
 __global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch<NB> AB) {
-  const AssocArgs& A = event_args(AB);
+  const AssocArgs& A = event_args_late(AB);
   const int np = n_cands(A);
   if (A.sc[S_MODE] == 0 || np < kFewCands || (int)blockIdx.x * kRunWaves >= np) return;
   __shared__ RejectShared RS[kRunWaves];
@@ -2458,20 +2472,20 @@ __global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch
       const int se = s == 0 ? sst[0] : (s == 1 ? sst[1] : sst[2]);
       const double2 xy = A.sxy[se + (int)((unsigned)key & 0xffffu)];
       const int nmax = max(n0, max(n1, n2));
+      const int mine = en - st;
+      const unsigned long long* from = keys + 2 * st;
       int rank = 0;
-      // every lane reads every round; rounds past the lane's own layer read a
-      // record inside the list and do not count
+      // every lane reads every round; rounds past the lane's own layer read what
+      // lies behind (at most 64 records past the list) and do not count
 #pragma unroll 4
-      for (int t = 0; t < nmax; ++t) {
-        const int e2 = st + t;
-        const unsigned long long k2 = keys[2 * (e2 < n ? e2 : n - 1)];
-        rank += (e2 < en && k2 < key) ? 1 : 0;
-      }
+      for (int t = 0; t < nmax; ++t) rank += (t < mine && from[2 * t] < key) ? 1 : 0;
       if (s >= 0 && rank < kk) S.sxy[s][rank] = xy;
       const unsigned smask = (1u << Ls[0]) | (1u << Ls[1]) | (1u << Ls[2]);
       const unsigned nsm = lmask & ~smask;
-      const int n_ns = __popc(nsm);
-      const int orderv = visit_order(nsm, o, cnt_l);
+      // lane i: the i-th layer to visit, first member | behind the last << 8 | layer << 16
+      const int orderv =
+          visit_order(nsm, smask, o, cnt_l, (mend_l - cnt_l) | mend_l << 8 | (lane & 15) << 16);
+      const float rm2_o = __shfl(rm2_l, orderv >> 16, kWave);
       wave_sync();
       // ---- seed circles: lane = 16 a + 4 b + c (seed_k <= 4)
       const int ia = lane >> 4, ib = (lane >> 2) & 3, ic = lane & 3;
@@ -2498,21 +2512,13 @@ __global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch
       const float thr = pre + 2e-6f * (fabsf(Af) * rmax * rmax +
                                        (fabsf(Bf) + fabsf(Cf)) * rmax + fabsf(Df));
       int c = C.ok ? 0 : -64;
-      unsigned sseq = smask;
-      int remaining = nS;
+#pragma unroll 1
       for (int it = 0; it < nS; ++it) {
-        int L;
-        if (it < n_ns) {
-          L = __builtin_amdgcn_readlane(orderv, it);
-        } else {
-          L = __builtin_ctz(sseq);
-          sseq &= sseq - 1u;
-        }
-        // lanes that cannot reach min_layers any more
-        if (__ballot(c + remaining >= cfg.min_layers) == 0ull) break;
-        --remaining;
-        const int me = bcasti(mend_l, o + L), ms = me - bcasti(cnt_l, o + L);
-        const float base = __builtin_fmaf(Af, bcastf(rm2_l, L), Df);  // layers of one radius
+        // no lane can reach min_layers any more
+        if (__ballot(c + nS - it >= cfg.min_layers) == 0ull) break;
+        const int at = __builtin_amdgcn_readlane(orderv, it);
+        const int ms = at & 0xff, me = (at >> 8) & 0xff;
+        const float base = __builtin_fmaf(Af, bcastf(rm2_o, it), Df);  // layers of one radius
         bool hit = false;
         for (int m = ms; m < me; m += 4) {
           // four members at a time (those past the layer's last do not count)
@@ -2547,7 +2553,7 @@ __global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch
 
 template <int NB>
 __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<NB> AB) {
-  const AssocArgs& A = event_args(AB);
+  const AssocArgs& A = event_args_late(AB);
   if (A.sc[S_MODE] == 0) return;
   __shared__ RunShared RS[kRunWaves];
   __shared__ RunLayer T[HT_MAX_LAYERS];
@@ -2784,8 +2790,7 @@ __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<N
         }
         const unsigned smask = (1u << Ls[0]) | (1u << Ls[1]) | (1u << Ls[2]);
         const unsigned nsm = lmask & ~smask;
-        const int n_ns = __popc(nsm);
-        const int orderv = visit_order(nsm, o, cnt_l);
+        const int orderv = visit_order(nsm, smask, o, cnt_l, lane & 15);
         if (A.origin_seed) ns[0] = 1;
         wave_sync();
         // ---- seed circles: lane = 16 a + 4 b + c (seed_k <= 4), in float32 for the
@@ -2845,17 +2850,10 @@ __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<N
         int on_road = 0;     // layers with a hit that may be on the road
         int amb2 = -1;       // layer << 16 | place of a second hit that may be nearer
         unsigned ambm = 0u;  // layers with more hits that may be the nearest
-        unsigned sseq = smask;
         int remaining = nS;
 #pragma unroll 1
         for (int it = 0; it < nS; ++it) {
-          int L;
-          if (it < n_ns) {
-            L = __builtin_amdgcn_readlane(orderv, it);
-          } else {
-            L = __builtin_ctz(sseq);
-            sseq &= sseq - 1u;
-          }
+          const int L = __builtin_amdgcn_readlane(orderv, it);
           // lanes that cannot reach min_layers any more
           active = active && on_road + remaining >= cfg.min_layers;
           --remaining;
