@@ -9,8 +9,8 @@
 //             a float32 record; ownership keys cleared; counters and the
 //             vertex accumulator zeroed;
 //   runs      each layer's radius range and hit count; the hits grouped by
-//             (layer, azimuth bucket) with a counting sort (layers, bcount,
-//             bscan, bscatter; small events: prep and runs in one launch,
+//             (layer, azimuth bucket) with a counting sort (bcount, bscan,
+//             bscatter; small events: prep and runs in one launch,
 //             prep_small).  Events with a layer of widely spread radii take the
 //             sweep instead;
 //   reject,   the seed search on the layer runs, one wave per candidate: member
@@ -438,9 +438,21 @@ __device__ __forceinline__ int bucket_of(float aw) {
   return t < 1.0f ? 0 : (t >= (float)(kBuckets - 1) ? kBuckets - 1 : (int)t);
 }
 
-// each layer's radius range and hit count (each workgroup's, then the event's)
+// whether the event's layers are narrow enough for the runs (wave-uniform)
+__device__ __forceinline__ bool layer_mode(const AssocArgs& A) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int L = lane & (HT_MAX_LAYERS - 1);
+  const float lo = __int_as_float(A.lay[L]), hi = __int_as_float(A.lay[HT_MAX_LAYERS + L]);
+  const bool wide = A.lay[2 * HT_MAX_LAYERS + L] > 0 && !(hi <= kLayerSpread * lo);
+  return __ballot(wide) == 0ull;
+}
+
+// Each layer's radius range and hit count (each workgroup's, then the event's),
+// and each member-eligible hit's bucket and slot in it.  One pass over the hits:
+// the buckets are counted before it is known whether the event takes the runs
+// (a launch of 4.5 us for the ranges alone, before).
 template <int NB>
-__global__ __launch_bounds__(256) void layers_kernel(AssocBatch<NB> AB) {
+__global__ __launch_bounds__(256) void bcount_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
   __shared__ int32_t lo[HT_MAX_LAYERS], hi[HT_MAX_LAYERS], cnt[HT_MAX_LAYERS];
   if (threadIdx.x < HT_MAX_LAYERS) {
@@ -451,17 +463,22 @@ __global__ __launch_bounds__(256) void layers_kernel(AssocBatch<NB> AB) {
   __syncthreads();
   const int n = hits_of(A);
   for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < n; h += gridDim.x * blockDim.x) {
-    const float rv = A.r[h];
+    const float rv = A.r[h], ph = A.phi[h];
     const int L = A.layer[h];
-    if (!hit_ok(rv, A.phi[h])) continue;
-    if (L >= HT_MAX_LAYERS) {
-      atomicAdd(&A.sc[S_NBAD], 1);
-      continue;
+    int key = -1;
+    if (hit_ok(rv, ph)) {
+      if (L >= HT_MAX_LAYERS) {
+        atomicAdd(&A.sc[S_NBAD], 1);
+      } else {
+        const int b = L * kBuckets + bucket_of(wrap_pi_f(ph));
+        key = b | (atomicAdd(&A.bkt[b], 1) << 15);  // b < 2^15, slots < 2^16
+        const int32_t k = __float_as_int(rv);  // positive: orders like the radius
+        if (k < lo[L]) atomicMin(&lo[L], k);
+        if (k > hi[L]) atomicMax(&hi[L], k);
+        atomicAdd(&cnt[L], 1);
+      }
     }
-    const int32_t k = __float_as_int(rv);  // positive: orders like the radius
-    if (k < lo[L]) atomicMin(&lo[L], k);
-    if (k > hi[L]) atomicMax(&hi[L], k);
-    atomicAdd(&cnt[L], 1);
+    A.hkey[h] = key;
   }
   __syncthreads();
   if (threadIdx.x < HT_MAX_LAYERS && cnt[threadIdx.x] > 0) {
@@ -471,41 +488,13 @@ __global__ __launch_bounds__(256) void layers_kernel(AssocBatch<NB> AB) {
   }
 }
 
-// whether the event's layers are narrow enough for the runs (wave-uniform)
-__device__ __forceinline__ bool layer_mode(const AssocArgs& A) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int L = lane & (HT_MAX_LAYERS - 1);
-  const float lo = __int_as_float(A.lay[L]), hi = __int_as_float(A.lay[HT_MAX_LAYERS + L]);
-  const bool wide = A.lay[2 * HT_MAX_LAYERS + L] > 0 && !(hi <= kLayerSpread * lo);
-  return __ballot(wide) == 0ull;
-}
-
-// each member-eligible hit's bucket and slot in it
-template <int NB>
-__global__ __launch_bounds__(256) void bcount_kernel(AssocBatch<NB> AB) {
-  const AssocArgs& A = event_args(AB);
-  const bool on = layer_mode(A);
-  if (blockIdx.x == 0 && threadIdx.x == 0) A.sc[S_MODE] = on ? 1 : 0;
-  const int t0 = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
-  if (!on) return;
-  const int n = hits_of(A);
-  for (int h = t0; h < n; h += step) {
-    const float rv = A.r[h], ph = A.phi[h];
-    const int L = A.layer[h];
-    int key = -1;
-    if (hit_ok(rv, ph) && L < HT_MAX_LAYERS) {
-      const int b = L * kBuckets + bucket_of(wrap_pi_f(ph));
-      key = b | (atomicAdd(&A.bkt[b], 1) << 15);  // b < 2^15, slots < 2^16
-    }
-    A.hkey[h] = key;
-  }
-}
-
 // one workgroup per layer: its row of bucket starts, both copies of its hits
 template <int NB>
 __global__ __launch_bounds__(256) void bscan_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
-  if (A.sc[S_MODE] == 0) return;
+  const bool on = layer_mode(A);
+  if (blockIdx.x == 0 && threadIdx.x == 0) A.sc[S_MODE] = on ? 1 : 0;
+  if (!on) return;
   __shared__ int32_t wsum[4];
   constexpr int G = kBuckets / 256;  // buckets per thread
   static_assert(G % 4 == 0, "whole 16-byte vectors per thread");
@@ -582,9 +571,9 @@ __global__ __launch_bounds__(256) void bscatter_kernel(AssocBatch<NB> AB) {
 
 // Small events (at most kPrepHits hits of the bound): everything above in one
 // launch, the sort by one workgroup per event with its bucket counters in LDS.
-// Five launches of 2 to 5 us each, nothing in them but latency, become one: 8.5 us
-// instead of 18 at 250 hits, 14 instead of 22 at 1500; at 3600 hits one workgroup
-// would take 28 us and the five launches 27.  Workgroup 0 sorts, the others clear.
+// Four launches of 4 to 5 us each, nothing in them but latency, become one: 8.5 us
+// instead of 18 at 250 hits, 14 instead of 19 at 1500; at 3600 hits one workgroup
+// would take 28 us and the four launches 20.  Workgroup 0 sorts, the others clear.
 constexpr int kPrepHits = 2048;
 constexpr int kPrepThreads = 1024;
 template <int NB>
@@ -3989,8 +3978,6 @@ int assoc_sequence(const AssocBatch<NB>& AB, const Plan* const* P, int32_t n_hit
     const int hblocks = blocks_for(n_hits, 256) < 256 ? blocks_for(n_hits, 256) : 256;
     const dim3 hgrid(hblocks, 1, NB);
     P0.prof_mark(HT_STAGE_MEMBERS, 0, s);
-    layers_kernel<NB><<<hgrid, 256, 0, s>>>(AB);
-    HT_CHECK(hipGetLastError());
     bcount_kernel<NB><<<hgrid, 256, 0, s>>>(AB);
     HT_CHECK(hipGetLastError());
     bscan_kernel<NB><<<dim3(HT_MAX_LAYERS, 1, NB), 256, 0, s>>>(AB);
