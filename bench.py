@@ -116,8 +116,7 @@ def copy_calibration():
 
 # the sources a kernel's code comes from (plan and launch code excluded)
 KERNEL_SOURCES = {"vote": ("vote.hip", "ht_device.h"),
-                  "refine": ("assoc.hip", "ht_device.h"),
-                  "members": ("assoc.hip", "ht_device.h")}
+                  "refine": ("assoc.hip", "ht_device.h")}
 
 
 def kernel_source_sha(kernel):

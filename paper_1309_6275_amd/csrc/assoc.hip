@@ -2019,7 +2019,7 @@ refine_kernel(AssocBatch<NB> AB, int n_lo, int n_hi) {
 // road.
 //
 // Bound by VALU issue (rocprofv3: 78% of the SIMDs' issue cycles on 55k-hit
-// events, about all of them on events of smeared radii; 576 instructions per
+// events, about all of them on events of smeared radii; some 550 instructions per
 // candidate in reject_kernel).  Member lists written to memory and read back,
 // gathered hit by hit, cost more than the search itself: with the hits sorted
 // once per event a candidate's members are contiguous runs.  Member lists and

@@ -228,7 +228,7 @@ __device__ __forceinline__ void build_windows(const int32_t* __restrict__ acc, i
 // are two whole rows of three cells and two single cells.  A row is read once
 // for its three phi0 offsets and as the first and the second row: 12 row reads
 // and 54 reads of one cell per tile, where every tap of every position was read
-// by itself (216) and conv1 went through LDS.  480 thousand windows: 195 -> 69 us
+// by itself (216) and conv1 went through LDS.  452 thousand windows: 195 -> 69 us
 // (before: 2175 vector instructions and 1800 LDS cycles a tile).
 template <bool FUSED, bool ACT>
 __global__ __launch_bounds__(kFwdWaves * 64, 4) void forward_kernel(

@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256) void flag4s_kernel(PeakBatch<NB> PB, int n_qpt
 }
 
 // One wave per tile: its 16 ballot words in the first lanes, then 256 cells at
-// a time; no barrier.  480 thousand peaks of 8.4 million cells: 10.9 -> 8.2 us
+// a time; no barrier.  8.4 million cells: 10.9 -> 8.2 us
 // against a workgroup per tile (8192 of them).
 constexpr int kEmitTiles = 4;  // tiles (waves) of a workgroup
 
