@@ -44,6 +44,7 @@
 #include <type_traits>
 
 #include "ht_internal.h"
+#include "run_search.h"
 
 namespace ht {
 namespace {
@@ -2034,7 +2035,6 @@ constexpr int kRunWaves = 4;
 constexpr int kRunWords = 64;    // member bits kept for 64 * 64 run hits; longer runs are tested again
 constexpr int kListRun = 256;    // run hits and
 constexpr int kListMembers = 128;  // members of a candidate that reject_kernel takes
-constexpr int kStage = 256;      // hits staged at a time
 constexpr int kTab = 256;        // buckets whose starts are staged
 constexpr int kScanAll = 16;     // runs of at most this many hits are read whole by every lane
 constexpr int kPending = -3;     // candidate status: not looked at by reject_kernel
@@ -2944,10 +2944,10 @@ __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<N
           // visit's number share a word, the number in the low 9 bits: the order of
           // the words is the order of |f| to 2^-14, and infinities and what is not a
           // number come last.
-          constexpr unsigned kNum = 511u;
+          constexpr unsigned kNum = kVisitNum;
           const int at0 = shortr ? bb : 0;
-          const unsigned top = __float_as_uint(thr) & ~kNum;  // no hit at or beyond it
-          float b1 = thr, b2 = thr, b3 = thr;
+          const unsigned top = road_words(__float_as_uint(thr));  // no hit at or beyond it
+          float b1 = __uint_as_float(top), b2 = b1, b3 = b1;
           int be = -1, be2 = -1;
 #pragma unroll 1
           for (int g0 = 0; g0 < len; g0 += kStage) {
