@@ -2949,24 +2949,19 @@ __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<N
           const unsigned top = road_words(__float_as_uint(thr));  // no hit at or beyond it
           float b1 = __uint_as_float(top), b2 = b1, b3 = b1;
           int be = -1, be2 = -1;
+          const Arcs arcs = order_arcs(ea, eb, ec, ed);
 #pragma unroll 1
           for (int g0 = 0; g0 < len; g0 += kStage) {
             if (!shortr) stage(g0);
-            // the lower arc first, the other from behind what that visit reads (a hit
-            // visited twice would look like two)
-            const bool swap = ec < ed && ec < ea;
-            const int fa = swap ? ec : ea, fb = swap ? ed : eb;
-            const int ga = max(swap ? ea : ec, fa < fb ? fa + ((fb - fa + 3) & ~3) : 0);
-            const int gb = swap ? eb : ed;
             unsigned k1 = top, k2 = top, k3 = top;
             int num = 0, num1 = 0;
 #pragma unroll 1
             for (int arc = 0; arc < 2; ++arc) {
-              int e = max(arc ? ga : fa, g0) - g0;
-              const int end = min(arc ? gb : fb, g0 + kStage) - g0;
+              int e = stage_first(arc ? arcs.b0 : arcs.a0, g0) - g0;
+              const int end = stage_end(arc ? arcs.b1 : arcs.a1, g0) - g0;
               while (__ballot(e < end)) {
                 if (e < end) {
-                  constexpr int kW = 4;
+                  constexpr int kW = kVisit;
                   float f[kW];
                   float2 v[kW];
 #pragma unroll
@@ -2990,15 +2985,12 @@ __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<N
                   }
                   e += kW;
                 }
-                num += 4;
+                num += kVisit;
               }
               if (arc == 0) num1 = num;
             }
             // this stage's three smallest into the run's
-            auto place = [&](unsigned key) {
-              const int x = (int)(key & kNum);
-              return x < num1 ? max(fa, g0) + x : max(ga, g0) + x - num1;
-            };
+            auto place = [&](unsigned key) { return visit_place(arcs, g0, (int)(key & kNum), num1); };
             auto insert = [&](unsigned key) {
               if (key >= top) return;
               const float f = __uint_as_float(key & ~kNum);

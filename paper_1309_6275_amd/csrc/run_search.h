@@ -13,6 +13,7 @@
 namespace ht {
 
 constexpr int kStage = 256;           // hits of a run staged at a time
+constexpr int kVisit = 4;             // hits of a visit
 // A hit's |f| and the number of its visit share a word, the number in the low
 // bits: two arcs of kStage hits in whole visits.
 constexpr uint32_t kVisitNum = 511u;
@@ -25,6 +26,35 @@ static_assert(2 * kStage <= (int)kVisitNum + 1, "every visited hit of a stage ha
 HT_RUN_FN uint32_t road_words(uint32_t thr_bits) {
   const uint32_t end = (thr_bits | kVisitNum) + 1u;
   return end < 0x7f800000u ? end : 0x7f800000u;
+}
+
+// The two arcs [a0, a1) and [b0, b1) of a lane's road, in order and at least a visit
+// apart, so that no place is read for both (a hit visited twice would look like
+// two, and one skipped for that reason would be lost): closer ones become one,
+// with the hits between, whose visit changes nothing.
+struct Arcs {
+  int a0, a1, b0, b1;
+};
+HT_RUN_FN Arcs order_arcs(int a0, int a1, int b0, int b1) {
+  const bool swap = b0 < b1 && b0 < a0;
+  Arcs v;
+  v.a0 = swap ? b0 : a0;
+  v.a1 = swap ? b1 : a1;
+  v.b0 = swap ? a0 : b0;
+  v.b1 = swap ? a1 : b1;
+  if (v.a0 < v.a1 && v.b0 < v.b1 && v.b0 < v.a1 + kVisit) {
+    v.a1 = v.b1 > v.a1 ? v.b1 : v.a1;
+    v.b0 = v.b1 = 0;
+  }
+  return v;
+}
+// A stage [g0, g0 + kStage) visits an arc from its first place there (a stage's
+// visits start anew) while the place is below its end there.
+HT_RUN_FN int stage_first(int begin, int g0) { return begin > g0 ? begin : g0; }
+HT_RUN_FN int stage_end(int end, int g0) { return end < g0 + kStage ? end : g0 + kStage; }
+// the place of the hit with number x, num1 numbers having gone to the first arc
+HT_RUN_FN int visit_place(const Arcs& v, int g0, int x, int num1) {
+  return x < num1 ? stage_first(v.a0, g0) + x : stage_first(v.b0, g0) + x - num1;
 }
 
 }  // namespace ht

@@ -1,5 +1,5 @@
 """GPU parity of the seed search on the layer runs at its edges: hits at the edge
-of the road.
+of the road, and a second arc behind the end of a stage.
 
 Every result is compared with the oracle as in test_gpu_assoc (bit-exact, the
 refit to rounding)."""
@@ -21,17 +21,22 @@ def event(r, phi, layer):
                            layer=np.concatenate(layer).astype(np.uint8), n_hits=int(r.size))
 
 
-def run_small(torch, ht, grid, ev, cfg, min_votes=8):  # noqa: F811
-    """Vote, peaks and assoc_cluster with a plan of a few thousand peaks; returns the
-    results and the list."""
+def run_small(torch, ht, grid, ev, cfg, min_votes=8, lin=None):  # noqa: F811
+    """Vote, peaks and assoc_cluster with a plan of a few thousand peaks; with lin,
+    assoc_cluster on those cells instead.  Returns the results and the list."""
     plan = ht.Plan(grid, max_hits=8192, max_peaks=4096, max_member_cap=1024, max_tracks=4096)
     d = lambda a: torch.from_numpy(a).cuda()
     r, phi, layer = d(ev.r), d(ev.phi), d(ev.layer)
     peaks = torch.full((4096, 2), -1, dtype=torch.int32, device="cuda")
     nf = torch.zeros(1, dtype=torch.int32, device="cuda")
-    acc = torch.empty(plan.acc_shape, dtype=torch.int32, device="cuda")
-    ht.hough_vote(plan, r, phi, acc)
-    ht.hough_peaks(plan, acc, min_votes, peaks, nf)
+    if lin is None:
+        acc = torch.empty(plan.acc_shape, dtype=torch.int32, device="cuda")
+        ht.hough_vote(plan, r, phi, acc)
+        ht.hough_peaks(plan, acc, min_votes, peaks, nf)
+    else:
+        peaks[:len(lin), 0] = d(np.asarray(lin, np.int32))
+        peaks[:, 1] = 0
+        nf += len(lin)
     bufs = ht.ClusterBuffers(ev.n_hits, 4096, 512, 1 << 15, cfg["n_rho"], cfg["n_theta"])
     ht.assoc_cluster(plan, r, phi, layer, peaks, nf, cfg, bufs, with_vacc=True)
     torch.cuda.synchronize()
@@ -64,3 +69,35 @@ def test_runs_hits_at_the_roads_edge(torch, ht, oracle, part):  # noqa: F811
         want = run_oracle(oracle, grid, ev, None, pk, cfg)
         compare(got, want, f"road {road!r}")
         assert np.sum(want["tracks"]["n_inliers"] == 10) >= n // 2
+
+
+@pytest.mark.parametrize("before", [249, 250, 251, 252, 253, 254, 255, 509])
+def test_runs_second_arc_behind_a_stage(torch, ht, oracle, before):  # noqa: F811
+    """A straight track crosses the innermost circle twice; both crossings are inside
+    its member window.  `before` hits of that layer lie in front of the first
+    crossing, a few just off the road at it, across a stage's end, and one on the
+    road at the second, with nothing between."""
+    d0, road, r0 = 3.45, 0.1, 4.0
+    radii = np.float32(G.RADII)
+    grid = dict(CF.GRID_3D, n_phi=64, n_qpt=33, n_d0=4, d0_lo=-4.6, d0_hi=4.6)
+    cfg = dict(CF.CLUSTER_3D, member_cap=1024, win_bins=3, road_sigmas=5.0, sigma_rphi=road / 5.0)
+    for k in (1, 2, 3, 5, 6, 7, 9):
+        rng = np.random.default_rng(100 * before + k)
+        axis = rng.uniform(-2.0, 1.5)  # direction of the point nearest the beam line
+        line = axis - np.arccos(d0 / radii[1:].astype(np.float64))
+        a0 = np.arccos(d0 / r0)
+        # off the road by a third to nine tenths of an azimuth bucket
+        edge = -np.arccos((d0 - road) / r0) - rng.uniform(0.3, 0.9, k) * 2 * np.pi / 2048
+        assert np.all(np.abs(r0 * np.cos(edge) - d0) > road)
+        front = -a0 - rng.uniform(0.3, 0.7, before)
+        inner = axis + np.concatenate([front, edge, [a0]])
+        ev = event([np.full(inner.size, r0), radii[1:]], [inner, line],
+                   [np.zeros(inner.size), np.arange(1, 10)])
+        print(f"{before} before, {k} at the edge", flush=True)
+        phi0 = axis - 0.5 * np.pi  # the track's direction, in the middle of the q/pT axis
+        i = int(np.floor((phi0 + np.pi) / (2 * np.pi) * 64)) % 64
+        lin = np.sort([(3 * 33 + j) * 64 + (i + di) % 64 for j in range(12, 21) for di in (-1, 0, 1)])
+        got, pk = run_small(torch, ht, grid, ev, cfg, lin=lin)
+        want = run_oracle(oracle, grid, ev, None, pk, cfg)
+        compare(got, want, f"{before} {k}")
+        assert want["counts"][1] >= 1 and want["tracks"]["n_inliers"].max() == 10

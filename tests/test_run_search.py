@@ -1,5 +1,6 @@
 """The integer arithmetic of the road search on the layer runs (csrc/run_search.h),
-compiled for the CPU: which hits pass the road's bound."""
+compiled for the CPU: which hits pass the road's bound, and which hits of a run the
+lanes visit."""
 import ctypes
 import os
 import subprocess
@@ -13,6 +14,37 @@ SHIM = r"""
 #include "run_search.h"
 extern "C" uint32_t road_words(uint32_t b) { return ht::road_words(b); }
 extern "C" uint32_t visit_num() { return ht::kVisitNum; }
+// The places of a run of len hits that each of n lanes visits for its arcs [arc[0],
+// arc[1]) and [arc[2], arc[3]), as the kernel's loops take them: seen[lane * len +
+// place] counts the visits.  Returns 0, or the line of the check that failed.
+extern "C" int visits(int n, int len, const int* arcs, int* seen) {
+  using namespace ht;
+  for (int g0 = 0; g0 < len; g0 += kStage) {
+    const int ge = len < g0 + kStage ? len : g0 + kStage;
+    int num = 0, num1 = 0;
+    for (int arc = 0; arc < 2; ++arc) {
+      for (bool more = true; more;) {
+        more = false;
+        for (int l = 0; l < n; ++l) {
+          const int* a = arcs + 4 * l;
+          const Arcs v = order_arcs(a[0], a[1], a[2], a[3]);
+          const int e = stage_first(arc ? v.b0 : v.a0, g0) + num - (arc ? num1 : 0);
+          if (e >= stage_end(arc ? v.b1 : v.a1, g0)) continue;
+          more = true;
+          for (int u = 0; u < kVisit; ++u) {
+            if (e < g0 || e + u >= ge + 4) return __LINE__;   // outside the staged hits and the pad
+            if (num + u > (int)kVisitNum) return __LINE__;
+            if (arc == 1 && visit_place(v, g0, num + u, num1) != e + u) return __LINE__;
+            if (e + u < ge) seen[l * len + e + u]++;          // behind: no members
+          }
+        }
+        if (more) num += kVisit;
+      }
+      if (arc == 0) num1 = num;
+    }
+  }
+  return 0;
+}
 """
 
 
@@ -51,3 +83,33 @@ def test_road_words_keep_every_hit_on_the_road(lib):
         end = lib.road_words(bits(t))
         for b in (bits(np.inf), bits(np.nan), 0x7fffffff):
             assert ((b & ~num) | 0) >= end
+
+
+def test_every_place_of_both_arcs_is_visited_once(lib):
+    """Runs below and above a stage, arcs with and without a gap, adjacent ones across
+    the stages' ends among them."""
+    rng = np.random.default_rng(6)
+    for trial in range(4000):
+        n = int(rng.integers(1, 5))
+        len_ = int(rng.choice([rng.integers(1, 257), rng.integers(257, 1400)]))
+        arcs = np.zeros((n, 4), np.int32)
+        for l in range(n):
+            p = np.sort(rng.integers(0, len_ + 1, 4))
+            if rng.random() < 0.5:  # the second arc a few hits behind the first
+                p[2] = min(p[1] + rng.integers(0, 4), len_)
+                p[3] = max(p[2], p[3])
+            if rng.random() < 0.5:
+                p = p[[2, 3, 0, 1]]
+            if rng.random() < 0.1:
+                p[rng.integers(0, 2) * 2 + np.arange(2)] = 0
+            arcs[l] = p
+        seen = np.zeros((n, len_), np.int32)
+        rc = lib.visits(n, len_, arcs.ctypes.data_as(ctypes.c_void_p),
+                        seen.ctypes.data_as(ctypes.c_void_p))
+        assert rc == 0, (rc, len_, arcs)
+        for l in range(n):
+            want = np.zeros(len_, bool)
+            want[arcs[l, 0]:arcs[l, 1]] = True
+            want[arcs[l, 2]:arcs[l, 3]] = True
+            assert np.all(seen[l][want] == 1), (len_, arcs[l])
+            assert seen[l].max() <= 1
