@@ -2448,21 +2448,15 @@ __global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch
       const int sst[3] = {bcasti(R.st, o + Ls[0]), bcasti(R.st, o + Ls[1]), bcasti(R.st, o + Ls[2])};
       const int mst[3] = {bcasti(mend_l, o + Ls[0]) - n0, bcasti(mend_l, o + Ls[1]) - n1,
                           bcasti(mend_l, o + Ls[2]) - n2};
-      // the three seed layers side by side: lane -> (seed layer, member)
-      int s = -1, st = 0, en = 0, q = 0;
-      if (lane < n0) { s = 0; st = mst[0]; en = st + n0; }
-      else if (lane < n0 + n1) { s = 1; st = mst[1]; en = st + n1; q = n0; }
-      else if (lane < n0 + n1 + n2) { s = 2; st = mst[2]; en = st + n2; q = n0 + n1; }
-      const int e = s < 0 ? 0 : st + lane - q;
+      const SeedLane sl = seed_lane(lane, n0, n1, n2, mst[0], mst[1], mst[2]);
+      const int s = sl.s, mine = sl.n;
       const unsigned long long* keys =
           reinterpret_cast<const unsigned long long*>(&S.mem[0]) + 1;  // every other word
-      const unsigned long long key = keys[2 * e];
+      const unsigned long long key = keys[2 * sl.e];
       // (the coordinates' load runs beside the ranking)
-      const int se = s == 0 ? sst[0] : (s == 1 ? sst[1] : sst[2]);
-      const double2 xy = A.sxy[se + (int)((unsigned)key & 0xffffu)];
+      const double2 xy = A.sxy[seed_record(s, sst[0], sst[1], sst[2], (uint32_t)key)];
       const int nmax = max(n0, max(n1, n2));
-      const int mine = en - st;
-      const unsigned long long* from = keys + 2 * st;
+      const unsigned long long* from = keys + 2 * sl.st;
       int rank = 0;
       // every lane reads every round; rounds past the lane's own layer read what
       // lies behind (at most 64 records past the list) and do not count

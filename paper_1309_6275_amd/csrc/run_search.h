@@ -28,6 +28,31 @@ HT_RUN_FN uint32_t road_words(uint32_t thr_bits) {
   return end < 0x7f800000u ? end : 0x7f800000u;
 }
 
+// The three seed layers' listed members side by side over the lanes: the lane's
+// seed layer s, the layer's first entry and entry count in the list, and the lane's
+// entry.  A lane without one (s = -1, no entries) takes the first entry of layer 2,
+// so that its entry's place is one of the run that it is looked up in.
+struct SeedLane {
+  int s, st, n, e;
+};
+HT_RUN_FN SeedLane seed_lane(int lane, int n0, int n1, int n2, int st0, int st1, int st2) {
+  SeedLane v;
+  int q = lane;
+  v.s = -1;
+  v.st = st2;
+  v.n = 0;
+  if (lane < n0) { v.s = 0; v.st = st0; v.n = n0; q = 0; }
+  else if (lane < n0 + n1) { v.s = 1; v.st = st1; v.n = n1; q = n0; }
+  else if (lane < n0 + n1 + n2) { v.s = 2; v.n = n2; q = n0 + n1; }
+  v.e = v.st + lane - q;
+  return v;
+}
+// the record of an entry of seed layer s (-1: of layer 2) whose place in the layer's
+// run is the low half of hp; the runs begin at r0, r1 and r2
+HT_RUN_FN int seed_record(int s, int r0, int r1, int r2, uint32_t hp) {
+  return (s == 0 ? r0 : (s == 1 ? r1 : r2)) + (int)(hp & 0xffffu);
+}
+
 // The two arcs [a0, a1) and [b0, b1) of a lane's road, in order and at least a visit
 // apart, so that no place is read for both (a hit visited twice would look like
 // two, and one skipped for that reason would be lost): closer ones become one,

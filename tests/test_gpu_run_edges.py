@@ -1,5 +1,6 @@
 """GPU parity of the seed search on the layer runs at its edges: hits at the edge
-of the road, and a second arc behind the end of a stage.
+of the road, a second arc behind the end of a stage, and an event that fills its
+plan with a thin outermost layer.
 
 Every result is compared with the oracle as in test_gpu_assoc (bit-exact, the
 refit to rounding)."""
@@ -101,3 +102,31 @@ def test_runs_second_arc_behind_a_stage(torch, ht, oracle, before):  # noqa: F81
         want = run_oracle(oracle, grid, ev, None, pk, cfg)
         compare(got, want, f"{before} {k}")
         assert want["counts"][1] >= 1 and want["tracks"]["n_inliers"].max() == 10
+
+
+def test_reject_event_fills_the_plan(torch, ht, oracle):  # noqa: F811
+    """As many hits as the plan holds, the last layer a handful of them, and enough
+    candidates for the float32 rejection: the lanes without a seed read within the
+    stored hits."""
+    W = CF.WORKLOADS[2]
+    grid, cfg = W["grid"], W["cluster"]
+    src = G.make_event(2, W["seed0"] + 71, n_prompt=120, n_noise=240)
+    line = np.flatnonzero(src.layer == 9)[:4]
+    ev = event([src.r, np.full(4, 100.0)], [src.phi, src.phi[line]], [src.layer, np.full(4, 15)])
+    n = ev.n_hits
+    plan = ht.Plan(grid, max_hits=n, max_peaks=1 << 17, max_member_cap=128, max_tracks=4096)
+    d = lambda a: torch.from_numpy(a).cuda()
+    r, phi, layer = d(ev.r), d(ev.phi), d(ev.layer)
+    acc = torch.empty(plan.acc_shape, dtype=torch.int32, device="cuda")
+    peaks = torch.full((1 << 17, 2), -1, dtype=torch.int32, device="cuda")
+    nf = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ht.hough_vote(plan, r, phi, acc)
+    ht.hough_peaks(plan, acc, W["min_votes"], peaks, nf)
+    bufs = ht.ClusterBuffers(n, 4096, 512, 1 << 15, cfg["n_rho"], cfg["n_theta"])
+    ht.assoc_cluster(plan, r, phi, layer, peaks, nf, cfg, bufs, with_vacc=True)
+    torch.cuda.synchronize()
+    np_ = int(nf.item())
+    assert 12288 <= np_ <= 1 << 17
+    want = run_oracle(oracle, grid, ev, None, peaks[:np_].cpu().numpy(), cfg)
+    compare(bufs.to_host(n), want, "full plan")
+    assert np.any(want["tracks"]["n_layers"] == 11)  # the thin layer is an outermost seed layer

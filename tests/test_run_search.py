@@ -1,6 +1,6 @@
 """The integer arithmetic of the road search on the layer runs (csrc/run_search.h),
-compiled for the CPU: which hits pass the road's bound, and which hits of a run the
-lanes visit."""
+compiled for the CPU: which hits pass the road's bound, which hits of a run the
+lanes visit, and where the seeds are read."""
 import ctypes
 import os
 import subprocess
@@ -13,6 +13,13 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = r"""
 #include "run_search.h"
 extern "C" uint32_t road_words(uint32_t b) { return ht::road_words(b); }
+extern "C" void seed_lane(int lane, const int* n, const int* st, int* out) {
+  const ht::SeedLane v = ht::seed_lane(lane, n[0], n[1], n[2], st[0], st[1], st[2]);
+  out[0] = v.s; out[1] = v.st; out[2] = v.n; out[3] = v.e;
+}
+extern "C" int seed_record(int s, const int* run, uint32_t hp) {
+  return ht::seed_record(s, run[0], run[1], run[2], hp);
+}
 extern "C" uint32_t visit_num() { return ht::kVisitNum; }
 // The places of a run of len hits that each of n lanes visits for its arcs [arc[0],
 // arc[1]) and [arc[2], arc[3]), as the kernel's loops take them: seen[lane * len +
@@ -113,3 +120,41 @@ def test_every_place_of_both_arcs_is_visited_once(lib):
             want[arcs[l, 2]:arcs[l, 3]] = True
             assert np.all(seen[l][want] == 1), (len_, arcs[l])
             assert seen[l].max() <= 1
+
+
+def test_seed_records_lie_in_their_runs(lib):
+    """A list of members (each a place in its layer's run) and its three seed layers,
+    whose runs lie anywhere in the stored records: every lane, with a seed member or
+    without one, reads a record of a seed layer's run."""
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    rng = np.random.default_rng(8)
+    for _ in range(200):
+        layers = int(rng.integers(3, 17))
+        lens = rng.integers(1, 40, layers)          # run lengths
+        lens[rng.random(layers) < 0.4] = 1
+        n = np.minimum(rng.integers(1, 15, layers), lens)  # members
+        place = [np.sort(rng.choice(lens[l], n[l], replace=False)) for l in range(layers)]
+        first = np.cumsum(n) - n
+        hp = np.concatenate(place)
+        seeds = np.sort(rng.choice(layers, 3, replace=False))
+        if rng.random() < 0.2:
+            seeds[1] = seeds[0]
+        run = np.int32(rng.integers(0, 1000, layers))
+        ns, st, rs = (np.int32(a[seeds]) for a in (n, first, run))
+        if ns.sum() > 64:
+            continue
+        seen = []
+        for lane in range(64):
+            out = np.zeros(4, np.int32)
+            lib.seed_lane(lane, p(ns), p(st), p(out))
+            s, l_st, l_n, e = (int(v) for v in out)
+            word = int(rng.integers(0, 65536)) << 16 | int(hp[e])
+            rec = lib.seed_record(s, p(rs), ctypes.c_uint32(word))
+            L = seeds[s if s >= 0 else 2]
+            assert run[L] <= rec < run[L] + lens[L], (lane, s)
+            if s >= 0:
+                assert rec == run[L] + place[L][e - first[L]] and (l_st, l_n) == (first[L], n[L])
+                seen.append((s, e))
+            else:
+                assert l_n == 0 and 0 <= l_st <= hp.size
+        assert len(set(seen)) == len(seen) == ns.sum()
