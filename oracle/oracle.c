@@ -590,6 +590,8 @@ static void refine(const or_grid* g, const tables* tb, const window_t* wd, const
   out->n_layers = 0;
   out->n_inliers = 0;
   out->ss = 0.0;
+  out->n_members = 0;
+  out->n_tests = 0;
   for (int L = 0; L < OR_MAX_LAYERS; ++L) out->hit[L] = -1;
   /* a cell index outside the grid is not a candidate */
   if (lin < 0 || (int64_t)lin >= (int64_t)np * nq * g->n_d0) return;
@@ -598,8 +600,6 @@ static void refine(const or_grid* g, const tables* tb, const window_t* wd, const
   float half_n = 0.5f * (float)np;
   float wbase = 0.5f + (float)cfg->win_bins;
   int nm = 0;
-  out->n_members = 0;
-  out->n_tests = 0;
   out->status = 1;
   out->n_layers = 0;
   out->n_inliers = 0;
