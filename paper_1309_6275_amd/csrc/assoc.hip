@@ -280,6 +280,7 @@ struct AssocArgs {
   ht_cluster_cfg cfg;
   // scratch
   int32_t* mcount;
+  int32_t* tile_rng;   // sweep: first and one past the last list entry of each column tile
   // member_cap slots per candidate: hit | layer << 16, |x - cell centre| bits
   uint2* pool;
   int32_t* cstat;
@@ -383,6 +384,29 @@ __device__ __forceinline__ void prep_clear(const AssocArgs& A, int surv_groups, 
   for (int64_t v = t0; v < ncell_v; v += step) A.vacc[v] = 0;
 }
 
+// ---- the sweep's list ranges: a workgroup of the sweep owns the peaks of a tile of 64
+// columns of one d0 plane, one stretch of the (cell-ordered) list.  Entries
+// outside the grid may stand anywhere in it.
+__device__ __forceinline__ int col_tiles_of(const AssocArgs& A) { return (A.n_qpt + kWave - 1) / kWave; }
+__device__ __forceinline__ int tile_of(const AssocArgs& A, int p) {
+  const int lin = A.peaks[p].lin;
+  if (lin < 0 || lin >= A.n_cells) return -1;
+  const int col = lin / A.n_phi, k = col / A.n_qpt;
+  return k * col_tiles_of(A) + (col - k * A.n_qpt) / kWave;
+}
+__device__ __forceinline__ void clear_tiles(const AssocArgs& A, int64_t t0, int64_t step) {
+  const int64_t n = 2 * (int64_t)col_tiles_of(A) * A.n_d0;
+  for (int64_t t = t0; t < n; t += step) A.tile_rng[t] = t & 1 ? 0 : 0x7fffffff;
+}
+// entry p's part of them, and its member count cleared
+__device__ __forceinline__ void mark_entry(const AssocArgs& A, int p, int np) {
+  A.mcount[p] = 0;
+  const int t = tile_of(A, p);
+  if (t < 0) return;
+  if (p == 0 || tile_of(A, p - 1) != t) atomicMin(&A.tile_rng[2 * t], p);
+  if (p + 1 == np || tile_of(A, p + 1) != t) atomicMax(&A.tile_rng[2 * t + 1], p + 1);
+}
+
 template <int NB>
 __global__ void init_kernel(AssocBatch<NB> AB, int surv_groups) {
   const AssocArgs& A = event_args(AB);
@@ -392,6 +416,7 @@ __global__ void init_kernel(AssocBatch<NB> AB, int surv_groups) {
   if (tid < 16) A.sc[tid] = tid == S_NP ? peaks_of(A) : 0;
   if (tid < 3 * HT_MAX_LAYERS) A.lay[tid] = tid < HT_MAX_LAYERS ? 0x7fffffff : 0;
   for (int64_t w = tid; w < kBucketKeys; w += stride) A.bkt[w] = 0;
+  clear_tiles(A, tid, stride);
   const int n_hits = hits_of(A);
   for (int64_t h = tid; h < n_hits; h += stride) {
     double x, y, q;
@@ -550,14 +575,14 @@ __device__ __forceinline__ void put_records(const AssocArgs& A, int h, int e, in
 }
 
 // the hits' records in bucket order, both copies; events that take the sweep get
-// their member counts cleared instead
+// their member counts cleared and their list ranges marked instead
 template <int NB>
 __global__ __launch_bounds__(256) void bscatter_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
   if (A.sc[S_MODE] == 0) {
     const int np = n_cands(A);
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < np; q += gridDim.x * blockDim.x)
-      A.mcount[q] = 0;
+      mark_entry(A, q, np);
     return;
   }
   const int n = hits_of(A);
@@ -637,8 +662,11 @@ __global__ __launch_bounds__(kPrepThreads) void prep_small_kernel(AssocBatch<NB>
   if (tid < 16)
     A.sc[tid] = tid == S_NP ? peaks_of(A) : (tid == S_MODE ? (on ? 1 : 0) : (tid == S_NBAD ? nbad : 0));
   if (!on) {
+    clear_tiles(A, tid, kPrepThreads);
+    __threadfence();
+    __syncthreads();
     const int np = peaks_of(A);
-    for (int p = tid; p < np; p += kPrepThreads) A.mcount[p] = 0;
+    for (int p = tid; p < np; p += kPrepThreads) mark_entry(A, p, np);
     return;
   }
   // one wave per layer: its row of bucket starts, 128 buckets at a time
@@ -681,10 +709,13 @@ __global__ __launch_bounds__(kPrepThreads) void prep_small_kernel(AssocBatch<NB>
 // ---- member sweep -----------------------------------------------------------
 // LDS per column: the column's peak bits (starting at bit i = 0) and the
 // number of peaks before each 32-bit word.  The workgroup owns the peaks of
-// its 64 columns, which are consecutive in the (cell-ordered) peak list, so
+// its 64 columns, a stretch of the (cell-ordered) peak list, so
 // it counts their members with LDS atomics and writes each member straight
 // into its candidate's member_cap slots of the pool: one sweep, and the
-// workgroup's member lists form one contiguous region of the pool.
+// workgroup's member lists form one contiguous region of the pool.  A peak's
+// rank among the workgroup's is its place in the stretch; where entries outside
+// the grid stand between them the place of each rank is kept in memory (the
+// candidates' layer counts, which the seed search writes later).
 constexpr int kMaxPhiWords = 32;  // n_phi <= 1024
 constexpr int kMaxWgPeaks = 4096; // LDS counters; more peaks fall back to global counters
 constexpr int kQueue = 2 * kWave; // per-wave queue of (hit, column) pairs with a peak in reach
@@ -707,6 +738,7 @@ struct SweepShared {
   uint32_t qbits[kSweepWaves][kQueue];
   uint32_t qmeta[kSweepWaves][kQueue];
   int32_t np_wg, p_lo;
+  int32_t dense;  // whether every entry of the stretch is a peak of these columns
   // per (distinct hit radius, column): arcsine (NaN when |u| > 1), u, and
   // the upper bound of the member window
   RadiusSet R;
@@ -727,6 +759,11 @@ struct SweepShared {
 // only means one more member test of a candidate that is dropped anyway.
 __device__ __forceinline__ uint32_t live_bits(SweepShared& S, int cl, int w) {
   return __hip_atomic_load(&S.lbits[cl][w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// the place in the workgroup's stretch of its peak of a rank
+__device__ __forceinline__ int sweep_place(const AssocArgs& A, const SweepShared& S, int rank) {
+  return S.dense ? rank : A.cnl[S.p_lo + rank];
 }
 
 template <typename F>
@@ -785,7 +822,7 @@ __device__ __forceinline__ void sweep_members(const AssocArgs& A, SweepShared& S
         if (!(adx <= w)) continue;
         const int wi = ic >> 5;
         const uint32_t below = S.cbits[cl][wi] & ((1u << (ic & 31)) - 1u);
-        const int q = S.cfirst[cl] + S.cpre[cl][wi] + __popc(below);
+        const int q = sweep_place(A, S, S.cfirst[cl] + S.cpre[cl][wi] + __popc(below));
         if (q < 0 || q >= np_wg) continue;  // only for peak lists not sorted by cell
         if (fn(q, hh, adx)) atomicAnd(&S.lbits[cl][wi], ~(1u << (ic & 31)));
       }
@@ -898,7 +935,7 @@ __device__ __forceinline__ void sweep_members(const AssocArgs& A, SweepShared& S
             const float adx = cell_adx(x, ic, n_phi);
             if (!(adx <= w)) continue;
             const uint32_t below = S.cbits[lane][wi] & ((1u << (bit + b)) - 1u);
-            const int q = cfirst + S.cpre[lane][wi] + __popc(below);
+            const int q = sweep_place(A, S, cfirst + S.cpre[lane][wi] + __popc(below));
             if (q < 0 || q >= np_wg) continue;  // only for peak lists not sorted by cell
             if (fn(q, hh, adx)) atomicAnd(&S.lbits[lane][wi], ~(1u << (ic & 31)));
           }
@@ -946,7 +983,7 @@ __device__ void drop_overfull(const AssocArgs& A, SweepShared& S, int k, int j0,
         ii = ii < 0 ? ii + n_phi : (ii >= n_phi ? ii - n_phi : ii);
         sum += row[ii];
       }
-      const int q = q0 + rank;
+      const int q = sweep_place(A, S, q0 + rank);
       ++rank;
       if (sum <= lim || q < 0 || q >= np_wg) continue;
       atomicAnd(&S.lbits[cl][w], ~(1u << bit));
@@ -977,26 +1014,15 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
   const int nwords = (n_phi + 31) >> 5;
   const int cap = A.cfg.member_cap;
   // the workgroup's peaks: its columns' cells are consecutive, so in a list in
-  // cell order they are the entries p_lo .. p_lo + np_wg - 1 (any other list leaves
-  // some of them out)
+  // cell order they are among the entries p_lo .. p_lo + np_wg - 1 with nothing but
+  // entries outside the grid between (any other list leaves some of them out)
   const int n_cols = min(kWave, A.n_qpt - j0);
   const int64_t lin0 = ((int64_t)k * A.n_qpt + j0) * n_phi, lin1 = lin0 + (int64_t)n_cols * n_phi;
   for (int e = threadIdx.x; e < kWave * nwords; e += kSweepThreads) S.cbits[e / nwords][e % nwords] = 0u;
-  if (threadIdx.x < 2) {
-    const int64_t want = threadIdx.x ? lin1 : lin0;
-    int a = 0, b = n_cands(A);  // the first entry at or beyond the cell
-    while (a < b) {
-      const int m = a + (b - a) / 2;
-      if (A.peaks[m].lin < want) a = m + 1;
-      else b = m;
-    }
-    if (threadIdx.x) S.np_wg = a;
-    else S.p_lo = a;
-  }
-  __syncthreads();
-  const int p_lo = S.p_lo;
-  const int np_wg = S.np_wg - p_lo;
+  const int32_t* rng = A.tile_rng + 2 * ((int64_t)k * gridDim.x + blockIdx.x);
+  const int p_lo = rng[0], np_wg = rng[1] - p_lo;
   if (np_wg <= 0) return;
+  __syncthreads();
   for (int q = threadIdx.x; q < np_wg; q += kSweepThreads) {
     const int64_t c = (int64_t)A.peaks[p_lo + q].lin - lin0;
     if (c < 0 || c >= lin1 - lin0) continue;
@@ -1013,10 +1039,26 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
       s += __popc(S.cbits[threadIdx.x][w]);
     }
     S.ccnt[threadIdx.x] = s;
-    S.cfirst[threadIdx.x] = wave_incl_scan_i32(s, threadIdx.x) - s;
-    if (threadIdx.x == 0) S.np_wg = np_wg;
+    const int incl = wave_incl_scan_i32(s, threadIdx.x);
+    S.cfirst[threadIdx.x] = incl - s;
+    if (threadIdx.x == kWave - 1) {
+      S.np_wg = np_wg;
+      S.p_lo = p_lo;
+      S.dense = incl == np_wg;
+    }
   }
   __syncthreads();
+  if (!S.dense) {
+    for (int q = threadIdx.x; q < np_wg; q += kSweepThreads) {
+      const int64_t c = (int64_t)A.peaks[p_lo + q].lin - lin0;
+      if (c < 0 || c >= lin1 - lin0) continue;
+      const int cl = (int)c / n_phi, ic = (int)c - cl * n_phi, w = ic >> 5;
+      const uint32_t below = S.cbits[cl][w] & ((1u << (ic & 31)) - 1u);
+      A.cnl[p_lo + S.cfirst[cl] + S.cpre[cl][w] + __popc(below)] = q;
+    }
+    __threadfence_block();
+    __syncthreads();
+  }
   uint2* pool = A.pool + (size_t)p_lo * cap;
   const bool lds_cnt = n_slices == 1 && np_wg <= kMaxWgPeaks;
   if (lds_cnt) {
@@ -3940,6 +3982,7 @@ AssocArgs make_args(const Plan& P, const float* r, const float* phi, const uint8
   A.peak_cap = peak_cap;
   A.cfg = cfg;
   A.mcount = P.d_mcount;
+  A.tile_rng = P.d_tile_rng;
   A.pool = P.d_mem;
   A.cstat = P.d_cstat;
   A.cnl = P.d_cnl;
