@@ -62,7 +62,7 @@ int dalloc(Plan* plan, T** p, size_t n) {
 
 void free_plan(Plan* p) {
   void* ptrs[] = {p->d_kap,       p->d_kapc,      p->d_d0c,       p->d_q,         p->d_t,        p->d_bits,      p->d_tile_cnt,
-                  p->d_tile_off,  p->d_tile_rng,  p->d_hx,       p->d_hy,
+                  p->d_tile_off,  p->d_hx,       p->d_hy,
                   p->d_hq,        p->d_hitB,      p->d_mcount,    p->d_mem,      p->d_cstat,
                   p->d_cgeo,      p->d_chit,      p->d_cnl,      p->d_owner_key, p->d_ctile_cnt,
                   p->d_ctile_off, p->d_trk_peak,  p->d_arc0,     p->d_arcn,     p->d_arci0,    p->d_arcin,      p->d_tunit,      p->d_vacc,
@@ -164,7 +164,6 @@ int ht_plan_create(const ht_grid* grid, const ht_limits* lim, ht_plan** out) {
   if (rc == HT_OK) rc = dalloc(p, &p->d_bits, (size_t)((p->n_tiles + 3) / 4) * 32 + 2);
   if (rc == HT_OK) rc = dalloc(p, &p->d_tile_cnt, (size_t)p->n_tiles);
   if (rc == HT_OK) rc = dalloc(p, &p->d_tile_off, (size_t)p->n_tiles);
-  if (rc == HT_OK) rc = dalloc(p, &p->d_tile_rng, (size_t)2 * g.n_d0 * ((g.n_qpt + 63) / 64));
   if (rc == HT_OK) rc = dalloc(p, &p->d_hx, nh);
   if (rc == HT_OK) rc = dalloc(p, &p->d_hy, nh);
   if (rc == HT_OK) rc = dalloc(p, &p->d_hq, nh);

@@ -280,7 +280,6 @@ struct AssocArgs {
   ht_cluster_cfg cfg;
   // scratch
   int32_t* mcount;
-  int32_t* tile_rng;   // sweep: first and one past the last list entry of each column tile
   // member_cap slots per candidate: hit | layer << 16, |x - cell centre| bits
   uint2* pool;
   int32_t* cstat;
@@ -384,29 +383,6 @@ __device__ __forceinline__ void prep_clear(const AssocArgs& A, int surv_groups, 
   for (int64_t v = t0; v < ncell_v; v += step) A.vacc[v] = 0;
 }
 
-// ---- the sweep's list ranges: a workgroup of the sweep owns the peaks of a tile of 64
-// columns of one d0 plane, one stretch of the (cell-ordered) list.  Entries
-// outside the grid may stand anywhere in it.
-__device__ __forceinline__ int col_tiles_of(const AssocArgs& A) { return (A.n_qpt + kWave - 1) / kWave; }
-__device__ __forceinline__ int tile_of(const AssocArgs& A, int p) {
-  const int lin = A.peaks[p].lin;
-  if (lin < 0 || lin >= A.n_cells) return -1;
-  const int col = lin / A.n_phi, k = col / A.n_qpt;
-  return k * col_tiles_of(A) + (col - k * A.n_qpt) / kWave;
-}
-__device__ __forceinline__ void clear_tiles(const AssocArgs& A, int64_t t0, int64_t step) {
-  const int64_t n = 2 * (int64_t)col_tiles_of(A) * A.n_d0;
-  for (int64_t t = t0; t < n; t += step) A.tile_rng[t] = t & 1 ? 0 : 0x7fffffff;
-}
-// entry p's part of them, and its member count cleared
-__device__ __forceinline__ void mark_entry(const AssocArgs& A, int p, int np) {
-  A.mcount[p] = 0;
-  const int t = tile_of(A, p);
-  if (t < 0) return;
-  if (p == 0 || tile_of(A, p - 1) != t) atomicMin(&A.tile_rng[2 * t], p);
-  if (p + 1 == np || tile_of(A, p + 1) != t) atomicMax(&A.tile_rng[2 * t + 1], p + 1);
-}
-
 template <int NB>
 __global__ void init_kernel(AssocBatch<NB> AB, int surv_groups) {
   const AssocArgs& A = event_args(AB);
@@ -416,7 +392,6 @@ __global__ void init_kernel(AssocBatch<NB> AB, int surv_groups) {
   if (tid < 16) A.sc[tid] = tid == S_NP ? peaks_of(A) : 0;
   if (tid < 3 * HT_MAX_LAYERS) A.lay[tid] = tid < HT_MAX_LAYERS ? 0x7fffffff : 0;
   for (int64_t w = tid; w < kBucketKeys; w += stride) A.bkt[w] = 0;
-  clear_tiles(A, tid, stride);
   const int n_hits = hits_of(A);
   for (int64_t h = tid; h < n_hits; h += stride) {
     double x, y, q;
@@ -575,14 +550,14 @@ __device__ __forceinline__ void put_records(const AssocArgs& A, int h, int e, in
 }
 
 // the hits' records in bucket order, both copies; events that take the sweep get
-// their member counts cleared and their list ranges marked instead
+// their member counts cleared instead
 template <int NB>
 __global__ __launch_bounds__(256) void bscatter_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
   if (A.sc[S_MODE] == 0) {
     const int np = n_cands(A);
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < np; q += gridDim.x * blockDim.x)
-      mark_entry(A, q, np);
+      A.mcount[q] = 0;
     return;
   }
   const int n = hits_of(A);
@@ -662,11 +637,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_small_kernel(AssocBatch<NB>
   if (tid < 16)
     A.sc[tid] = tid == S_NP ? peaks_of(A) : (tid == S_MODE ? (on ? 1 : 0) : (tid == S_NBAD ? nbad : 0));
   if (!on) {
-    clear_tiles(A, tid, kPrepThreads);
-    __threadfence();
-    __syncthreads();
     const int np = peaks_of(A);
-    for (int p = tid; p < np; p += kPrepThreads) mark_entry(A, p, np);
+    for (int p = tid; p < np; p += kPrepThreads) A.mcount[p] = 0;
     return;
   }
   // one wave per layer: its row of bucket starts, 128 buckets at a time
@@ -737,7 +709,8 @@ struct SweepShared {
   float qe[kSweepWaves][kQueue];
   uint32_t qbits[kSweepWaves][kQueue];
   uint32_t qmeta[kSweepWaves][kQueue];
-  int32_t np_wg, p_lo;
+  int32_t np_wg, p_lo, p_hi;
+  int32_t s_lo, s_hi;  // while the stretch is looked for: it lies between these entries
   int32_t dense;  // whether every entry of the stretch is a peak of these columns
   // per (distinct hit radius, column): arcsine (NaN when |u| > 1), u, and
   // the upper bound of the member window
@@ -995,6 +968,47 @@ __device__ void drop_overfull(const AssocArgs& A, SweepShared& S, int k, int j0,
   }
 }
 
+// The stretch [p_lo, p_hi) of the (cell-ordered) list that holds the cells lin0 ..
+// lin1 - 1; entries outside the grid may stand anywhere in it.  The workgroup reads
+// one entry per thread, spread over the list, and then every entry between the
+// last one before lin0 and the first one from lin1 on: two rounds of loads (a binary
+// search by one thread takes 18, and an entry outside the grid misleads it).
+// p_lo > p_hi when there is none.  Whole workgroup; ends with a barrier.
+__device__ __forceinline__ void find_stretch(const AssocArgs& A, SweepShared& S, int64_t lin0,
+                                             int64_t lin1) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int np = n_cands(A);
+  if (threadIdx.x == 0) {
+    S.s_lo = -1;
+    S.s_hi = np;
+    S.p_lo = 0x7fffffff;
+    S.p_hi = 0;
+  }
+  __syncthreads();
+  const int step = (np + kSweepThreads - 1) / kSweepThreads;
+  {
+    const int p = (int)threadIdx.x * step;
+    const int64_t lin = p < np ? (int64_t)A.peaks[p].lin : -1;
+    const bool ok = lin >= 0 && lin < A.n_cells;
+    const uint64_t lo = __ballot(ok && lin < lin0), hi = __ballot(ok && lin >= lin1);
+    const int p0 = bcasti(p, 0);
+    if (lane == 0 && lo) atomicMax(&S.s_lo, p0 + (63 - __builtin_clzll(lo)) * step);
+    if (lane == 0 && hi) atomicMin(&S.s_hi, p0 + __builtin_ctzll(hi) * step);
+  }
+  __syncthreads();
+  const int end = S.s_hi;
+  for (int b = S.s_lo + 1 + (int)(threadIdx.x & ~(kWave - 1)); b < end; b += kSweepThreads) {
+    const int p = b + lane;
+    const int64_t lin = p < end ? (int64_t)A.peaks[p].lin : -1;
+    const uint64_t in = __ballot(lin >= lin0 && lin < lin1);
+    if (lane == 0 && in) {
+      atomicMin(&S.p_lo, b + __builtin_ctzll(in));
+      atomicMax(&S.p_hi, b + 64 - __builtin_clzll(in));
+    }
+  }
+  __syncthreads();
+}
+
 template <int NB>
 __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB) {
   __shared__ SweepShared S;
@@ -1019,10 +1033,9 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
   const int n_cols = min(kWave, A.n_qpt - j0);
   const int64_t lin0 = ((int64_t)k * A.n_qpt + j0) * n_phi, lin1 = lin0 + (int64_t)n_cols * n_phi;
   for (int e = threadIdx.x; e < kWave * nwords; e += kSweepThreads) S.cbits[e / nwords][e % nwords] = 0u;
-  const int32_t* rng = A.tile_rng + 2 * ((int64_t)k * gridDim.x + blockIdx.x);
-  const int p_lo = rng[0], np_wg = rng[1] - p_lo;
+  find_stretch(A, S, lin0, lin1);
+  const int p_lo = S.p_lo, np_wg = S.p_hi - p_lo;
   if (np_wg <= 0) return;
-  __syncthreads();
   for (int q = threadIdx.x; q < np_wg; q += kSweepThreads) {
     const int64_t c = (int64_t)A.peaks[p_lo + q].lin - lin0;
     if (c < 0 || c >= lin1 - lin0) continue;
@@ -1043,7 +1056,6 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
     S.cfirst[threadIdx.x] = incl - s;
     if (threadIdx.x == kWave - 1) {
       S.np_wg = np_wg;
-      S.p_lo = p_lo;
       S.dense = incl == np_wg;
     }
   }
@@ -3982,7 +3994,6 @@ AssocArgs make_args(const Plan& P, const float* r, const float* phi, const uint8
   A.peak_cap = peak_cap;
   A.cfg = cfg;
   A.mcount = P.d_mcount;
-  A.tile_rng = P.d_tile_rng;
   A.pool = P.d_mem;
   A.cstat = P.d_cstat;
   A.cnl = P.d_cnl;

@@ -62,7 +62,6 @@ struct Plan {
   int32_t* d_tile_off;   // [n_tiles]
   int32_t n_tiles;
   // refinement scratch
-  int32_t* d_tile_rng;   // [2 n_d0 ceil(n_qpt / 64)] list entries of each column tile (sweep)
   double* d_hx;          // [max_hits] hit x, y, x^2+y^2
   double* d_hy;
   double* d_hq;
