@@ -188,7 +188,7 @@ int ht_plan_create(const ht_grid* grid, const ht_limits* lim, ht_plan** out) {
   if (rc == HT_OK) rc = dalloc(p, &p->d_vtile, (size_t)lim->max_vertex_cells / 1024 + 1);
   if (rc == HT_OK) rc = dalloc(p, &p->d_scalars, 16);
   if (rc == HT_OK) rc = dalloc(p, &p->d_spread, ht::kSpreadWords);
-  if (rc == HT_OK) rc = dalloc(p, &p->d_lay, (size_t)3 * HT_MAX_LAYERS);
+  if (rc == HT_OK) rc = dalloc(p, &p->d_lay, (size_t)6 * HT_MAX_LAYERS);
   if (rc == HT_OK) rc = dalloc(p, &p->d_bkt, (size_t)ht::kBucketKeys);
   if (rc == HT_OK) rc = dalloc(p, &p->d_bkt_off, (size_t)HT_MAX_LAYERS * ht::kRunRow);
   if (rc == HT_OK) rc = dalloc(p, &p->d_hkey, nh);

@@ -11,8 +11,8 @@
 //   runs      each layer's radius range and hit count; the hits grouped by
 //             (layer, azimuth bucket) with a counting sort (bcount, bscan,
 //             bscatter; small events: prep and runs in one launch,
-//             prep_small).  Events with a layer of widely spread radii take the
-//             sweep instead;
+//             prep_small).  Events with a layer of widely spread radii take
+//             member lists instead;
 //   reject,   the seed search on the layer runs, one wave per candidate: member
 //   runs      layers, seed layers, the seed_k nearest members of each seed
 //             layer by rank, then one seed combination per lane (<= 64) tested
@@ -20,9 +20,9 @@
 //             lane wins by (inliers, sum, index) and offers each inlier hit its
 //             64-bit ownership key (atomicMax); totals go to spread counters.
 //             reject_kernel settles the many candidates that fail in float32;
-//   members,  events that take the sweep only: the members of every candidate by
-//   refine    a sweep shaped like the vote (member_kernel), then the seed search
-//             on those lists;
+//   members,  those events only: the members of every candidate from the hits grouped
+//   refine    by (radius, azimuth bucket), or by a sweep shaped like the vote
+//             (member_kernel), then the seed search on those lists;
 //   survive   ordered compaction of the candidates owning >= min_layers
 //             hits into the track list (tile counts and their sums per 64
 //             tiles, then each tile places its survivors);
@@ -53,15 +53,15 @@ constexpr int kSweepWaves = 16;
 constexpr int kSweepThreads = kSweepWaves * kWave;
 constexpr int kMaxMembers = 1024; // largest member_cap (LDS slots per wave in refine)
 constexpr int kGridCap = 8192;    // grid-stride launches use at most this many blocks
-constexpr int kSweepGrid = 4096;  // ... and the seed search behind the member sweep
 
 // S_NBAD: valid hits whose layer is HT_MAX_LAYERS or more (they vote but are no members)
 constexpr float kPiF = 3.14159265358979f;
 constexpr float k2PiF = 6.28318530717959f;
 
-// S_MODE: 1 when the seed search reads the layer runs (see layer_mode)
+// S_MODE: where a candidate's members come from (see "layer runs" below)
 // S_QUEUE: candidates that reject_kernel could not reject, listed in mcount
 enum { S_NP = 0, S_NBAD = 2, S_NTRK = 3, S_NOBJ = 4, S_NMEM = 5, S_MODE = 6, S_QUEUE = 7 };
+enum { MODE_SWEEP = 0, MODE_RUNS = 1, MODE_CLASSES = 2 };
 // The seed search's totals (road tests, refined candidates, candidates over
 // member_cap, (candidate, member) pairs within it) are summed per workgroup
 // and added to kSpread counters in separate 128-byte lines, chosen by
@@ -302,6 +302,7 @@ struct AssocArgs {
   unsigned long long* spread;  // [kSpreadWords] spread counters
   // layer runs
   int32_t* lay;        // smallest and largest radius (float bits) and hits of each layer
+  int32_t* cls;        // the same of each radius class
   int32_t* bkt;        // hits per (layer, bucket)
   int32_t* bkt_off;    // bucket starts
   int32_t* hkey;       // each hit's bucket key | slot << 15, or -1
@@ -309,7 +310,7 @@ struct AssocArgs {
   float4* srad;        // r, 1/r, the window's hit part
   float* sphi;         // azimuth
   double2* sxy;        // x, y
-  double* sq;          // x^2+y^2
+  double* sq;          // x^2+y^2 (classes: hit | layer << 16, in 32 bits)
   // outputs
   ht_cluster_out out;
 };
@@ -421,9 +422,15 @@ __device__ __forceinline__ int wave_incl_scan_i32(int v, int lane) {
 // The member-eligible hits (valid, layer below HT_MAX_LAYERS) are therefore
 // sorted by (layer, azimuth bucket), and one wave per candidate reads what it
 // needs of each layer's run of buckets (runs_kernel): no member lists are
-// written.  Events with a layer whose radii spread over more than a quarter
-// take the sweep (member_kernel, refine_kernel) instead: there a candidate's
-// interval is no longer narrow.
+// written.
+// Where a layer's radii spread over more than a quarter (a layer number for several
+// shells, a hit with another layer's number) a candidate's interval on it is no
+// longer narrow.  If all those hits have at most kMaxRadii distinct radii, they are
+// sorted by (radius class, azimuth bucket) instead, and one wave per candidate
+// writes its member list from the classes' runs (class_lists) for refine_kernel.
+// Events with more radii than that take the sweep (member_kernel).  In us for
+// assoc_cluster, runs / class lists / sweep: 3.6k hits 341 / 462 / 712 (one hit with
+// another layer's number), 16k hits 970 / 1640 / 2540, 55k hits 1800 / 4960 / 8420.
 constexpr float kLayerSpread = 1.25f;
 
 // azimuth in [-pi, pi) (up to rounding) and its bucket, the same function for
@@ -489,50 +496,6 @@ __global__ __launch_bounds__(256) void bcount_kernel(AssocBatch<NB> AB) {
   }
 }
 
-// one workgroup per layer: its row of bucket starts, both copies of its hits
-template <int NB>
-__global__ __launch_bounds__(256) void bscan_kernel(AssocBatch<NB> AB) {
-  const AssocArgs& A = event_args(AB);
-  const bool on = layer_mode(A);
-  if (blockIdx.x == 0 && threadIdx.x == 0) A.sc[S_MODE] = on ? 1 : 0;
-  if (!on) return;
-  __shared__ int32_t wsum[4];
-  constexpr int G = kBuckets / 256;  // buckets per thread
-  static_assert(G % 4 == 0, "whole 16-byte vectors per thread");
-  const int L = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int base = 0, cnt = 0;
-  for (int l = 0; l <= L; ++l) {
-    base += 2 * cnt;
-    cnt = A.lay[2 * HT_MAX_LAYERS + l];
-  }
-  int32_t c[G];
-  int sum = 0;
-#pragma unroll
-  for (int g = 0; g < G; g += 4) {
-    const int4 v = *reinterpret_cast<const int4*>(A.bkt + L * kBuckets + (int)threadIdx.x * G + g);
-    c[g] = v.x; c[g + 1] = v.y; c[g + 2] = v.z; c[g + 3] = v.w;
-    sum += v.x + v.y + v.z + v.w;
-  }
-  const int incl = wave_incl_scan_i32(sum, lane);
-  if (lane == kWave - 1) wsum[wave] = incl;
-  __syncthreads();
-  int run = base + incl - sum;
-  for (int w = 0; w < wave; ++w) run += wsum[w];
-  int32_t* row = A.bkt_off + L * kRunRow + (int)threadIdx.x * G;
-#pragma unroll
-  for (int g = 0; g < G; g += 4) {
-    int4 o;
-    o.x = run; run += c[g];
-    o.y = run; run += c[g + 1];
-    o.z = run; run += c[g + 2];
-    o.w = run; run += c[g + 3];
-    *reinterpret_cast<int4*>(row + g) = o;
-    o.x += cnt; o.y += cnt; o.z += cnt; o.w += cnt;
-    *reinterpret_cast<int4*>(row + kBuckets + g) = o;
-  }
-  if (threadIdx.x == 255) A.bkt_off[L * kRunRow + 2 * kBuckets] = run + cnt;
-}
-
 // a hit's records at place e of its layer's row, and in the second copy cnt behind
 __device__ __forceinline__ void put_records(const AssocArgs& A, int h, int e, int cnt, double x,
                                             double y, double q, float4 hb) {
@@ -549,12 +512,195 @@ __device__ __forceinline__ void put_records(const AssocArgs& A, int h, int e, in
   }
 }
 
+// inclusive prefix sum within each row of 16 lanes (row_shr with zero fill)
+__device__ __forceinline__ int row_scan_incl(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  return v;
+}
+
+// the same of a radius class: its azimuth and member word, all that its lists take
+__device__ __forceinline__ int32_t* class_words(const AssocArgs& A) {
+  return reinterpret_cast<int32_t*>(A.sq);
+}
+__device__ __forceinline__ void put_class_records(const AssocArgs& A, int h, int e, int cnt, float ph) {
+  int32_t* word = class_words(A);
+  A.sphi[e] = A.sphi[e + cnt] = ph;
+  word[e] = word[e + cnt] = (int)member_word(A, h);
+}
+
+// The distinct radii of the member-eligible hits, in increasing order, while there are
+// at most kMaxRadii of them; a workgroup stops looking once there are more.
+struct ClassSet {
+  uint32_t key[kRadSlots];  // hash of float bits
+  float r[kMaxRadii];       // the classes' radii, infinity behind the last
+  int32_t cnt[2];           // bscan: hits of smaller radii, hits of the class
+  int32_t found;
+};
+__device__ __forceinline__ int class_of(const ClassSet& C, float rv) {
+  int c = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxRadii; ++i) c += C.r[i] < rv ? 1 : 0;
+  return c;
+}
+__device__ __forceinline__ void class_init(ClassSet& C) {
+  if (threadIdx.x < kRadSlots) C.key[threadIdx.x] = kRadEmpty;
+  if (threadIdx.x < 2) C.cnt[threadIdx.x] = 0;
+  if (threadIdx.x == 0) C.found = 0;
+}
+__device__ __forceinline__ int class_found(const ClassSet& C) {
+  return __hip_atomic_load(&C.found, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void class_add(ClassSet& C, float rv) {
+  const uint32_t k = __float_as_uint(rv);
+  uint32_t slot = rad_hash(k);
+  // (found exceeds kMaxRadii long before the slots are full)
+  for (int p = 0; p < kRadSlots && class_found(C) <= kMaxRadii; ++p) {
+    const uint32_t v =
+        __hip_atomic_load(&C.key[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (v == k) return;
+    if (v == kRadEmpty) {
+      const uint32_t old = atomicCAS(&C.key[slot], kRadEmpty, k);
+      if (old == kRadEmpty) atomicAdd(&C.found, 1);
+      if (old == kRadEmpty || old == k) return;
+    }
+    slot = (slot + 1) & (kRadSlots - 1);
+  }
+}
+// Orders the classes once every hit has been added; returns their number (more than
+// kMaxRadii: too many, no order).  Whole workgroup, with barriers.
+__device__ __forceinline__ int class_order(ClassSet& C) {
+  __syncthreads();
+  const int n = C.found;
+  if (n > kMaxRadii) return n;
+  if (threadIdx.x < kMaxRadii) C.r[threadIdx.x] = __builtin_inff();
+  __syncthreads();
+  if (threadIdx.x < kRadSlots) {
+    const uint32_t k = C.key[threadIdx.x];
+    int rank = 0;
+    for (int s = 0; s < kRadSlots; ++s) rank += C.key[s] < k ? 1 : 0;  // positive: ordered bits
+    if (k != kRadEmpty) C.r[rank] = __uint_as_float(k);
+  }
+  __syncthreads();
+  return n;
+}
+static_assert(kMaxRadii == HT_MAX_LAYERS, "a class takes a layer's row");
+
+constexpr int kScanThreads = 1024;
+// The starts of a row's buckets from their counts c0 and c1 (two buckets per thread),
+// both copies, for a row of cnt hits whose records begin at base; returns the starts
+// in c0 and c1.  Whole workgroup.
+__device__ __forceinline__ void put_row(const AssocArgs& A, int L, int base, int cnt, int& c0, int& c1,
+                                        int32_t* wsum) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  static_assert(kBuckets == 2 * kScanThreads, "two buckets per thread");
+  const int sum = c0 + c1;
+  const int incl = wave_incl_scan_i32(sum, lane);
+  if (lane == kWave - 1) wsum[wave] = incl;
+  __syncthreads();
+  int run = base + incl - sum;
+  const int before = row_scan_incl(lane < wave ? wsum[lane & 15] : 0);
+  run += __builtin_amdgcn_readlane(before, 15);
+  c1 = run + c0;
+  c0 = run;
+  int32_t* row = A.bkt_off + L * kRunRow;
+  const int b = 2 * (int)threadIdx.x;
+  *reinterpret_cast<int2*>(row + b) = make_int2(c0, c1);
+  *reinterpret_cast<int2*>(row + kBuckets + b) = make_int2(c0 + cnt, c1 + cnt);
+  if (threadIdx.x == kScanThreads - 1) row[2 * kBuckets] = run + sum + cnt;
+}
+
+// a hit's class, bucket and slot in it (15 classes, 2048 buckets, 65535 hits: 31 bits)
+static_assert(kBuckets == 1 << 11 && kMaxRadii == 1 << 4, "a class key is a positive word");
+__device__ __forceinline__ int class_key(int c, int b, int slot) { return c << 27 | slot << 11 | b; }
+
+// One workgroup per layer: its row of bucket starts, both copies of its hits.  Events
+// by radius class are counted here, a class per workgroup, by two passes over the
+// hits that ordinary events do not pay for; a workgroup rewrites the keys of its own
+// class (the others look at their sign only).
+template <int NB>
+__global__ __launch_bounds__(kScanThreads) void bscan_kernel(AssocBatch<NB> AB) {
+  const AssocArgs& A = event_args(AB);
+  __shared__ int32_t wsum[kScanThreads / kWave];
+  __shared__ ClassSet C;
+  __shared__ int32_t cnt_b[kBuckets];
+  const int L = blockIdx.x, tid = threadIdx.x;
+  if (layer_mode(A)) {
+    if (L == 0 && tid == 0) A.sc[S_MODE] = MODE_RUNS;
+    int base = 0, cnt = 0;
+    for (int l = 0; l <= L; ++l) {
+      base += 2 * cnt;
+      cnt = A.lay[2 * HT_MAX_LAYERS + l];
+    }
+    const int2 v = *reinterpret_cast<const int2*>(A.bkt + L * kBuckets + 2 * tid);
+    int c0 = v.x, c1 = v.y;
+    put_row(A, L, base, cnt, c0, c1, wsum);
+    return;
+  }
+  const int n = hits_of(A);
+  class_init(C);
+  for (int b = tid; b < kBuckets; b += kScanThreads) cnt_b[b] = 0;
+  __syncthreads();
+  // kLoads hits per thread in flight: the passes are bound by the loads' latency
+  constexpr int kLoads = 8;
+  int key[kLoads];
+  float r[kLoads];
+  const auto load = [&](int h0) {
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      const int h = h0 + tid + u * kScanThreads;
+      key[u] = h < n ? A.hkey[h] : -1;  // (bcount's: the eligible hits)
+      r[u] = h < n ? A.r[h] : 0.0f;
+    }
+  };
+  // (64 hits tell an event of many radii from one of few)
+  if (tid < kWave && tid < n && A.hkey[tid] >= 0) class_add(C, A.r[tid]);
+  __syncthreads();
+  for (int h0 = 0; h0 < n && class_found(C) <= kMaxRadii; h0 += kLoads * kScanThreads) {
+    load(h0);
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+      if (key[u] >= 0) class_add(C, r[u]);
+  }
+  const int ncls = class_order(C);
+  if (L == 0 && tid == 0) A.sc[S_MODE] = ncls <= kMaxRadii ? MODE_CLASSES : MODE_SWEEP;
+  if (ncls > kMaxRadii) return;
+  const float rL = C.r[L];
+  int below = 0, mine = 0;  // hits of smaller radii and of this class
+  for (int h0 = 0; h0 < n; h0 += kLoads * kScanThreads) {
+    load(h0);
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) {
+      if (key[u] < 0) continue;
+      below += r[u] < rL ? 1 : 0;
+      if (r[u] == rL) {
+        ++mine;
+        const int b = key[u] & (kBuckets - 1);
+        A.hkey[h0 + tid + u * kScanThreads] = class_key(L, b, atomicAdd(&cnt_b[b], 1));
+      }
+    }
+  }
+  if (below) atomicAdd(&C.cnt[0], below);
+  if (mine) atomicAdd(&C.cnt[1], mine);
+  __syncthreads();
+  const int cnt = C.cnt[1];
+  if (tid == 0) {
+    A.cls[L] = A.cls[HT_MAX_LAYERS + L] = __float_as_int(rL);
+    A.cls[2 * HT_MAX_LAYERS + L] = cnt;
+  }
+  int c0 = cnt_b[2 * tid], c1 = cnt_b[2 * tid + 1];
+  put_row(A, L, 2 * C.cnt[0], cnt, c0, c1, wsum);
+}
+
 // the hits' records in bucket order, both copies; events that take the sweep get
 // their member counts cleared instead
 template <int NB>
 __global__ __launch_bounds__(256) void bscatter_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
-  if (A.sc[S_MODE] == 0) {
+  const bool classes = A.sc[S_MODE] == MODE_CLASSES;
+  if (A.sc[S_MODE] == MODE_SWEEP) {
     const int np = n_cands(A);
     for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < np; q += gridDim.x * blockDim.x)
       A.mcount[q] = 0;
@@ -564,9 +710,14 @@ __global__ __launch_bounds__(256) void bscatter_kernel(AssocBatch<NB> AB) {
   for (int h = blockIdx.x * blockDim.x + threadIdx.x; h < n; h += gridDim.x * blockDim.x) {
     const int key = A.hkey[h];
     if (key < 0) continue;
-    const int L = (key & (kBucketKeys - 1)) / kBuckets, b = key & (kBuckets - 1);
-    const int e = A.bkt_off[L * kRunRow + b] + (key >> 15);
-    put_records(A, h, e, A.lay[2 * HT_MAX_LAYERS + L], A.hx[h], A.hy[h], A.hq[h], A.hitB[h]);
+    const int L = classes ? key >> 27 : (key & (kBucketKeys - 1)) / kBuckets;
+    const int slot = classes ? (key >> 11) & 0xffff : key >> 15;
+    const int e = A.bkt_off[L * kRunRow + (key & (kBuckets - 1))] + slot;
+    const int cnt = (classes ? A.cls : A.lay)[2 * HT_MAX_LAYERS + L];
+    if (classes)
+      put_class_records(A, h, e, cnt, A.hitB[h].w);
+    else
+      put_records(A, h, e, cnt, A.hx[h], A.hy[h], A.hq[h], A.hitB[h]);
   }
 }
 
@@ -584,6 +735,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_small_kernel(AssocBatch<NB>
   __shared__ uint32_t cnt2[kBucketKeys / 2];  // bucket counts, then starts within the layer, two a word
   __shared__ int32_t lo[HT_MAX_LAYERS], hi[HT_MAX_LAYERS], cnt[HT_MAX_LAYERS];
   __shared__ int32_t nbad;
+  __shared__ ClassSet C;
   if (blockIdx.x > 0) {
     prep_clear(A, surv_groups, (int64_t)(blockIdx.x - 1) * kPrepThreads + threadIdx.x,
                (int64_t)(gridDim.x - 1) * kPrepThreads);
@@ -624,19 +776,50 @@ __global__ __launch_bounds__(kPrepThreads) void prep_small_kernel(AssocBatch<NB>
     key[u] = b | ((int)((old >> sh) & 0xffffu) << 15);
   }
   __syncthreads();
-  bool on;
+  int mode;
   {
     const int L = lane & (HT_MAX_LAYERS - 1);
     const bool wide = cnt[L] > 0 && !(__int_as_float(hi[L]) <= kLayerSpread * __int_as_float(lo[L]));
-    on = __ballot(wide) == 0ull;
+    mode = __ballot(wide) == 0ull ? MODE_RUNS : MODE_CLASSES;
   }
   if (tid < 3 * HT_MAX_LAYERS)
     A.lay[tid] = tid < HT_MAX_LAYERS ? lo[tid]
                                      : (tid < 2 * HT_MAX_LAYERS ? hi[tid - HT_MAX_LAYERS]
                                                                 : cnt[tid - 2 * HT_MAX_LAYERS]);
+  if (mode == MODE_CLASSES) {
+    // the same sort with the radius classes as its rows
+    __syncthreads();
+    class_init(C);
+    for (int w = tid; w < kBucketKeys / 2; w += kPrepThreads) cnt2[w] = 0u;
+    if (tid < HT_MAX_LAYERS) cnt[tid] = 0;
+    __syncthreads();
+    if (wave == 0 && key[0] >= 0) class_add(C, rec[0].z);  // (as in bscan_kernel)
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (key[u] >= 0) class_add(C, rec[u].z);
+    if (class_order(C) > kMaxRadii) mode = MODE_SWEEP;
+    if (mode == MODE_CLASSES) {
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        if (key[u] < 0) continue;
+        const int c = class_of(C, rec[u].z);
+        const int b = c * kBuckets + (key[u] & (kBuckets - 1));
+        const int sh = (b & 1) * 16;
+        const uint32_t old = atomicAdd(&cnt2[b >> 1], 1u << sh);
+        key[u] = b | ((int)((old >> sh) & 0xffffu) << 15);
+        atomicAdd(&cnt[c], 1);
+      }
+      __syncthreads();
+      if (tid < HT_MAX_LAYERS) {
+        A.cls[tid] = A.cls[HT_MAX_LAYERS + tid] = __float_as_int(C.r[tid]);
+        A.cls[2 * HT_MAX_LAYERS + tid] = cnt[tid];
+      }
+    }
+  }
   if (tid < 16)
-    A.sc[tid] = tid == S_NP ? peaks_of(A) : (tid == S_MODE ? (on ? 1 : 0) : (tid == S_NBAD ? nbad : 0));
-  if (!on) {
+    A.sc[tid] = tid == S_NP ? peaks_of(A) : (tid == S_MODE ? mode : (tid == S_NBAD ? nbad : 0));
+  if (mode == MODE_SWEEP) {
     const int np = peaks_of(A);
     for (int p = tid; p < np; p += kPrepThreads) A.mcount[p] = 0;
     return;
@@ -674,7 +857,232 @@ __global__ __launch_bounds__(kPrepThreads) void prep_small_kernel(AssocBatch<NB>
     int base = 0;
     for (int l = 0; l < L; ++l) base += 2 * cnt[l];
     const int e = base + (int)((cnt2[k >> 1] >> ((k & 1) * 16)) & 0xffffu) + (key[u] >> 15);
-    put_records(A, tid + u * kPrepThreads, e, cnt[L], x[u], y[u], q[u], rec[u]);
+    const int h = tid + u * kPrepThreads;
+    if (mode == MODE_RUNS)
+      put_records(A, h, e, cnt[L], x[u], y[u], q[u], rec[u]);
+    else
+      put_class_records(A, h, e, cnt[L], rec[u].w);
+  }
+}
+
+// what a workgroup keeps of the event's layers
+struct alignas(16) RunLayer {
+  float rhi, rm, irm, hw;      // largest and middle radius, 1 / rm, half the spread (0: one radius)
+  float irlo, rlo, e5;         // 1 / rlo, smallest radius, the window's hit part (one radius)
+  int32_t cnt;
+};
+
+// the event's layers as every workgroup keeps them (whole workgroup); returns the
+// largest radius
+__device__ __forceinline__ float load_layers(const AssocArgs& A, const int32_t* rows, RunLayer* T) {
+  if (threadIdx.x < HT_MAX_LAYERS) {
+    const int L = threadIdx.x;
+    const int cnt = rows[2 * HT_MAX_LAYERS + L];
+    const float lo = cnt ? __int_as_float(rows[L]) : 1.0f;
+    const float hi = cnt ? __int_as_float(rows[HT_MAX_LAYERS + L]) : 1.0f;
+    const float m = 0.5f * (lo + hi);
+    const float ilo = 1.0f / lo;
+    RunLayer t;
+    t.rlo = lo;
+    t.rhi = hi;
+    t.rm = lo == hi ? lo : m;
+    t.irm = lo == hi ? ilo : 1.0f / m;
+    t.hw = lo == hi ? 0.0f : 0.5f * (hi - lo) + 1e-6f * hi;  // the rounding of m included
+    t.irlo = ilo;
+    t.e5 = member_e5(lo, ilo, A.hd0, A.hk, A.invw);
+    t.cnt = cnt;
+    T[L] = t;
+  }
+  __syncthreads();
+  float rmax = 0.0f;
+  for (int L = 0; L < HT_MAX_LAYERS; ++L) rmax = T[L].cnt > 0 ? fmaxf(rmax, T[L].rhi) : rmax;
+  return bcastf(rmax, 0);
+}
+
+// one layer's run for the candidate at cell lin (-1: none), on the lane that
+// calls it
+struct LayerRun {
+  float s, w;  // layers of one radius: arcsine (NaN: no votes) and window
+  int c0, nb;  // first bucket and bucket count
+  int st, len; // first hit and hit count
+  int i, col;  // the candidate's cell in its column, and the column
+  bool wide;   // several radii
+};
+__device__ __forceinline__ LayerRun layer_run(const AssocArgs& A, const RunLayer& t, int L,
+                                              int lin) {
+  LayerRun R;
+  R.s = __builtin_nanf("");
+  R.w = 0.0f;
+  R.c0 = R.nb = R.st = R.len = R.i = R.col = 0;
+  R.wide = false;
+  if (lin < 0) return R;
+  const int col = lin / A.n_phi;
+  const int i = lin - col * A.n_phi;
+  R.i = i;
+  R.col = col;
+  if (t.cnt <= 0) return R;
+  const float ck = A.kap[col % A.n_qpt], cq = A.qt[col], ct = A.tt[col];
+  const float wbase = 0.5f + (float)A.cfg.win_bins;
+  R.wide = t.hw > 0.0f;
+  bool have = false, all = false;
+  float slo = 0.0f, ds = 0.0f, w = 0.0f;
+  if (!R.wide) {
+    float x = 0.0f, u = 0.0f;
+    have = phi0_coord(t.rlo * t.rlo, t.irlo, 0.0f, ck, cq, ct, A.phi_lo, A.invw, &x, &u);
+    if (have) {
+      R.s = slo = asin_f(u);
+      R.w = w = member_window(t.e5, u, wbase);
+    }
+  } else {
+    // u over the layer's radii: within du of its value at the middle radius
+    const float um = ct * __builtin_fmaf(ck, t.rm, cq * t.irm);
+    const float slope = fabsf(ct) * (fabsf(ck) + fabsf(cq) * t.irlo * t.irlo);
+    const float du = slope * t.hw +
+                     1e-5f * fabsf(ct) * (fabsf(ck) * t.rhi + fabsf(cq) * t.irlo) + 1e-6f;
+    const float ulo = um - du, uhi = um + du;
+    const float ux = fmaxf(fabsf(ulo), fabsf(uhi));
+    have = !(ulo > 1.0f) && !(uhi < -1.0f);
+    all = !(ux <= 0.9995f);
+    if (have && !all) {
+      slo = asin_f(ulo);
+      ds = asin_f(uhi) - slo;
+      const float e5 = 1.0001f * A.invw * (A.hd0 * t.irlo + A.hk * t.rhi * 0.5f);
+      w = wbase + e5 * 1.5f * __builtin_amdgcn_rsqf(1.0f - ux * ux) * 1.001f;
+    }
+  }
+  if (have) {
+    // azimuths whose x lies within w of the cell centre, as bucket
+    // coordinates [lo, lo + len] (periodic), with a bucket of margin
+    const float binw = 1.0f / A.invw;
+    const float xc = (float)i + 0.5f;
+    const float a = ((xc - w) * binw + A.phi_lo) + slo;
+    const float lo = bucket_coord(wrap_pi_f(a)) - 1.0f;
+    const float len = (2.0f * w * binw + ds) * ((float)kBuckets / k2PiF) + 2.0f;
+    if (all || !(len < (float)(kBuckets - 2)) || !(lo == lo)) {
+      R.nb = kBuckets;
+    } else {
+      const int b0 = (int)floorf(lo);
+      R.nb = (int)floorf(lo + len) + 1 - b0;  // at most kBuckets
+      R.c0 = b0 < 0 ? b0 + kBuckets : (b0 >= kBuckets ? b0 - kBuckets : b0);
+    }
+    const int32_t* row = A.bkt_off + L * kRunRow;
+    R.st = row[R.c0];
+    R.len = row[R.c0 + R.nb] - R.st;
+  }
+  return R;
+}
+
+// The exact member test of hit e (azimuth ph) for the candidate at cell i of
+// column col, on a layer of arcsine s and window w (events with layers of
+// several radii: the hit's own); adx is the ranking key.
+__device__ __forceinline__ bool run_member(const AssocArgs& A, bool any_wide, int i, int col, int e,
+                                           float ph, float s, float w, float* adx) {
+  float x;
+  bool ok = true;
+  if (any_wide) {
+    const float4 h = A.srad[e];
+    float u = 0.0f;
+    x = 0.0f;
+    ok = phi0_coord(h.x * h.x, h.y, ph, A.kap[col % A.n_qpt], A.qt[col], A.tt[col], A.phi_lo,
+                    A.invw, &x, &u);
+    w = ok ? member_window(h.z, u, 0.5f + (float)A.cfg.win_bins) : -1.0f;
+  } else {
+    x = ((ph - s) - A.phi_lo) * A.invw;
+  }
+  *adx = cell_adx(x, i, A.n_phi);
+  return ok && *adx <= w;
+}
+
+// run of position t among the runs of a candidate's 16 lanes (from lane o), laid
+// end to end: the first that ends behind t
+__device__ __forceinline__ int run_of(int rend, int o, int t) {
+  int q = o;
+#pragma unroll
+  for (int step = HT_MAX_LAYERS / 2; step > 0; step >>= 1) {
+    const int end = __shfl(rend, q + step - 1, kWave);
+    if (end <= t) q += step;
+  }
+  return q;
+}
+
+// lane's share of a word of member bits m (positions t0 .. t0 + 63): the members
+// of its run, positions b .. e - 1
+__device__ __forceinline__ int run_share(uint64_t m, int t0, int b, int e) {
+  const int x = b > t0 ? b - t0 : 0, y = e - t0 < kWave ? e - t0 : kWave;
+  if (y <= x) return 0;
+  uint64_t f = m >> x;
+  if (y - x < kWave) f &= (1ull << (y - x)) - 1ull;
+  return __popcll(f);
+}
+
+// The member lists of an event by radius class, one wave (w of nw) per candidate, four
+// candidates' runs worked out at a time: the classes' runs laid end to end, their
+// hits tested with the sweep's own operations and the members written in order.
+// A list stops once it holds more than member_cap.  Whole workgroup.
+__device__ __forceinline__ void class_lists(const AssocArgs& A, RunLayer* T, int w, int nw) {
+  load_layers(A, A.cls, T);
+  const int lane = threadIdx.x & (kWave - 1);
+  const int np = n_cands(A), cap = A.cfg.member_cap;
+  const int32_t* words = class_words(A);
+  for (int p4 = w; p4 < np; p4 += 4 * nw) {
+    // lane 16 g + c: class c of candidate p4 + g nw
+    int lin_l = -1;
+    if (p4 + (lane >> 4) * nw < np) lin_l = A.peaks[p4 + (lane >> 4) * nw].lin;
+    if (lin_l >= A.n_cells) lin_l = -1;
+    const LayerRun R = layer_run(A, T[lane & 15], lane & 15, lin_l);
+    const int rend_l = row_scan_incl(R.len);
+    const int rbase = R.st - (rend_l - R.len);
+    for (int g = 0; g < 4; ++g) {
+      const int p = p4 + g * nw;
+      if (p >= np) break;
+      const int o = 16 * g;
+      const int total = bcasti(rend_l, o + HT_MAX_LAYERS - 1);
+      const int i = bcasti(R.i, o), col = bcasti(R.col, o);
+      uint2* pool = A.pool + (size_t)p * cap;
+      int n = 0;
+      const auto test = [&](bool in, float ph, int word, float s, float win) {
+        float adx = 0.0f;
+        const bool mem = in && run_member(A, false, i, col, 0, ph, s, win, &adx);
+        const uint64_t m = __ballot(mem);
+        const int slot = n + __popcll(m & ((1ull << lane) - 1ull));
+        if (mem && slot < cap) pool[slot] = make_uint2((unsigned)word, __float_as_uint(adx));
+        n += __popcll(m);
+      };
+      if (total > 3 * kWave) {
+        // dense: class by class (the lookup of a hit's run costs more than the partly
+        // filled last pass of each run)
+        for (unsigned cls = (unsigned)(__ballot(R.len > 0) >> o) & 0xffffu; cls && n <= cap;
+             cls &= cls - 1u) {
+          const int c = o + __builtin_ctz(cls);
+          const int st = bcasti(R.st, c), len = bcasti(R.len, c);
+          const float s = bcastf(R.s, c), win = bcastf(R.w, c);
+          for (int t0 = 0; t0 < len; t0 += 4 * kWave) {
+            float ph[4];  // four passes' loads in flight
+            int word[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const int e = st + min(t0 + u * kWave + lane, len - 1);
+              ph[u] = A.sphi[e];
+              word[u] = words[e];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (t0 + u * kWave < len)
+                test(t0 + u * kWave + lane < len, ph[u], word[u], s, win);
+          }
+        }
+      } else {
+        for (int t0 = 0; t0 < total; t0 += kWave) {
+          const int t = t0 + lane;
+          const int q = run_of(rend_l, o, t);
+          const int e = __shfl(rbase, q, kWave) + t;
+          const bool in = t < total;
+          test(in, in ? A.sphi[e] : 0.0f, in ? words[e] : 0, __shfl(R.s, q, kWave),
+               __shfl(R.w, q, kWave));
+        }
+      }
+      if (lane == 0) A.mcount[p] = n;
+    }
   }
 }
 
@@ -718,6 +1126,7 @@ struct SweepShared {
   float s_tab[kMaxRadii][kWave];
   float u_tab[kMaxRadii][kWave];
   float whi_tab[kMaxRadii][kWave];
+  RunLayer T[HT_MAX_LAYERS];  // events by radius class
 };
 
 // One pass over the workgroup's (hit, column) pairs; for every member
@@ -1016,7 +1425,13 @@ __global__ __launch_bounds__(kSweepThreads) void member_kernel(AssocBatch<NB> AB
   const int n_slices = gridDim.z / NB;
   const int slice = (int)blockIdx.z % n_slices;
   const AssocArgs& A = AB.a[NB == 1 ? 0 : (int)blockIdx.z / n_slices];
-  if (A.sc[S_MODE] != 0) return;  // the seed search reads the layer runs
+  if (A.sc[S_MODE] == MODE_RUNS) return;  // the seed search reads the layer runs
+  if (A.sc[S_MODE] == MODE_CLASSES) {
+    const int block = (slice * (int)gridDim.y + (int)blockIdx.y) * (int)gridDim.x + (int)blockIdx.x;
+    class_lists(A, S.T, block * kSweepWaves + (int)(threadIdx.x / kWave),
+                n_slices * (int)gridDim.y * (int)gridDim.x * kSweepWaves);
+    return;
+  }
   const int j0 = blockIdx.x * kWave;
   const int k = blockIdx.y;
   const int n_all = hits_of(A);
@@ -1353,6 +1768,11 @@ struct RefineShape {
   // be resident); else left to the compiler
   static constexpr int kMinWavesPerSimd =
       CAP <= 128 ? 7 : (CAP >= 1024 ? 2 : (CAP == 512 ? 4 : 1));
+  // Workgroups at most.  Twice as many even out the last ones (cap 256 on 16k hits of
+  // their own radii 1253 -> 1170 us, cap 1024 on 55k hits 3303 -> 3227, cap 128 on 3.6k
+  // hits 206 -> 198), and cost an event on the layer runs, for which they all return at
+  // once, 1.5 us: cap 128 is left with the fewer.
+  static constexpr int kGrid = CAP <= 128 ? kGridCap / 2 : kGridCap;
 };
 
 __device__ __forceinline__ void wave_sync() {
@@ -1425,15 +1845,6 @@ __device__ __forceinline__ double readlane_d(double v, int l) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// inclusive prefix sum within each row of 16 lanes (row_shr with zero fill)
-__device__ __forceinline__ int row_scan_incl(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-  return v;
-}
-
 // index of the n-th (0-based) set bit of a 16-bit mask
 __device__ __forceinline__ int nth_set_bit(unsigned mask, int n) {
   for (int L = 0; L < HT_MAX_LAYERS; ++L) {
@@ -1449,7 +1860,7 @@ template <int CAP, int NB>
 __global__ __launch_bounds__(RefineShape<CAP>::kWaves * kWave, RefineShape<CAP>::kMinWavesPerSimd) void
 refine_kernel(AssocBatch<NB> AB, int n_lo, int n_hi) {
   const AssocArgs& A = event_args(AB);
-  if (A.sc[S_MODE] != 0) return;  // the seed search reads the layer runs
+  if (A.sc[S_MODE] == MODE_RUNS) return;  // the seed search reads the layer runs
   constexpr int W = RefineShape<CAP>::kWaves;
   // members per chunk of the road loop (registers: 4 per member); the
   // short member lists of caps up to 128 keep one member at a time, which
@@ -2119,13 +2530,6 @@ struct RunShared {
   double2 sxy[3][4];
 };
 
-// what a workgroup keeps of the event's layers
-struct alignas(16) RunLayer {
-  float rhi, rm, irm, hw;      // largest and middle radius, 1 / rm, half the spread (0: one radius)
-  float irlo, rlo, e5;         // 1 / rlo, smallest radius, the window's hit part (one radius)
-  int32_t cnt;
-};
-
 // arccosine for |x| <= 1, Abramowitz & Stegun 4.4.45 (error below 7e-5)
 __device__ __forceinline__ float acos_coarse(float x) {
   const float a = fabsf(x);
@@ -2168,149 +2572,6 @@ __device__ __forceinline__ int wave_argmin(int a, int b) {
     tie = __ballot(a == m && b == mb);
   }
   return __builtin_ctzll(tie);
-}
-
-// the event's layers as every workgroup keeps them (whole workgroup); returns the
-// largest radius
-__device__ __forceinline__ float load_layers(const AssocArgs& A, RunLayer* T) {
-  if (threadIdx.x < HT_MAX_LAYERS) {
-    const int L = threadIdx.x;
-    const int cnt = A.lay[2 * HT_MAX_LAYERS + L];
-    const float lo = cnt ? __int_as_float(A.lay[L]) : 1.0f;
-    const float hi = cnt ? __int_as_float(A.lay[HT_MAX_LAYERS + L]) : 1.0f;
-    const float m = 0.5f * (lo + hi);
-    const float ilo = 1.0f / lo;
-    RunLayer t;
-    t.rlo = lo;
-    t.rhi = hi;
-    t.rm = lo == hi ? lo : m;
-    t.irm = lo == hi ? ilo : 1.0f / m;
-    t.hw = lo == hi ? 0.0f : 0.5f * (hi - lo) + 1e-6f * hi;  // the rounding of m included
-    t.irlo = ilo;
-    t.e5 = member_e5(lo, ilo, A.hd0, A.hk, A.invw);
-    t.cnt = cnt;
-    T[L] = t;
-  }
-  __syncthreads();
-  float rmax = 0.0f;
-  for (int L = 0; L < HT_MAX_LAYERS; ++L) rmax = T[L].cnt > 0 ? fmaxf(rmax, T[L].rhi) : rmax;
-  return bcastf(rmax, 0);
-}
-
-// one layer's run for the candidate at cell lin (-1: none), on the lane that
-// calls it
-struct LayerRun {
-  float s, w;  // layers of one radius: arcsine (NaN: no votes) and window
-  int c0, nb;  // first bucket and bucket count
-  int st, len; // first hit and hit count
-  int i, col;  // the candidate's cell in its column, and the column
-  bool wide;   // several radii
-};
-__device__ __forceinline__ LayerRun layer_run(const AssocArgs& A, const RunLayer& t, int L,
-                                              int lin) {
-  LayerRun R;
-  R.s = __builtin_nanf("");
-  R.w = 0.0f;
-  R.c0 = R.nb = R.st = R.len = R.i = R.col = 0;
-  R.wide = false;
-  if (lin < 0) return R;
-  const int col = lin / A.n_phi;
-  const int i = lin - col * A.n_phi;
-  R.i = i;
-  R.col = col;
-  if (t.cnt <= 0) return R;
-  const float ck = A.kap[col % A.n_qpt], cq = A.qt[col], ct = A.tt[col];
-  const float wbase = 0.5f + (float)A.cfg.win_bins;
-  R.wide = t.hw > 0.0f;
-  bool have = false, all = false;
-  float slo = 0.0f, ds = 0.0f, w = 0.0f;
-  if (!R.wide) {
-    float x = 0.0f, u = 0.0f;
-    have = phi0_coord(t.rlo * t.rlo, t.irlo, 0.0f, ck, cq, ct, A.phi_lo, A.invw, &x, &u);
-    if (have) {
-      R.s = slo = asin_f(u);
-      R.w = w = member_window(t.e5, u, wbase);
-    }
-  } else {
-    // u over the layer's radii: within du of its value at the middle radius
-    const float um = ct * __builtin_fmaf(ck, t.rm, cq * t.irm);
-    const float slope = fabsf(ct) * (fabsf(ck) + fabsf(cq) * t.irlo * t.irlo);
-    const float du = slope * t.hw +
-                     1e-5f * fabsf(ct) * (fabsf(ck) * t.rhi + fabsf(cq) * t.irlo) + 1e-6f;
-    const float ulo = um - du, uhi = um + du;
-    const float ux = fmaxf(fabsf(ulo), fabsf(uhi));
-    have = !(ulo > 1.0f) && !(uhi < -1.0f);
-    all = !(ux <= 0.9995f);
-    if (have && !all) {
-      slo = asin_f(ulo);
-      ds = asin_f(uhi) - slo;
-      const float e5 = 1.0001f * A.invw * (A.hd0 * t.irlo + A.hk * t.rhi * 0.5f);
-      w = wbase + e5 * 1.5f * __builtin_amdgcn_rsqf(1.0f - ux * ux) * 1.001f;
-    }
-  }
-  if (have) {
-    // azimuths whose x lies within w of the cell centre, as bucket
-    // coordinates [lo, lo + len] (periodic), with a bucket of margin
-    const float binw = 1.0f / A.invw;
-    const float xc = (float)i + 0.5f;
-    const float a = ((xc - w) * binw + A.phi_lo) + slo;
-    const float lo = bucket_coord(wrap_pi_f(a)) - 1.0f;
-    const float len = (2.0f * w * binw + ds) * ((float)kBuckets / k2PiF) + 2.0f;
-    if (all || !(len < (float)(kBuckets - 2)) || !(lo == lo)) {
-      R.nb = kBuckets;
-    } else {
-      const int b0 = (int)floorf(lo);
-      R.nb = (int)floorf(lo + len) + 1 - b0;  // at most kBuckets
-      R.c0 = b0 < 0 ? b0 + kBuckets : (b0 >= kBuckets ? b0 - kBuckets : b0);
-    }
-    const int32_t* row = A.bkt_off + L * kRunRow;
-    R.st = row[R.c0];
-    R.len = row[R.c0 + R.nb] - R.st;
-  }
-  return R;
-}
-
-// The exact member test of hit e (azimuth ph) for the candidate at cell i of
-// column col, on a layer of arcsine s and window w (events with layers of
-// several radii: the hit's own); adx is the ranking key.
-__device__ __forceinline__ bool run_member(const AssocArgs& A, bool any_wide, int i, int col, int e,
-                                           float ph, float s, float w, float* adx) {
-  float x;
-  bool ok = true;
-  if (any_wide) {
-    const float4 h = A.srad[e];
-    float u = 0.0f;
-    x = 0.0f;
-    ok = phi0_coord(h.x * h.x, h.y, ph, A.kap[col % A.n_qpt], A.qt[col], A.tt[col], A.phi_lo,
-                    A.invw, &x, &u);
-    w = ok ? member_window(h.z, u, 0.5f + (float)A.cfg.win_bins) : -1.0f;
-  } else {
-    x = ((ph - s) - A.phi_lo) * A.invw;
-  }
-  *adx = cell_adx(x, i, A.n_phi);
-  return ok && *adx <= w;
-}
-
-// run of position t among the runs of a candidate's 16 lanes (from lane o), laid
-// end to end: the first that ends behind t
-__device__ __forceinline__ int run_of(int rend, int o, int t) {
-  int q = o;
-#pragma unroll
-  for (int step = HT_MAX_LAYERS / 2; step > 0; step >>= 1) {
-    const int end = __shfl(rend, q + step - 1, kWave);
-    if (end <= t) q += step;
-  }
-  return q;
-}
-
-// lane's share of a word of member bits m (positions t0 .. t0 + 63): the members
-// of its run, positions b .. e - 1
-__device__ __forceinline__ int run_share(uint64_t m, int t0, int b, int e) {
-  const int x = b > t0 ? b - t0 : 0, y = e - t0 < kWave ? e - t0 : kWave;
-  if (y <= x) return 0;
-  uint64_t f = m >> x;
-  if (y - x < kWave) f &= (1ull << (y - x)) - 1ull;
-  return __popcll(f);
 }
 
 // seed layers: innermost, middle and outermost of the outer min(nS, min_layers)
@@ -2406,14 +2667,14 @@ template <int NB>
 __global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args_late(AB);
   const int np = n_cands(A);
-  if (A.sc[S_MODE] == 0 || np < kFewCands || (int)blockIdx.x * kRunWaves >= np) return;
+  if (A.sc[S_MODE] != MODE_RUNS || np < kFewCands || (int)blockIdx.x * kRunWaves >= np) return;
   __shared__ RejectShared RS[kRunWaves];
   __shared__ RunLayer T[HT_MAX_LAYERS];
   __shared__ unsigned long long tot[kRunWaves][5];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   RejectShared& S = RS[wave];
-  const float rmax = load_layers(A, T);
+  const float rmax = load_layers(A, A.lay, T);
   const ht_cluster_cfg& cfg = A.cfg;
   const double road = (double)cfg.road_sigmas * (double)cfg.sigma_rphi;
   double ktol = (0.5 + (double)cfg.box_margin) * A.kap_bin;
@@ -2591,7 +2852,7 @@ __global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch
 template <int NB>
 __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args_late(AB);
-  if (A.sc[S_MODE] == 0) return;
+  if (A.sc[S_MODE] != MODE_RUNS) return;
   __shared__ RunShared RS[kRunWaves];
   __shared__ RunLayer T[HT_MAX_LAYERS];
   __shared__ unsigned long long tot[kRunWaves][5];
@@ -2617,7 +2878,7 @@ __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<N
   };
   next_pending();
   if (!__syncthreads_or(qi < nq || pend != 0)) return;  // nothing for this workgroup
-  load_layers(A, T);
+  load_layers(A, A.lay, T);
   const ht_cluster_cfg& cfg = A.cfg;
   const int cap = cfg.member_cap;
   const double road = (double)cfg.road_sigmas * (double)cfg.sigma_rphi;
@@ -3947,8 +4208,8 @@ template <int CAP, int NB>
 void launch_refine(const AssocBatch<NB>& AB, int peak_cap, hipStream_t s, int n_lo = 0,
                    int n_hi = 0x7fffffff) {
   constexpr int W = RefineShape<CAP>::kWaves;
-  const int blocks = blocks_for(peak_cap, W);
-  refine_kernel<CAP, NB><<<dim3(blocks < kSweepGrid ? blocks : kSweepGrid, 1, NB), W * kWave, 0, s>>>(AB, n_lo, n_hi);
+  const int blocks = blocks_for(peak_cap, W), most = RefineShape<CAP>::kGrid;
+  refine_kernel<CAP, NB><<<dim3(blocks < most ? blocks : most, 1, NB), W * kWave, 0, s>>>(AB, n_lo, n_hi);
 }
 
 // The arguments of one event's assoc_cluster.
@@ -4014,6 +4275,7 @@ AssocArgs make_args(const Plan& P, const float* r, const float* phi, const uint8
   A.sc = P.d_scalars;
   A.spread = P.d_spread;
   A.lay = P.d_lay;
+  A.cls = P.d_lay + 3 * HT_MAX_LAYERS;
   A.bkt = P.d_bkt;
   A.bkt_off = P.d_bkt_off;
   A.hkey = P.d_hkey;
@@ -4056,7 +4318,7 @@ int assoc_sequence(const AssocBatch<NB>& AB, const Plan* const* P, int32_t n_hit
     P0.prof_mark(HT_STAGE_MEMBERS, 0, s);
     bcount_kernel<NB><<<hgrid, 256, 0, s>>>(AB);
     HT_CHECK(hipGetLastError());
-    bscan_kernel<NB><<<dim3(HT_MAX_LAYERS, 1, NB), 256, 0, s>>>(AB);
+    bscan_kernel<NB><<<dim3(HT_MAX_LAYERS, 1, NB), kScanThreads, 0, s>>>(AB);
     HT_CHECK(hipGetLastError());
     bscatter_kernel<NB><<<hgrid, 256, 0, s>>>(AB);
     HT_CHECK(hipGetLastError());

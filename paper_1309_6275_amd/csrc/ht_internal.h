@@ -87,7 +87,8 @@ struct Plan {
   int32_t* d_scalars;    // [16] device counters
   unsigned long long* d_spread;  // [kSpreadWords] counters spread over 128-byte lines
   // layer runs
-  int32_t* d_lay;       // [3 HT_MAX_LAYERS] smallest and largest radius (float bits), hits of each layer
+  int32_t* d_lay;       // [6 HT_MAX_LAYERS] smallest and largest radius (float bits), hits of each
+                        // layer, then the same of each radius class
   int32_t* d_bkt;       // [kBucketKeys] hits per (layer, bucket)
   int32_t* d_bkt_off;   // [HT_MAX_LAYERS][kRunRow] bucket starts in the records below
   int32_t* d_hkey;      // [max_hits] bucket key | slot << 15 of each hit, -1 if none
