@@ -265,8 +265,8 @@ int hough_peaks_noalloc(const ht_grid* grid, const int32_t* acc, int32_t min_vot
  *   acc            NULL, or the accumulator hough_vote (or hough_vote_n)
  *                  wrote for these hits with this plan (device, read only).
  *                  Results are the same either way; with it, a candidate
- *                  whose member count provably exceeds member_cap is dropped
- *                  before the member search: every valid hit with a layer
+ *                  whose member count provably exceeds member_cap can be
+ *                  dropped before the member search: every valid hit with a layer
  *                  below HT_MAX_LAYERS that votes within win_bins bins of
  *                  the cell in its column is a member, so the votes of those
  *                  2 win_bins + 1 cells, less the valid hits of higher

@@ -1768,11 +1768,11 @@ struct RefineShape {
   // be resident); else left to the compiler
   static constexpr int kMinWavesPerSimd =
       CAP <= 128 ? 7 : (CAP >= 1024 ? 2 : (CAP == 512 ? 4 : 1));
-  // Workgroups at most.  Twice as many even out the last ones (cap 256 on 16k hits of
-  // their own radii 1253 -> 1170 us, cap 1024 on 55k hits 3303 -> 3227, cap 128 on 3.6k
-  // hits 206 -> 198), and cost an event on the layer runs, for which they all return at
-  // once, 1.5 us: cap 128 is left with the fewer.
-  static constexpr int kGrid = CAP <= 128 ? kGridCap / 2 : kGridCap;
+  // Workgroups at most.  On large lists twice as many even out the last ones for cap
+  // 256 (16k hits of their own radii 1253 -> 1170 us) and 1024 (55k hits 3303 -> 3227), not
+  // for 512 (1113 -> 1108) and hardly for 128 (3.6k hits 206 -> 198); an event on the layer
+  // runs, for which they all return at once, pays 1.5 us for them.
+  static constexpr bool kMoreOnLarge = CAP == 256 || CAP == 1024;
 };
 
 __device__ __forceinline__ void wave_sync() {
@@ -2849,6 +2849,21 @@ __global__ __launch_bounds__(kRunWaves * kWave, 8) void reject_kernel(AssocBatch
   add_totals<kRunWaves>(A, tot);
 }
 
+// The lane's part of the votes in the 2 win_bins + 1 cells around cell i of column col
+// (the 16 lanes of a candidate call it): their sum, less the valid hits of higher layers,
+// is a lower bound of the candidate's member count (see drop_overfull).
+__device__ __forceinline__ int votes_around(const AssocArgs& A, int i, int col) {
+  int sum = 0;
+  const int b = A.cfg.win_bins;
+  const int32_t* row = A.acc + (size_t)col * A.n_phi;
+  for (int d = (int)(threadIdx.x & 15) - b; d <= b; d += 16) {
+    int ii = i + d;  // |d| < n_phi / 4: one period of correction
+    ii = ii < 0 ? ii + A.n_phi : (ii >= A.n_phi ? ii - A.n_phi : ii);
+    sum += row[ii];
+  }
+  return sum;
+}
+
 template <int NB>
 __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args_late(AB);
@@ -2912,18 +2927,39 @@ __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<N
         }
       }
       const int g4 = lane >> 4;
-      const int pl4 = g4 == 0 ? pg[0] : (g4 == 1 ? pg[1] : (g4 == 2 ? pg[2] : pg[3]));
+      int pl4 = g4 == 0 ? pg[0] : (g4 == 1 ? pg[1] : (g4 == 2 ? pg[2] : pg[3]));
       int lin_l = -1;
       if (pl4 >= 0) lin_l = A.peaks[pl4].lin;
       if (lin_l >= A.n_cells) lin_l = -1;
       const LayerRun R = layer_run(A, T[lane & 15], lane & 15, lin_l);
       const bool any_wide = __ballot(R.wide) != 0ull;
       const int rend_l = row_scan_incl(R.len);  // end of layer L's run, the runs laid end to end
+      // Candidates over member_cap by their votes, looked up where the runs hold so many
+      // hits that a third of them in the middle would prove it: done, marked by -2.  (55k
+      // hits, cap 128: assoc_cluster 234 -> 170 us, cap 256: 277 -> 253; asked for
+      // every candidate, 31k hits at cap 256 took 842 us a pass for 826: few are proven.)
+      if (A.acc) {
+        const bool ask = __shfl(rend_l, 15, 16) > 3 * cap;
+        if (__ballot(ask)) {
+          const int votes = __shfl(row_scan_incl(ask ? votes_around(A, R.i, R.col) : 0), 15, 16);
+          if (votes > cap + A.sc[S_NBAD]) {
+            if ((lane & 15) == 0) {
+              A.cstat[pl4] = -2;
+              A.cnl[pl4] = 0;
+              atomicAdd(&tot[wave][2], 1ull);
+            }
+            pl4 = -2;
+          }
+        }
+      }
 #pragma unroll 1
       for (int g = 0; g < 4; ++g) {
         const int o = 16 * g;  // the candidate's first lane
         const int p = bcasti(pl4, o);
-        if (p < 0) break;
+        if (p < 0) {
+          if (p == -1) break;
+          continue;  // over member_cap by its votes
+        }
         const int i = bcasti(R.i, o), col = bcasti(R.col, o);
         wave_sync();  // (the previous candidate's LDS is read)
         // ---- members: a bit for each run hit, and their counts
@@ -4208,7 +4244,8 @@ template <int CAP, int NB>
 void launch_refine(const AssocBatch<NB>& AB, int peak_cap, hipStream_t s, int n_lo = 0,
                    int n_hi = 0x7fffffff) {
   constexpr int W = RefineShape<CAP>::kWaves;
-  const int blocks = blocks_for(peak_cap, W), most = RefineShape<CAP>::kGrid;
+  const int blocks = blocks_for(peak_cap, W);
+  const int most = RefineShape<CAP>::kMoreOnLarge && peak_cap > 1 << 20 ? kGridCap : kGridCap / 2;
   refine_kernel<CAP, NB><<<dim3(blocks < most ? blocks : most, 1, NB), W * kWave, 0, s>>>(AB, n_lo, n_hi);
 }
 
