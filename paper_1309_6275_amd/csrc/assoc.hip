@@ -3206,8 +3206,10 @@ __global__ __launch_bounds__(kRunWaves * kWave, 5) void runs_kernel(AssocBatch<N
           const int32_t* row = A.bkt_off + L * kRunRow + c0;
           const int nb = bcasti(R.nb, o + L);
           const bool tab = nb < kTab && len > kScanAll;
-          if (tab)
+          if (tab) {
             for (int q = lane; q <= nb; q += kWave) S.tab[q] = (uint16_t)(row[q] - st);
+            wave_sync();  // every lane reads other lanes' entries below
+          }
           // hits [g0, g0 + kStage) of a long run into LDS
           auto stage = [&](int g0) {
             wave_sync();
