@@ -9,10 +9,11 @@ displaced-jet workload (~3.6k hits, 16 events per step) is measured after it
 and reported under its own key.  Prints one JSON line: whole-job Hough
 votes/s (value), events/s, p50/p99 event latency, track efficiency and fake
 rate of the outputs, the roofline of the dominant kernel and of the vote
-kernel (the operations each kernel actually executed, against the published
-MI355X vector peak of its precision; the library's HIP-event stage timers on
-the launch stream give the kernel times), and the CPU oracle timed on a
-bounded sample on the host cores.
+kernel (the vote: the operations it executed, against the published MI355X
+vector peak of its precision; the seed search, which is bound by instruction
+issue: the vector instructions counted for it, against the issue rate; the
+library's HIP-event stage timers on the launch stream give the kernel times),
+and the CPU oracle timed on a bounded sample on the host cores.
 
     python bench.py [--steps K] [--warmup W] [--batch B] [--workload 1|2|3]
                     [--second-workload 0|1|2|3]
@@ -50,6 +51,9 @@ FP64_PEAK_TFLOPS = 78.6
 # single-issue rate of plain (not fused, not packed) vector operations:
 # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, reported beside the published peaks
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
+# vector instructions: one wave64 instruction every four cycles on each of the
+# 256 x 4 SIMDs (additions and multiply-adds issue faster)
+ISSUE_PEAK_GIPS = 256 * 4 * 2.4e9 / 4 / 1e9
 HBM_PEAK_GBS = 8000.0
 # events per step and CPU-oracle events per workload
 DEFAULT_BATCH = {1: 64, 2: 16, 3: 4}
@@ -116,7 +120,7 @@ def copy_calibration():
 
 # the sources a kernel's code comes from (plan and launch code excluded)
 KERNEL_SOURCES = {"vote": ("vote.hip", "ht_device.h"),
-                  "refine": ("assoc.hip", "ht_device.h")}
+                  "refine": ("assoc.hip", "run_search.h", "ht_device.h")}
 
 
 def kernel_source_sha(kernel):
@@ -127,9 +131,10 @@ def kernel_source_sha(kernel):
     return h.hexdigest()[:16]
 
 
-def traffic_from_profile(kernel, workload):
-    """HBM bytes per launch of `kernel` from the committed rocprofv3 counter
-    summary, if it was taken on the current source of that kernel."""
+def from_profile(kernel, workload, key):
+    """A figure per launch of `kernel` from the committed rocprofv3 counter
+    summary (HBM bytes, vector instructions), if it was taken on the current
+    source of that kernel."""
     path = os.path.join(ROOT, "profiles", f"{kernel}_cfg{workload}_hbm_counters.md")
     if not os.path.exists(path):
         return None
@@ -140,7 +145,7 @@ def traffic_from_profile(kernel, workload):
     d = json.loads(m.group(1))
     if d.get("kernel_source_sha") != kernel_source_sha(kernel):
         return None
-    return float(d["hbm_bytes_per_launch"])
+    return float(d[key]) if key in d else None
 
 
 def cpu_baseline(W, events, workload):
@@ -682,8 +687,9 @@ def measure(args, workload, B, steps, warmup, cpu_events, concurrent):
     #  16 distinct radii of its workgroup) computes u, the |u| test and the
     #  arcsine once per (radius, column), 27 fp32 operations, and per vote
     #  x = ((phi - s) - PHI_LO) * INVW and the floor, 4 operations.
-    #  refine: 13 fp64 operations per float64 circle distance the kernel
-    #  computed (work[1]); the float32 pre-filter is not counted.
+    #  refine: the vector instructions that its counters hold for this workload
+    #  and source, and beside them 13 fp64 operations per float64 circle distance
+    #  the kernels computed (work[1]); the float32 search is not in those.
     table_path = all(n <= 16 for n in radii)
     vote_exec = np.mean([(OPS_PER_EVAL + OPS_PER_VOTE) * n * ncol + 4 * V if table_path
                          else OPS_PER_EVAL * E + OPS_PER_VOTE * V
@@ -696,7 +702,8 @@ def measure(args, workload, B, steps, warmup, cpu_events, concurrent):
         t = avg_ms[kernel] / 1e3
         achieved = executed_ops / t / 1e12
         return {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
-                "frac": achieved / peak, "traffic": traffic_from_profile(kernel, workload),
+                "frac": achieved / peak,
+                "traffic": from_profile(kernel, workload, "hbm_bytes_per_launch"),
                 "kernel": f"{kernel}_kernel", "avg_launch_ms": avg_ms[kernel], "dtype": dtype,
                 "executed_ops_per_launch": executed_ops,
                 "method_ops_per_launch": method_ops,
@@ -706,8 +713,19 @@ def measure(args, workload, B, steps, warmup, cpu_events, concurrent):
 
     rl = {"vote": roofline("vote", vote_exec, vote_method, FP32_PEAK_TFLOPS, "f32"),
           "refine": roofline("refine", refine_exec, refine_method, FP64_PEAK_TFLOPS, "f64")}
+    rl["refine"]["kernel"] = "reject_kernel + runs_kernel"  # (refine_kernel returns at once)
+    valu = from_profile("refine", workload, "valu_instructions_per_launch")
+    if valu:
+        rate = valu / (avg_ms["refine"] / 1e3) / 1e9
+        old = rl["refine"]
+        rl["refine"] = dict(old, bound="issue", achieved=rate, peak=ISSUE_PEAK_GIPS,
+                            unit="G wave-instructions/s", frac=rate / ISSUE_PEAK_GIPS,
+                            dtype="f32+f64", valu_instructions_per_launch=valu,
+                            f64_tflops=old["achieved"], f64_frac=old["frac"])
+        for key in ("single_issue_peak", "frac_single_issue"):  # of float operations
+            del rl["refine"][key]
     # the dominant kernel by measured time among the timed kernels with an
-    # operation count (the member sweep has none of its own)
+    # operation count (the grouping of the hits has none of its own)
     dominant = max(("vote", "refine"), key=lambda k: avg_ms.get(k, 0.0))
 
     cpu = None

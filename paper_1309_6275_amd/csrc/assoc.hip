@@ -29,7 +29,7 @@
 //   fit+vvote one launch: float64 Gauss-Newton, one wave per track (lanes =
 //             hits), beside one thread per (track, vertex row) voting its
 //             crossing arcs into the vertex accumulator (the Kalman filter,
-//             one thread per track, runs as a launch of its own first);
+//             16 lanes per track, runs as a launch of its own first);
 //   vpeaks    vertex local maxima in cell order: counts per 1024-cell tile,
 //             then each tile places its own (vpcount, vpemit);
 //   vcount,   member counts, one wave per (object, 64 tracks), then one
@@ -619,7 +619,9 @@ __device__ __forceinline__ int class_key(int c, int b, int slot) { return c << 2
 // One workgroup per layer: its row of bucket starts, both copies of its hits.  Events
 // by radius class are counted here, a class per workgroup, by two passes over the
 // hits that ordinary events do not pay for; a workgroup rewrites the keys of its own
-// class (the others look at their sign only).
+// class (the others look at their sign only).  55k hits: 51 us with eight hits per
+// thread in flight (164 with one, and the records written by these workgroups too);
+// ordinary events 4.6 us.
 template <int NB>
 __global__ __launch_bounds__(kScanThreads) void bscan_kernel(AssocBatch<NB> AB) {
   const AssocArgs& A = event_args(AB);
@@ -1018,7 +1020,9 @@ __device__ __forceinline__ int run_share(uint64_t m, int t0, int b, int e) {
 // The member lists of an event by radius class, one wave (w of nw) per candidate, four
 // candidates' runs worked out at a time: the classes' runs laid end to end, their
 // hits tested with the sweep's own operations and the members written in order.
-// A list stops once it holds more than member_cap.  Whole workgroup.
+// A list stops once it holds more than member_cap.  Bound by the loads' latency (four
+// waves per SIMD beside the sweep's LDS): 55k hits, 231 thousand candidates 427 us, with
+// the hits' words gathered from the layer runs' records 506.  Whole workgroup.
 __device__ __forceinline__ void class_lists(const AssocArgs& A, RunLayer* T, int w, int nw) {
   load_layers(A, A.cls, T);
   const int lane = threadIdx.x & (kWave - 1);
@@ -1381,7 +1385,8 @@ __device__ void drop_overfull(const AssocArgs& A, SweepShared& S, int k, int j0,
 // lin1 - 1; entries outside the grid may stand anywhere in it.  The workgroup reads
 // one entry per thread, spread over the list, and then every entry between the
 // last one before lin0 and the first one from lin1 on: two rounds of loads (a binary
-// search by one thread takes 18, and an entry outside the grid misleads it).
+// search by one thread takes 18, and an entry outside the grid misleads it; 3.6k hits
+// of their own radii take 753 us in assoc_cluster either way).
 // p_lo > p_hi when there is none.  Whole workgroup; ends with a barrier.
 __device__ __forceinline__ void find_stretch(const AssocArgs& A, SweepShared& S, int64_t lin0,
                                              int64_t lin1) {
@@ -2484,11 +2489,11 @@ refine_kernel(AssocBatch<NB> AB, int n_lo, int n_hi) {
 // computed, for the lanes that can still win, instead of one per hit on the
 // road.
 //
-// Bound by VALU issue (rocprofv3: 78% of the SIMDs' issue cycles on 55k-hit
-// events, about all of them on events of smeared radii; some 550 instructions per
-// candidate in reject_kernel).  Member lists written to memory and read back,
-// gathered hit by hit, cost more than the search itself: with the hits sorted
-// once per event a candidate's members are contiguous runs.  Member lists and
+// Bound by VALU issue (rocprofv3: 90% of the issue rate on 55k-hit events, 91% in
+// reject_kernel on 3.6k-hit ones; some 550 instructions per candidate there).
+// Member lists written to memory and read back, gathered hit by hit, cost more
+// than the search itself: with the hits sorted once per event a candidate's
+// members are contiguous runs.  Member lists and
 // seed search per event, before and after, in ms: 55k hits on ten radii (member_cap
 // 1024) 4.84 -> 1.69; 3000 tracks with smeared radii (member sweep before) 11.9 ->
 // 3.2; 3.6k hits (cap 128) 0.41 -> 0.27; four 2.5k-hit events in a batch (cap 256)

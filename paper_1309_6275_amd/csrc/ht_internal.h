@@ -96,7 +96,7 @@ struct Plan {
   float4* d_srad;       // [2 max_hits] r, 1/r, the window's hit part
   float* d_sphi;        // [2 max_hits] azimuth
   double2* d_sxy;       // [2 max_hits] x, y
-  double* d_sq;         // [2 max_hits] x^2+y^2
+  double* d_sq;         // [2 max_hits] x^2+y^2; events by radius class: hit | layer << 16 (32 bits)
   // stage timing (ht_profile_*): HIP events recorded around the stages of
   // later calls; plan calls are ordered, so the counters need no locking
   mutable int32_t prof_depth;          // 0: off
